@@ -8,11 +8,16 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["raster.hip", "resolve.hip", "runtime.hip", "autotune.hip", "compress.hip"]
+# Translation units: (source, object name, macros).  The stage-1 fast kernel's variants of one
+# workgroup size and triangles per lane are a unit each, so that they compile in parallel.
+UNITS = [("raster.hip", f"raster_{b}_{t}", [f"-DCURAST_FAST_BLOCK={b}", f"-DCURAST_FAST_TPT={t}"])
+         for t in (8, 4, 2, 1) for b in (64, 128, 256, 512)]
+UNITS += [(f, f[:-4], []) for f in ("raster.hip", "resolve.hip", "runtime.hip", "autotune.hip", "compress.hip")]
 LIB = os.path.join(HERE, "libcurast.so")
 ARCH = os.environ.get("CURAST_OFFLOAD_ARCH", "gfx950")
 
@@ -33,28 +38,30 @@ FLAGS = [
 
 
 def build(verbose: bool = False) -> str:
-    objs = []
     build_dir = os.path.join(HERE, "_build")
     os.makedirs(build_dir, exist_ok=True)
-    procs = []
-    for src in SOURCES:
-        obj = os.path.join(build_dir, src.replace(".hip", ".o"))
-        cmd = [hipcc()] + [f for f in FLAGS if f != "-shared"] + ["-I", os.path.join(ROOT, "include"), "-c",
-                                                                  os.path.join(CSRC, src), "-o", obj]
+    objs = [os.path.join(build_dir, name + ".o") for _, name, _ in UNITS]
+
+    def compile_unit(unit, obj):
+        src, _, macros = unit
+        cmd = [hipcc()] + [f for f in FLAGS if f != "-shared"] + macros + [
+            "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
-        objs.append(obj)
+        return subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+    jobs = max(1, min(int(os.environ.get("MAX_JOBS", "0") or 0) or (os.cpu_count() or 1), 16))
+    with ThreadPoolExecutor(jobs) as pool:
+        results = list(pool.map(compile_unit, UNITS, objs))
     failed = []
-    for src, p in procs:
-        out, _ = p.communicate()
-        text = out.decode(errors="replace")
+    for (src, name, _), p in zip(UNITS, results):
+        text = p.stdout.decode(errors="replace")
         # the host pass does not know the packed-fp32 feature name; that warning is harmless
         lines = [ln for ln in text.splitlines() if "packed-fp32-ops" not in ln]
         if lines and (verbose or p.returncode):
             print("\n".join(lines), flush=True)
         if p.returncode:
-            failed.append(src)
+            failed.append(name)
     if failed:
         raise RuntimeError(f"hipcc failed for {failed}")
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs

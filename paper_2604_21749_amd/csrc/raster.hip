@@ -185,6 +185,7 @@ __device__ inline void raster_any_thread(const Clip c[3], uint64_t id, const Vie
     }
 }
 
+#ifndef CURAST_FAST_BLOCK
 // ----------------------------------------------------------------------------------------------
 // Clear (also resets the queue counters of the frame)
 // ----------------------------------------------------------------------------------------------
@@ -209,6 +210,8 @@ __global__ void __launch_bounds__(256) clear_kernel(RasterArgs a)
         }
     }
 }
+
+#endif  // CURAST_FAST_BLOCK
 
 // ----------------------------------------------------------------------------------------------
 // Stage 1: one lane per triangle, looping over the draws (instances x views) of its work item
@@ -1199,6 +1202,43 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
     st.flush(a.stats);
 }
 
+// The fast kernel's variants of one workgroup size and triangles per lane are a translation unit of
+// their own (this file compiled with CURAST_FAST_BLOCK and CURAST_FAST_TPT set), so that the sixteen of
+// them compile in parallel; the unit without the two macros holds everything else.
+template <int BLOCK, int TPT>
+hipError_t stage1_fast_strips(const RasterArgs& a, bool strips, bool spheres, bool stats, uint32_t grid,
+                              hipStream_t s);
+
+#ifdef CURAST_FAST_BLOCK
+// Launches whose meshes are all plain or all compressed use a kernel without the per-mesh
+// compression branch (Sec. 4.6 notes the same for its kernels); mixed launches decide per mesh.
+template <int BLOCK, int TPT, bool STRIPS, bool SPH>
+static hipError_t stage1_fast_dispatch(const RasterArgs& a, bool stats, uint32_t grid, hipStream_t s)
+{
+    // the statistics variants (a measurement aid) decide per mesh, which is right for any launch
+    const bool any = (a.compressed_parts >> a.part) & 1u, all = (a.compressed_parts >> (a.part + 8)) & 1u;
+    if (stats) stage1_fast_kernel<BLOCK, TPT, STRIPS, true, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    else if (all) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    else if (any) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    else stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 0, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    return hipGetLastError();
+}
+
+template <int BLOCK, int TPT>
+hipError_t stage1_fast_strips(const RasterArgs& a, bool strips, bool spheres, bool stats, uint32_t grid,
+                                     hipStream_t s)
+{
+    if constexpr (TPT == 1) return stage1_fast_dispatch<BLOCK, TPT, false, false>(a, stats, grid, s);
+    else if (!strips) return stage1_fast_dispatch<BLOCK, TPT, false, false>(a, stats, grid, s);
+    else return spheres ? stage1_fast_dispatch<BLOCK, TPT, true, true>(a, stats, grid, s)
+                   : stage1_fast_dispatch<BLOCK, TPT, true, false>(a, stats, grid, s);
+}
+
+template hipError_t stage1_fast_strips<CURAST_FAST_BLOCK, CURAST_FAST_TPT>(const RasterArgs&, bool, bool, bool, uint32_t,
+                                                                          hipStream_t);
+
+#else
+
 // ----------------------------------------------------------------------------------------------
 // Stage 1 with vertex sharing, for triangles drawn many times (instances x views).  One wavefront
 // per workgroup: it deduplicates the vertex indices of its 64*TPT triangles in an LDS hash table
@@ -1745,35 +1785,12 @@ hipError_t launch_stage1(const RasterArgs& a, uint32_t block, uint32_t tpt, bool
     }
 }
 
-// Launches whose meshes are all plain or all compressed use a kernel without the per-mesh
-// compression branch (Sec. 4.6 notes the same for its kernels); mixed launches decide per mesh.
-template <int BLOCK, int TPT, bool STRIPS, bool SPH>
-static hipError_t stage1_fast_dispatch(const RasterArgs& a, bool stats, uint32_t grid, hipStream_t s)
-{
-    // the statistics variants (a measurement aid) decide per mesh, which is right for any launch
-    const bool any = (a.compressed_parts >> a.part) & 1u, all = (a.compressed_parts >> (a.part + 8)) & 1u;
-    if (stats) stage1_fast_kernel<BLOCK, TPT, STRIPS, true, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else if (all) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else if (any) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 0, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    return hipGetLastError();
-}
-
-template <int BLOCK, int TPT>
-static hipError_t stage1_fast_strips(const RasterArgs& a, bool strips, bool spheres, bool stats, uint32_t grid,
-                                     hipStream_t s)
-{
-    if (!strips) return stage1_fast_dispatch<BLOCK, TPT, false, false>(a, stats, grid, s);
-    return spheres ? stage1_fast_dispatch<BLOCK, TPT, true, true>(a, stats, grid, s)
-                   : stage1_fast_dispatch<BLOCK, TPT, true, false>(a, stats, grid, s);
-}
-
 template <int BLOCK>
 static hipError_t stage1_fast_tpt(const RasterArgs& a, uint32_t tpt, bool strips, bool spheres, bool stats,
                                   uint32_t grid, hipStream_t s)
 {
     switch (tpt) {
-    case 1: return stage1_fast_dispatch<BLOCK, 1, false, false>(a, stats, grid, s);
+    case 1: return stage1_fast_strips<BLOCK, 1>(a, strips, spheres, stats, grid, s);
     case 2: return stage1_fast_strips<BLOCK, 2>(a, strips, spheres, stats, grid, s);
     case 4: return stage1_fast_strips<BLOCK, 4>(a, strips, spheres, stats, grid, s);
     case 8: return stage1_fast_strips<BLOCK, 8>(a, strips, spheres, stats, grid, s);
@@ -1839,5 +1856,7 @@ hipError_t launch_stage3(const RasterArgs& a, uint32_t grid, bool stats, hipStre
     else stage3_kernel<false><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
+
+#endif  // CURAST_FAST_BLOCK
 
 }  // namespace curast
