@@ -34,8 +34,9 @@ hipError_t launch_stage2(const RasterArgs& a, uint32_t grid, bool stats, hipStre
 hipError_t launch_stage3(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_stage3_binned(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_project(const MeshDesc& mesh, const float A[12], float hW, float hH, float* out, hipStream_t s);
-hipError_t launch_compress_ranges(const uint32_t* idx, uint64_t n_idx, const float* pos, uint32_t V, uint32_t* out,
-                                  uint32_t cus, hipStream_t s);
+uint64_t compress_range_words();
+hipError_t launch_compress_ranges(const uint32_t* idx, uint64_t n_idx, const float* pos, uint32_t V, uint32_t* part,
+                                  uint32_t* out, hipStream_t s);
 hipError_t launch_compress(const uint32_t* idx, uint64_t n_idx, uint32_t bits, uint32_t base, uint32_t* packed,
                            uint64_t words, const float* pos, uint32_t V, const float lo[3], const float scale[3],
                            uint16_t* qpos, hipStream_t s);
@@ -110,7 +111,8 @@ struct curast_ctx {
     double stage_ms[kNumSlots] = {0};
     uint64_t timed_frames = 0;
     uint64_t draws_culled = 0;
-    uint32_t* ranges = nullptr;   // [8] index range and bounding box of curast_compress_prepare
+    uint32_t* range_parts = nullptr;   // partial results of curast_compress_prepare's reductions
+    uint32_t* ranges = nullptr;        // [8] pinned: its index range and bounding box
     char* na_scratch = nullptr;   // this device's copy of the allocation-free form's scratch array
 };
 
@@ -1229,7 +1231,8 @@ int curast_destroy(curast_ctx* ctx)
     if (ctx->large) hipFree(ctx->large);
     if (ctx->counters) hipFree(ctx->counters);
     if (ctx->stats) hipFree(ctx->stats);
-    if (ctx->ranges) hipFree(ctx->ranges);
+    if (ctx->range_parts) hipFree(ctx->range_parts);
+    if (ctx->ranges) hipHostFree(ctx->ranges);
     if (ctx->capture_stream) hipStreamDestroy(ctx->capture_stream);
     if (ctx->side_stream) hipStreamDestroy(ctx->side_stream);
     if (ctx->fork_ev) hipEventDestroy(ctx->fork_ev);
@@ -1488,13 +1491,13 @@ int curast_compress_prepare(curast_ctx* ctx, const curast_mesh* mesh, curast_com
     if (rc) return rc;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!ctx->ranges) HIP_TRY(ctx, hipMalloc(&ctx->ranges, 8 * sizeof(uint32_t)));
+    if (!ctx->range_parts) HIP_TRY(ctx, hipMalloc(&ctx->range_parts, compress_range_words() * sizeof(uint32_t)));
+    if (!ctx->ranges) HIP_TRY(ctx, hipHostMalloc(&ctx->ranges, 8 * sizeof(uint32_t), hipHostMallocDefault));
     const uint64_t n_idx = 3ull * mesh->num_triangles;
-    HIP_TRY(ctx, launch_compress_ranges(mesh->indices, n_idx, mesh->vertices, mesh->num_vertices, ctx->ranges,
-                                        (uint32_t)ctx->cus, s));
-    uint32_t r[8];
-    HIP_TRY(ctx, hipMemcpyAsync(r, ctx->ranges, sizeof r, hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, launch_compress_ranges(mesh->indices, n_idx, mesh->vertices, mesh->num_vertices, ctx->range_parts,
+                                        ctx->ranges, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
+    const uint32_t* r = ctx->ranges;
     const uint32_t imin = n_idx ? r[0] : 0u, imax = n_idx ? r[1] : 0u;
     const uint32_t span = imax - imin;
     info->index_min = imin;
