@@ -1488,10 +1488,11 @@ struct S2Poly {
 template <bool STATS>
 __global__ void __launch_bounds__(256) stage2_kernel(RasterArgs a)
 {
-    // Each wavefront takes 64 queue entries at a time.  Every lane sets up one of them (descriptor,
-    // index and vertex loads, transform, clip, snap: 64 dependent load chains in flight at once)
-    // and leaves the snapped polygon in LDS; then the whole wavefront rasterizes the 64 polygons
-    // one after the other.
+    // Each wavefront takes up to 64 queue entries at a time.  Every lane sets up one of them
+    // (descriptor, index and vertex loads, transform, clip, snap: 64 dependent load chains in flight
+    // at once) and leaves the snapped polygon in LDS; then the whole wavefront rasterizes the
+    // polygons one after the other.  That walk is the serial part, so a queue too short to give
+    // every wavefront 64 entries is spread over all of them (a few hundred triangles: 69 -> 14 us).
     __shared__ S2Poly s_poly[4][64];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wslot = threadIdx.x >> 6;
@@ -1500,11 +1501,12 @@ __global__ void __launch_bounds__(256) stage2_kernel(RasterArgs a)
     const unsigned long long n = min(a.counters[kCntQ2], (unsigned long long)a.q2_cap);
     const bool early_out = !(a.flags & kFlagNoEarlyOut);
     StatAcc<STATS> st;
-    for (unsigned long long base = (unsigned long long)wave * 64; base < n; base += (unsigned long long)nwaves * 64) {
+    const uint32_t per = (uint32_t)min((n + nwaves - 1) / nwaves, 64ull);   // entries per wavefront and round
+    for (unsigned long long base = (unsigned long long)wave * per; base < n; base += (unsigned long long)nwaves * per) {
         S2Poly& mine = s_poly[wslot][lane];
         const unsigned long long e = base + lane;
         uint32_t np = 0;
-        if (e < n) {
+        if (lane < per && e < n) {
             const Q2Entry q = a.q2[e];
             const DrawDesc& D = a.draws[q.draw];
             const uint32_t view = D.view & kDrawViewMask;
@@ -1533,7 +1535,7 @@ __global__ void __launch_bounds__(256) stage2_kernel(RasterArgs a)
         }
         mine.np = np;
         wave_lds_sync();
-        for (uint32_t l = 0; l < 64; ++l) {
+        for (uint32_t l = 0; l < per; ++l) {
             const S2Poly& P = s_poly[wslot][l];
             const uint32_t npl = __builtin_amdgcn_readfirstlane(P.np);
             if (npl < 3) continue;
