@@ -239,7 +239,7 @@ int curast_rasterize(curast_ctx* ctx, const float* vertices, uint32_t num_vertic
  * the same visibility buffer as curast_rasterize; it calls no hipMalloc, hipFree, hipMemcpy or
  * hipMemset, and on the host it allocates nothing either (except the message it stores when it
  * returns an error).  The plan is built in fixed arrays, its
- * descriptors go to the device as the argument of one small kernel, and descriptors, queues,
+ * descriptors go to the device as the argument of the clear kernel, and descriptors, queues,
  * counters and stage-3 bins live in a file-scope device array of about 17 MB per device (held
  * until the process ends; its address is taken once per device by curast_create), instead of the
  * context's buffers.  Its stage-2 queue holds 1M entries, its large-triangle store 64K records and
@@ -445,7 +445,7 @@ int curast_reset_stats(curast_ctx* ctx);
 /* Stage durations accumulated over frames run with CURAST_FLAG_TIMING, measured with HIP events
    on the launch stream (synchronizes those events): ms[0..8] = clear, stage-1 launch over the
    meshes with two or more draws (all meshes when s1_mode = 3), stage-1 launch over the other
-   meshes, stage-1 overflow pass, stage 2, stage 3, resolve (either form), resolve backward, whole
+   meshes, 0 (the stage-1 overflow pass is part of the stage-2 launch), stage 2, stage 3, resolve (either form), resolve backward, whole
    rasterized frame; *frames = number of rasterized frames timed.
    Batched (graph) frames contribute only the whole-frame time. */
 int curast_get_stage_times(curast_ctx* ctx, double ms[9], uint64_t* frames);

@@ -17,6 +17,7 @@ constexpr uint64_t kEmptyKey = ~uint64_t(0);
 constexpr int kTileSize = 64;                     // stage-3 screen tile (Sec. 4.2)
 constexpr int kMaxDim = 16384;
 constexpr uint32_t kNullRecord = 0xFFFFFFFFu;
+constexpr uint32_t kNoPart = 0xFFFFFFFFu;         // end of a tile's list of stage-3 parts
 // Stage 1 keeps triangles whose snapped bounding box spans less than this many 1/256-px units in
 // x and y: every edge-function value at a pixel centre of the box (and one step past it) then
 // fits in int32 (|E| <= 2 * ext * (ext + 384) < 2^31).
@@ -107,6 +108,7 @@ enum Counter : int {
     kCntQ2 = 0,                   // entries appended to Q2 (may exceed its capacity)
     kCntLarge = 1,                // large records reserved
     kCntQ3 = 2,                   // Q3 entries reserved
+    kCntTiles = 3,                // screen tiles with parts
     kNumCounters = 4
 };
 
@@ -147,12 +149,30 @@ struct RasterArgs {
     uint32_t s1_mode;             // 0 auto (= 2), 1 exact only, 2 fast reject (strip spheres in the
                                   // multi-draw launch), 3 vertex sharing for every mesh, 4 as 2 without spheres
     uint32_t part;                // stage-1 work items: 0 all, 1 the shared prefix, 2 the rest
-    uint32_t* tile_count;         // [n_tiles] parts per tile (zeroed by the clear kernel)
-    uint32_t* tile_offset;        // [n_tiles + 1] exclusive prefix of tile_count
-    uint32_t* q3_binned;          // [q3_cap] large-record index of every part, grouped by tile
+    uint32_t* tile_head;          // [n_tiles] last part linked to each tile (kNoPart: none; clear kernel)
+    uint32_t* tile_list;          // [n_tiles] the tiles that have parts, kCntTiles of them
+    uint32_t* q3_next;            // [q3_cap] the next part of the same tile, or kNoPart
     uint32_t compressed_parts;    // bit p: stage-1 part p has a compressed mesh; bit p + 8: every
                                   // mesh of part p is compressed (host-side kernel choice)
 };
+
+// A frame's descriptor block as a kernel argument (at most 4 KB in all), with what the clear needs.
+constexpr int kBlockWordsSmall = 240, kBlockWords = 960;
+template <int WORDS>
+struct FrameBlock {
+    uint32_t* dst;                // device copy of w[0 .. words)
+    unsigned long long* counters;
+    uint32_t* tile_head;
+    uint32_t words, views_word;   // words of the block in use; the first word of its views
+    uint32_t n_views, n_tiles;
+    uint32_t pad[2];
+    alignas(16) uint32_t w[WORDS];
+};
+static_assert(sizeof(FrameBlock<kBlockWords>) <= 4096 - 128, "fits a kernel argument");
+
+// Compression's index range and bounding box: workgroups per reduction (a multiple of 3) and words of
+// their partial results.
+constexpr uint32_t kRangeBlocks = 1536, kRangeWords = 2 * 6 * kRangeBlocks;
 
 // A mip-mapped RGBA8 texture: level l is max(1, w >> l) x max(1, h >> l) texels from off[l].
 struct TexDesc {

@@ -36,8 +36,6 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
 // 235 us for the range of 54 M indices; the two launches here take 67 us together
 // (324 MB, 52 us at the streaming read rate).
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
-constexpr uint32_t kRangeBlocks = 1536;        // of either kind; a multiple of 3 (see below)
-
 struct RangeAcc {
     uint32_t lo[3], hi[3];
 };
@@ -217,9 +215,7 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float* __restrict__
     }
 }
 
-uint64_t compress_range_words() { return 12ull * kRangeBlocks; }
-
-// part: compress_range_words() words of device scratch; out: 8 words of pinned host memory
+// part: kRangeWords words of device scratch; out: 8 words of pinned host memory
 hipError_t launch_compress_ranges(const uint32_t* idx, uint64_t n_idx, const float* pos, uint32_t V, uint32_t* part,
                                   uint32_t* out, hipStream_t s)
 {

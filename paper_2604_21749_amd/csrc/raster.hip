@@ -189,6 +189,18 @@ __device__ inline void raster_any_thread(const Clip c[3], uint64_t id, const Vie
 // ----------------------------------------------------------------------------------------------
 // Clear (also resets the queue counters of the frame)
 // ----------------------------------------------------------------------------------------------
+__device__ __forceinline__ void clear_view(unsigned long long* vis, uint64_t n, uint64_t tid, uint64_t stride)
+{
+    if (((uintptr_t)vis & 15) == 0) {
+        CURAST_GLOBAL ulonglong2* p = (CURAST_GLOBAL ulonglong2*)gl(vis);
+        const uint64_t n2 = n >> 1;
+        for (uint64_t i = tid; i < n2; i += stride) p[i] = make_ulonglong2(~0ull, ~0ull);
+        if ((n & 1) && tid == 0) gl(vis)[n - 1] = ~0ull;
+    } else {
+        for (uint64_t i = tid; i < n; i += stride) gl(vis)[i] = ~0ull;
+    }
+}
+
 __global__ void __launch_bounds__(256) clear_kernel(RasterArgs a)
 {
     if (blockIdx.x == 0 && threadIdx.x < kNumCounters) a.counters[threadIdx.x] = 0;
@@ -196,21 +208,39 @@ __global__ void __launch_bounds__(256) clear_kernel(RasterArgs a)
     const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint32_t nt = a.hdr->n_tiles;
-    for (uint64_t i = tid; i < nt; i += stride) a.tile_count[i] = 0;
+    for (uint64_t i = tid; i < nt; i += stride) a.tile_head[i] = kNoPart;
     for (uint32_t v = 0; v < nv; ++v) {
         const ViewDesc V = a.views[v];
-        const uint64_t n = (uint64_t)V.W * (uint64_t)V.H;
-        if (((uintptr_t)V.vis & 15) == 0) {
-            ulonglong2* p = reinterpret_cast<ulonglong2*>(V.vis);
-            const uint64_t n2 = n >> 1;
-            for (uint64_t i = tid; i < n2; i += stride) p[i] = make_ulonglong2(~0ull, ~0ull);
-            if ((n & 1) && tid == 0) V.vis[n - 1] = ~0ull;
-        } else {
-            for (uint64_t i = tid; i < n; i += stride) V.vis[i] = ~0ull;
-        }
+        clear_view(V.vis, (uint64_t)V.W * (uint64_t)V.H, tid, stride);
     }
 }
 
+// The same with the frame's descriptor block as part of the kernel argument: workgroup 0 writes the
+// block to device memory for the kernels that follow, and every workgroup reads the views it clears
+// from the argument.  Small frames are bound by launches: the copy that uploads larger blocks costs
+// 3-4 us on the stream and a gap before the next kernel.  With the stage-3 lists and the overflow pass
+// inside stage 2, a 320x240 low-poly frame and its resolve went from 81 to 61 us, a 512x512 frame of
+// 262K triangles from 90 to 71 us.
+template <int WORDS>
+__global__ void __launch_bounds__(256) frame_begin_kernel(FrameBlock<WORDS> b)
+{
+    // the argument read where it lies (it starts the kernel argument segment), not from a private copy
+    using Arg = const __attribute__((address_space(4))) FrameBlock<WORDS>;
+    Arg* k = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < kNumCounters) gl(k->counters)[threadIdx.x] = 0;
+        const uint32_t n = k->words;
+        for (uint32_t i = threadIdx.x; i < n; i += 256) gl(k->dst)[i] = k->w[i];
+    }
+    const uint32_t nt = k->n_tiles, nv = k->n_views;
+    for (uint64_t i = tid; i < nt; i += stride) gl(k->tile_head)[i] = kNoPart;
+    using View = const __attribute__((address_space(4))) ViewDesc;
+    View* views = (View*)(k->w + k->views_word);
+    for (uint32_t v = 0; v < nv; ++v)
+        clear_view(views[v].vis, (uint64_t)views[v].W * (uint64_t)views[v].H, tid, stride);
+}
 #endif  // CURAST_FAST_BLOCK
 
 // ----------------------------------------------------------------------------------------------
@@ -1382,10 +1412,10 @@ __global__ void __launch_bounds__(64) stage1_share_kernel(RasterArgs a, CURAST_D
 
 // Stage-1 overflow pass: when more triangles were forwarded than Q2 holds, every forwarded
 // triangle is rasterized here by one thread (those that did fit are drawn twice; the minimum is
-// idempotent).  Exits at once when nothing overflowed.
-__global__ void __launch_bounds__(256) stage1_overflow_kernel(RasterArgs a, CURAST_DESC_PARAMS)
+// idempotent).  Stage 2 calls it first: both only take atomic minima, so their order does not
+// matter, and a frame without overflow (almost every frame) saves a launch.
+__device__ __forceinline__ void stage1_overflow(const RasterArgs& a, CURAST_DESC_PARAMS)
 {
-    if (a.counters[kCntQ2] <= a.q2_cap) return;
     const FrameHeader hdr = *d_hdr;
     uint64_t first, total;
     work_range(hdr, a.part, first, total);
@@ -1486,8 +1516,10 @@ struct S2Poly {
 };
 
 template <bool STATS>
-__global__ void __launch_bounds__(256) stage2_kernel(RasterArgs a)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))   // what its LDS allows
+stage2_kernel(RasterArgs a, CURAST_DESC_PARAMS)
 {
+    if (a.counters[kCntQ2] > a.q2_cap) stage1_overflow(a, d_hdr, d_views, d_meshes, d_segs, d_draws);
     // Each wavefront takes up to 64 queue entries at a time.  Every lane sets up one of them
     // (descriptor, index and vertex loads, transform, clip, snap: 64 dependent load chains in flight
     // at once) and leaves the snapped polygon in LDS; then the whole wavefront rasterizes the
@@ -1582,7 +1614,12 @@ __global__ void __launch_bounds__(256) stage2_kernel(RasterArgs a)
                             qe.tx = (uint16_t)(tx0 + (uint32_t)(i % ntx));
                             qe.ty = (uint16_t)(ty0 + (uint32_t)(i / ntx));
                             a.q3[qbase + i] = qe;
-                            atomicAdd(a.tile_count + V.tile_base + (uint32_t)qe.ty * view_ntx + qe.tx, 1u);
+                            // prepend the part to its tile's list; the first part of a tile also
+                            // puts the tile on the frame's list of tiles
+                            const uint32_t tile = V.tile_base + (uint32_t)qe.ty * view_ntx + qe.tx;
+                            const uint32_t next = atomicExch(a.tile_head + tile, (uint32_t)(qbase + i));
+                            a.q3_next[qbase + i] = next;
+                            if (next == kNoPart) a.tile_list[atomicAdd(a.counters + kCntTiles, 1ull)] = tile;
                         }
                         if (lane == 0) st.add(kStQ3, (uint32_t)ntiles);
                     } else {
@@ -1641,104 +1678,75 @@ __global__ void __launch_bounds__(256) stage3_kernel(RasterArgs a)
 }
 
 // ----------------------------------------------------------------------------------------------
-// Stage 3 binned by screen tile.  The parts stage 2 produced are grouped by 64x64 tile (count,
-// scan, scatter); then one workgroup per non-empty tile walks all parts of its bin.  Lane l owns
-// the 16 pixels (l % 64, l / 64 + 4k) of the tile and keeps their running minimum keys in
-// registers, so the parts of one tile need no atomics at all and the tile costs one global 64-bit
-// atomic minimum per covered pixel however many large triangles overlap it.
+// Stage 3 binned by screen tile.  Stage 2 linked the parts of every 64x64 tile (a list head per
+// tile) and listed the tiles that have any, so one launch is enough: a workgroup takes a quarter of
+// a listed tile (16 rows) and walks all parts of its list.  Lane l owns the 4 pixels (l % 64,
+// l / 64 + 4k) of the quarter and keeps their running minimum keys in registers, so the parts of one
+// tile need no atomics among themselves and the tile costs one global 64-bit atomic minimum per
+// covered pixel however many large triangles overlap it.  The next part's record is loaded while
+// the current one is rasterized.  Latency bounds it on small views (a 512x512 ground plane has 64
+// tiles, fewer than compute units): whole tiles of 16 pixels per lane took 15.4 us there,
+// quarters take 7.6, and the scan and scatter launches that grouped the parts before cost 7-9 us in
+// every frame.
 // ----------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) tile_scan_kernel(RasterArgs a)
-{
-    __shared__ uint32_t s_part[1024];
-    __shared__ uint32_t s_carry;
-    const uint32_t n = a.hdr->n_tiles;
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < n; base += 1024) {
-        const uint32_t i = base + threadIdx.x;
-        const uint32_t v = i < n ? a.tile_count[i] : 0u;
-        s_part[threadIdx.x] = v;
-        __syncthreads();
-        for (uint32_t off = 1; off < 1024; off <<= 1) {           // inclusive Hillis-Steele scan
-            const uint32_t add = threadIdx.x >= off ? s_part[threadIdx.x - off] : 0u;
-            __syncthreads();
-            s_part[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const uint32_t carry = s_carry;
-        if (i < n) a.tile_offset[i] = carry + s_part[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 1023) s_carry = carry + s_part[1023];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) a.tile_offset[n] = s_carry;
-}
-
-__global__ void __launch_bounds__(256) tile_scatter_kernel(RasterArgs a, const ViewDesc* __restrict__ d_views)
-{
-    const unsigned long long n = min(a.counters[kCntQ3], (unsigned long long)a.q3_cap);
-    for (unsigned long long e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-         e += (uint64_t)gridDim.x * blockDim.x) {
-        const Q3Entry q = a.q3[e];
-        if (q.rec == kNullRecord) continue;
-        const ViewDesc& V = d_views[a.large[q.rec].view];
-        const uint32_t t = V.tile_base + (uint32_t)q.ty * ((uint32_t)(V.W + kTileSize - 1) / kTileSize) + q.tx;
-        const uint32_t left = atomicSub(a.tile_count + t, 1u);    // left..1: a distinct slot per part
-        a.q3_binned[a.tile_offset[t] + left - 1] = q.rec;
-    }
-}
+constexpr uint32_t kTileParts = 4;                    // workgroups' shares of a tile
+constexpr int kShareRows = kTileSize / (int)kTileParts;
+constexpr int kSharePixels = kShareRows / 4;          // per lane of a 256-lane workgroup
 
 template <bool STATS>
 __global__ void __launch_bounds__(256) stage3_tile_kernel(RasterArgs a, const ViewDesc* __restrict__ d_views)
 {
-    const uint32_t n_tiles = a.hdr->n_tiles;
-    const uint32_t nv = a.hdr->n_views;
+    const uint32_t n = (uint32_t)a.counters[kCntTiles] * kTileParts;
     const bool early_out = !(a.flags & kFlagNoEarlyOut);
     const int32_t col = threadIdx.x & 63;
     const int32_t row0 = threadIdx.x >> 6;
     StatAcc<STATS> st;
-    for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const uint32_t begin = a.tile_offset[t], end = a.tile_offset[t + 1];
-        if (begin == end) continue;
-        // the view that owns tile t (views are few: linear scan of their tile bases)
-        uint32_t v = 0;
-        while (v + 1 < nv && d_views[v + 1].tile_base <= t) ++v;
-        const ViewDesc V = d_views[v];
+    for (uint32_t item = blockIdx.x; item < n; item += gridDim.x) {
+        const uint32_t t = a.tile_list[item / kTileParts];
+        uint32_t part = a.tile_head[t];
+        LargeTri r = a.large[a.q3[part].rec];
+        const ViewDesc V = d_views[r.view];
         const uint32_t ntx = (uint32_t)(V.W + kTileSize - 1) / kTileSize;
         const uint32_t local = t - V.tile_base;
         const int32_t px = (int32_t)(local % ntx) * kTileSize + col;
-        const int32_t py0 = (int32_t)(local / ntx) * kTileSize + row0;
-        unsigned long long best[16];
+        const int32_t y_first = (int32_t)(local / ntx) * kTileSize + (int32_t)(item % kTileParts) * kShareRows;
+        const int32_t py0 = y_first + row0;
+        unsigned long long best[kSharePixels];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) best[k] = kEmptyKey;
-        for (uint32_t j = begin; j < end; ++j) {
-            const LargeTri r = a.large[a.q3_binned[j]];
+        for (int k = 0; k < kSharePixels; ++k) best[k] = kEmptyKey;
+        while (true) {
+            const LargeTri cur = r;
+            part = a.q3_next[part];
+            if (part != kNoPart) r = a.large[a.q3[part].rec];
             Tri64 tri;
-            if (!setup_tri64(r.X, r.Y, r.zI, V.W, V.H, tri)) continue;
-            if (px < tri.px0 || px > tri.px1) continue;
-            // edge values at (px, py0), stepped by four rows
-            int64_t e[3];
-            const int64_t step[3] = {(int64_t)tri.dx[0] * 1024, (int64_t)tri.dx[1] * 1024, (int64_t)tri.dx[2] * 1024};
+            if (setup_tri64(cur.X, cur.Y, cur.zI, V.W, V.H, tri) && tri.py0 < y_first + kShareRows &&
+                tri.py1 >= y_first && px >= tri.px0 && px <= tri.px1) {
+                // edge values at (px, py0), stepped by four rows
+                int64_t e[3];
+                const int64_t step[3] = {(int64_t)tri.dx[0] * 1024, (int64_t)tri.dx[1] * 1024,
+                                         (int64_t)tri.dx[2] * 1024};
 #pragma unroll
-            for (int k = 0; k < 3; ++k) e[k] = edge64(tri, k, px, py0);
-            const float area_f = (float)tri.area;
+                for (int k = 0; k < 3; ++k) e[k] = edge64(tri, k, px, py0);
+                const float area_f = (float)tri.area;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int32_t py = py0 + 4 * k;
-                if (py >= tri.py0 && py <= tri.py1 &&
-                    ((e[0] + tri.bias[0]) | (e[1] + tri.bias[1]) | (e[2] + tri.bias[2])) >= 0) {
-                    const float depth = frag_depth((float)e[0], (float)e[1], (float)e[2], tri.zI, area_f);
-                    const unsigned long long key = make_key(depth, r.id);
-                    best[k] = key < best[k] ? key : best[k];
-                    st.add(kStFragments);
+                for (int k = 0; k < kSharePixels; ++k) {
+                    const int32_t py = py0 + 4 * k;
+                    if (py >= tri.py0 && py <= tri.py1 &&
+                        ((e[0] + tri.bias[0]) | (e[1] + tri.bias[1]) | (e[2] + tri.bias[2])) >= 0) {
+                        const float depth = frag_depth((float)e[0], (float)e[1], (float)e[2], tri.zI, area_f);
+                        const unsigned long long key = make_key(depth, cur.id);
+                        best[k] = key < best[k] ? key : best[k];
+                        st.add(kStFragments);
+                    }
+                    e[0] += step[0];
+                    e[1] += step[1];
+                    e[2] += step[2];
                 }
-                e[0] += step[0];
-                e[1] += step[1];
-                e[2] += step[2];
             }
+            if (part == kNoPart) break;
         }
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
+        for (int k = 0; k < kSharePixels; ++k) {
             const int32_t py = py0 + 4 * k;
             if (best[k] != kEmptyKey && px < V.W && py < V.H)
                 write_fragment(V.vis + (size_t)py * (size_t)V.W + (size_t)px, best[k], early_out);
@@ -1753,6 +1761,18 @@ __global__ void __launch_bounds__(256) stage3_tile_kernel(RasterArgs a, const Vi
 hipError_t launch_clear(const RasterArgs& a, uint32_t grid, hipStream_t s)
 {
     clear_kernel<<<grid, 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_frame_begin(const FrameBlock<kBlockWordsSmall>& b, uint32_t grid, hipStream_t s)
+{
+    frame_begin_kernel<kBlockWordsSmall><<<grid, 256, 0, s>>>(b);
+    return hipGetLastError();
+}
+
+hipError_t launch_frame_begin(const FrameBlock<kBlockWords>& b, uint32_t grid, hipStream_t s)
+{
+    frame_begin_kernel<kBlockWords><<<grid, 256, 0, s>>>(b);
     return hipGetLastError();
 }
 
@@ -1830,23 +1850,15 @@ hipError_t launch_stage1_share(const RasterArgs& a, uint32_t tpt, bool stats, ui
     }
 }
 
-hipError_t launch_stage1_overflow(const RasterArgs& a, uint32_t grid, hipStream_t s)
-{
-    stage1_overflow_kernel<<<grid, 256, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    return hipGetLastError();
-}
-
 hipError_t launch_stage2(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s)
 {
-    if (stats) stage2_kernel<true><<<grid, 256, 0, s>>>(a);
-    else stage2_kernel<false><<<grid, 256, 0, s>>>(a);
+    if (stats) stage2_kernel<true><<<grid, 256, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    else stage2_kernel<false><<<grid, 256, 0, s>>>(a, CURAST_DESC_ARGS(a));
     return hipGetLastError();
 }
 
 hipError_t launch_stage3_binned(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s)
 {
-    tile_scan_kernel<<<1, 1024, 0, s>>>(a);
-    tile_scatter_kernel<<<grid, 256, 0, s>>>(a, a.views);
     if (stats) stage3_tile_kernel<true><<<grid, 256, 0, s>>>(a, a.views);
     else stage3_tile_kernel<false><<<grid, 256, 0, s>>>(a, a.views);
     return hipGetLastError();

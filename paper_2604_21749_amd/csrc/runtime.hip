@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -25,16 +26,16 @@
 
 namespace curast {
 hipError_t launch_clear(const RasterArgs& a, uint32_t grid, hipStream_t s);
+hipError_t launch_frame_begin(const FrameBlock<kBlockWordsSmall>& b, uint32_t grid, hipStream_t s);
+hipError_t launch_frame_begin(const FrameBlock<kBlockWords>& b, uint32_t grid, hipStream_t s);
 hipError_t launch_stage1(const RasterArgs& a, uint32_t block, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s);
 hipError_t launch_stage1_fast(const RasterArgs& a, uint32_t block, uint32_t tpt, bool strips, bool spheres, bool stats,
                               uint32_t grid, hipStream_t s);
 hipError_t launch_stage1_share(const RasterArgs& a, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s);
-hipError_t launch_stage1_overflow(const RasterArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_stage2(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_stage3(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_stage3_binned(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_project(const MeshDesc& mesh, const float A[12], float hW, float hH, float* out, hipStream_t s);
-uint64_t compress_range_words();
 hipError_t launch_compress_ranges(const uint32_t* idx, uint64_t n_idx, const float* pos, uint32_t V, uint32_t* part,
                                   uint32_t* out, hipStream_t s);
 hipError_t launch_compress(const uint32_t* idx, uint64_t n_idx, uint32_t bits, uint32_t base, uint32_t* packed,
@@ -96,9 +97,9 @@ struct curast_ctx {
     uint32_t q2_alloc = 0, large_alloc = 0, q3_alloc = 0;
     unsigned long long* counters = nullptr;
     unsigned long long* stats = nullptr;
-    uint32_t* tile_count = nullptr;
-    uint32_t* tile_offset = nullptr;
-    uint32_t* q3_binned = nullptr;
+    uint32_t* tile_head = nullptr;
+    uint32_t* tile_list = nullptr;
+    uint32_t* q3_next = nullptr;
     uint32_t tiles_alloc = 0;
     hipStream_t capture_stream = nullptr;
     // the second stream of the overlapped stage-1 launches, and the events that fork it from the
@@ -206,21 +207,22 @@ int ensure_tiles(curast_ctx* ctx, uint32_t n_tiles)
 {
     if (n_tiles + 1 <= ctx->tiles_alloc) return CURAST_OK;
     const uint32_t n = std::max<uint32_t>(n_tiles + 1, 4096);
-    if (ctx->tile_count) hipFree(ctx->tile_count);
-    if (ctx->tile_offset) hipFree(ctx->tile_offset);
-    ctx->tile_count = ctx->tile_offset = nullptr;
+    if (ctx->tile_head) hipFree(ctx->tile_head);
+    if (ctx->tile_list) hipFree(ctx->tile_list);
+    ctx->tile_head = ctx->tile_list = nullptr;
     ctx->tiles_alloc = 0;
-    if (hipMalloc(&ctx->tile_count, sizeof(uint32_t) * n) != hipSuccess ||
-        hipMalloc(&ctx->tile_offset, sizeof(uint32_t) * n) != hipSuccess)
+    if (hipMalloc(&ctx->tile_head, sizeof(uint32_t) * n) != hipSuccess ||
+        hipMalloc(&ctx->tile_list, sizeof(uint32_t) * n) != hipSuccess)
         return fail(ctx, CURAST_E_OOM, "tile bin allocation failed");
     ctx->tiles_alloc = n;
     drop_graphs(ctx);
     return CURAST_OK;
 }
 
-int ensure_staging(curast_ctx* ctx, Staging& st, size_t bytes)
+// Room for `bytes` in both buffers; with host_side also waits until the host one may be rewritten.
+int ensure_staging(curast_ctx* ctx, Staging& st, size_t bytes, bool host_side = true)
 {
-    if (st.pending) {
+    if (st.pending && (host_side || bytes > st.cap)) {
         HIP_TRY(ctx, hipEventSynchronize(st.ev));
         st.pending = false;
     }
@@ -256,10 +258,10 @@ int ensure_queues(curast_ctx* ctx)
         if (ctx->q3) hipFree(ctx->q3);
         ctx->q3 = nullptr;
         ctx->q3_alloc = 0;
-        if (ctx->q3_binned) hipFree(ctx->q3_binned);
-        ctx->q3_binned = nullptr;
+        if (ctx->q3_next) hipFree(ctx->q3_next);
+        ctx->q3_next = nullptr;
         if (hipMalloc(&ctx->q3, sizeof(Q3Entry) * (size_t)q3) != hipSuccess) return fail(ctx, CURAST_E_OOM, "Q3 allocation failed");
-        if (hipMalloc(&ctx->q3_binned, sizeof(uint32_t) * (size_t)q3) != hipSuccess)
+        if (hipMalloc(&ctx->q3_next, sizeof(uint32_t) * (size_t)q3) != hipSuccess)
             return fail(ctx, CURAST_E_OOM, "Q3 bin allocation failed");
         ctx->q3_alloc = q3;
         drop_graphs(ctx);
@@ -661,11 +663,11 @@ int build_plan(curast_ctx* ctx, const curast_options& o, const curast_mesh* mesh
     P.hdr.n_views = n_views;
     P.hdr.batch_tris = bt;
     P.hdr.draws_per_item = dpi;
-    P.off_views = align_up(sizeof(FrameHeader), 256);
-    P.off_meshes = align_up(P.off_views + sizeof(ViewDesc) * n_views, 256);
-    P.off_segs = align_up(P.off_meshes + sizeof(MeshDesc) * std::max<uint32_t>(M, 1), 256);
-    P.off_draws = align_up(P.off_segs + sizeof(Segment) * std::max<uint32_t>(M, 1), 256);
-    P.bytes = align_up(P.off_draws + sizeof(DrawDesc) * std::max<size_t>(P.draws.size(), 1), 256);
+    P.off_views = align_up(sizeof(FrameHeader), 64);
+    P.off_meshes = align_up(P.off_views + sizeof(ViewDesc) * n_views, 64);
+    P.off_segs = align_up(P.off_meshes + sizeof(MeshDesc) * std::max<uint32_t>(M, 1), 64);
+    P.off_draws = align_up(P.off_segs + sizeof(Segment) * std::max<uint32_t>(M, 1), 64);
+    P.bytes = align_up(P.off_draws + sizeof(DrawDesc) * std::max<size_t>(P.draws.size(), 1), 64);
     P.max_bytes = align_up(P.off_draws + sizeof(DrawDesc) * std::max<size_t>(P.max_draws, 1), 256);
     return CURAST_OK;
 }
@@ -703,9 +705,9 @@ RasterArgs make_args(curast_ctx* ctx, const Plan& P)
     a.flags = ctx->opt.flags;
     a.s1_mode = ctx->opt.s1_mode;
     a.part = 0;
-    a.tile_count = ctx->tile_count;
-    a.tile_offset = ctx->tile_offset;
-    a.q3_binned = ctx->q3_binned;
+    a.tile_head = ctx->tile_head;
+    a.tile_list = ctx->tile_list;
+    a.q3_next = ctx->q3_next;
     a.compressed_parts = P.compressed_parts;
     return a;
 }
@@ -733,18 +735,42 @@ TimedFrame* begin_timing(curast_ctx* ctx)
     return &ctx->timed.back();
 }
 
+uint32_t clear_grid(const curast_ctx* ctx, uint64_t total_pixels)
+{
+    const uint64_t pairs = (total_pixels + 1) / 2;
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 255) / 256, ctx->cus * 16ull));
+}
+
+// The frame's first launch when its descriptor block fits a kernel argument: writes the block to the
+// device and clears (see frame_begin_kernel).
+template <int WORDS>
+hipError_t frame_begin(const curast_ctx* ctx, const RasterArgs& a, const void* block, size_t bytes, size_t off_views,
+                       const FrameHeader& hdr, uint64_t total_pixels, hipStream_t s)
+{
+    FrameBlock<WORDS> b;
+    b.dst = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(a.hdr));
+    b.counters = a.counters;
+    b.tile_head = a.tile_head;
+    b.words = (uint32_t)((bytes + 3) / 4);
+    b.views_word = (uint32_t)(off_views / 4);
+    b.n_views = hdr.n_views;
+    b.n_tiles = hdr.n_tiles;
+    std::memcpy(b.w, block, bytes);
+    return launch_frame_begin(b, clear_grid(ctx, total_pixels), s);
+}
+
 // Launch the device part of a frame over the buffers in `a` (descriptors, queues, counters):
-// clear, stage 1, overflow pass, stage 2, stage 3.  Options other than a.flags come from ctx.
-int launch_frame(curast_ctx* ctx, const RasterArgs& a, uint64_t total_pixels, uint32_t grid1, uint32_t grid_share,
+// clear, stage 1, stage 2 (with stage 1's overflow pass), stage 3.  Options other than a.flags come from ctx.
+// `clear` launches the first one.
+template <class Clear>
+int launch_frame(curast_ctx* ctx, const RasterArgs& a, Clear clear, uint32_t grid1, uint32_t grid_share,
                  hipStream_t s, TimedFrame* tf)
 {
     const bool stats = a.flags & kFlagStats;
     const uint32_t cus = (uint32_t)ctx->cus;
-    const uint64_t pairs = (total_pixels + 1) / 2;
-    const uint32_t clear_grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 255) / 256, cus * 16ull));
     hipError_t e;
     if (tf) hipEventRecord(tf->ev[0], s);
-    e = launch_clear(a, clear_grid, s);
+    e = clear();
     if (e != hipSuccess) return hip_fail(ctx, e, "clear kernel launch");
     if (tf) hipEventRecord(tf->ev[1], s);
     {
@@ -798,9 +824,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, uint64_t total_pixels, ui
         }
     }
     if (tf) hipEventRecord(tf->ev[3], s);
-    e = launch_stage1_overflow(a, cus * 4, s);
-    if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 overflow kernel launch");
-    if (tf) hipEventRecord(tf->ev[4], s);
+    if (tf) hipEventRecord(tf->ev[4], s);   // the overflow pass is part of the stage-2 launch
     {
         // stage 2 writes with the atomic alone as well (see the stage-1 launches)
         RasterArgs a2 = a;
@@ -834,20 +858,30 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     rc = ensure_tiles(ctx, P.hdr.n_tiles);
     if (rc) return rc;
     const size_t bytes = use_graph ? P.max_bytes : P.bytes;
-    rc = ensure_staging(ctx, ctx->raster_stage, bytes);
+    // a small descriptor block travels as a kernel argument; larger ones through pinned memory
+    const bool inline_block = !use_graph && bytes <= sizeof(uint32_t) * kBlockWords;
+    alignas(16) char block[sizeof(uint32_t) * kBlockWords];
+    rc = ensure_staging(ctx, ctx->raster_stage, bytes, !inline_block);
     if (rc) return rc;
-    write_plan(P, ctx->raster_stage.host);
+    write_plan(P, inline_block ? block : ctx->raster_stage.host);
     ctx->draws_culled += P.draws_culled;
     log_plan(use_graph ? "batched frame" : "frame", P, M, n_views);
     TimedFrame* tf = begin_timing(ctx);
     if (!use_graph) {
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host, P.bytes, hipMemcpyHostToDevice, s));
-        HIP_TRY(ctx, hipEventRecord(ctx->raster_stage.ev, s));
-        ctx->raster_stage.pending = true;
+        const RasterArgs a = make_args(ctx, P);
+        if (!inline_block) {
+            HIP_TRY(ctx, hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host, P.bytes, hipMemcpyHostToDevice, s));
+            HIP_TRY(ctx, hipEventRecord(ctx->raster_stage.ev, s));
+            ctx->raster_stage.pending = true;
+        }
         const uint64_t shared = P.hdr.shared_batches;
-        rc = launch_frame(ctx, make_args(ctx, P), P.total_pixels, grid_for(P.hdr.total_batches - shared),
-                          shared ? grid_for(shared) : 0, s, tf);
-        return rc;
+        auto clear = [&] {
+            if (!inline_block) return launch_clear(a, clear_grid(ctx, P.total_pixels), s);
+            return bytes <= sizeof(uint32_t) * kBlockWordsSmall
+                       ? frame_begin<kBlockWordsSmall>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s)
+                       : frame_begin<kBlockWords>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s);
+        };
+        return launch_frame(ctx, a, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0, s, tf);
     }
     // graph path: one captured sequence per structure (sizes of the descriptor block, grid bound,
     // options); replays copy the new descriptor contents from the same pinned buffer
@@ -871,8 +905,9 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
         HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
         hipError_t e = hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host, P.max_bytes, hipMemcpyHostToDevice,
                                       ctx->capture_stream);
-        int lrc = e == hipSuccess ? launch_frame(ctx, make_args(ctx, P), P.total_pixels, grid1, grid1,
-                                                 ctx->capture_stream, nullptr)
+        const RasterArgs a = make_args(ctx, P);
+        auto clear = [&] { return launch_clear(a, clear_grid(ctx, P.total_pixels), ctx->capture_stream); };
+        int lrc = e == hipSuccess ? launch_frame(ctx, a, clear, grid1, grid1, ctx->capture_stream, nullptr)
                                   : hip_fail(ctx, e, "capture memcpy");
         hipGraph_t graph = nullptr;
         hipError_t e2 = hipStreamEndCapture(ctx->capture_stream, &graph);
@@ -908,8 +943,8 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
 // Allocation-free rasterization (curast_rasterize_noalloc)
 // ------------------------------------------------------------------------------------------------
 // One mesh (at most kFixedDraws instances) into one view with no allocation of any kind: the plan
-// is built in fixed arrays on the stack, its descriptors reach the device as the argument of one
-// small kernel, and descriptors, queues, counters and stage-3 bins live in the file-scope device
+// is built in fixed arrays on the stack, its descriptors reach the device as the argument of the
+// clear kernel, and descriptors, queues, counters and stage-3 bins live in the file-scope device
 // array `scratch` below instead of context buffers.  Host code must not use the array's name as an
 // address (it is a host-side handle): curast_create takes the device address with
 // hipGetSymbolAddress once per device and every use goes through that pointer.  Queues smaller
@@ -918,7 +953,7 @@ namespace {
 
 constexpr uint32_t kNaQ2 = 1u << 20;       // stage-2 queue entries (8 MB)
 constexpr uint32_t kNaLarge = 1u << 16;    // large-triangle records (3 MB)
-constexpr uint32_t kNaQ3 = 1u << 19;       // stage-3 tile parts (4 MB + 2 MB of bins)
+constexpr uint32_t kNaQ3 = 1u << 19;       // stage-3 tile parts (4 MB + 2 MB of links)
 constexpr uint32_t kNaTiles = (uint32_t)(kMaxDim / kTileSize) * (uint32_t)(kMaxDim / kTileSize) + 1;
 
 struct NaDesc {
@@ -928,17 +963,18 @@ struct NaDesc {
     Segment segs[2];
     DrawDesc draws[kFixedDraws];
 };
-static_assert(sizeof(NaDesc) % 4 == 0 && sizeof(NaDesc) <= 4096, "descriptor block fits one kernel argument");
+static_assert(sizeof(NaDesc) % 4 == 0 && sizeof(NaDesc) <= sizeof(uint32_t) * kBlockWords,
+              "descriptor block fits one kernel argument");
 
 constexpr size_t kNaOffCounters = align_up(sizeof(NaDesc), 256);
 constexpr size_t kNaOffStats = kNaOffCounters + 256;
-constexpr size_t kNaOffTileCount = kNaOffStats + 256;
-constexpr size_t kNaOffTileOffset = align_up(kNaOffTileCount + sizeof(uint32_t) * kNaTiles, 256);
-constexpr size_t kNaOffQ2 = align_up(kNaOffTileOffset + sizeof(uint32_t) * kNaTiles, 256);
+constexpr size_t kNaOffTileHead = kNaOffStats + 256;
+constexpr size_t kNaOffTileList = align_up(kNaOffTileHead + sizeof(uint32_t) * kNaTiles, 256);
+constexpr size_t kNaOffQ2 = align_up(kNaOffTileList + sizeof(uint32_t) * kNaTiles, 256);
 constexpr size_t kNaOffLarge = align_up(kNaOffQ2 + sizeof(Q2Entry) * kNaQ2, 256);
 constexpr size_t kNaOffQ3 = align_up(kNaOffLarge + sizeof(LargeTri) * kNaLarge, 256);
-constexpr size_t kNaOffBinned = align_up(kNaOffQ3 + sizeof(Q3Entry) * kNaQ3, 256);
-constexpr size_t kNaBytes = align_up(kNaOffBinned + sizeof(uint32_t) * kNaQ3, 256);
+constexpr size_t kNaOffNext = align_up(kNaOffQ3 + sizeof(Q3Entry) * kNaQ3, 256);
+constexpr size_t kNaBytes = align_up(kNaOffNext + sizeof(uint32_t) * kNaQ3, 256);
 static_assert(kNumCounters * sizeof(unsigned long long) <= 256 && kNumStats * sizeof(unsigned long long) <= 256,
               "counter areas");
 
@@ -946,14 +982,6 @@ static_assert(kNumCounters * sizeof(unsigned long long) <= 256 && kNumStats * si
 
 // The allocation-free form's scratch (about 17 MB per device, held until the process ends).
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
-
-// Copies the frame's descriptor block from the kernel argument into the scratch array.
-__global__ void __launch_bounds__(256) noalloc_descriptor_kernel(NaDesc d, NaDesc* out)
-{
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&d);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(out);
-    for (uint32_t i = threadIdx.x; i < (uint32_t)(sizeof(NaDesc) / 4); i += blockDim.x) dst[i] = src[i];
-}
 
 namespace {
 
@@ -1003,12 +1031,12 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
     a.draws = dd->draws;
     a.counters = reinterpret_cast<unsigned long long*>(base + kNaOffCounters);
     a.stats = reinterpret_cast<unsigned long long*>(base + kNaOffStats);
-    a.tile_count = reinterpret_cast<uint32_t*>(base + kNaOffTileCount);
-    a.tile_offset = reinterpret_cast<uint32_t*>(base + kNaOffTileOffset);
+    a.tile_head = reinterpret_cast<uint32_t*>(base + kNaOffTileHead);
+    a.tile_list = reinterpret_cast<uint32_t*>(base + kNaOffTileList);
     a.q2 = reinterpret_cast<Q2Entry*>(base + kNaOffQ2);
     a.large = reinterpret_cast<LargeTri*>(base + kNaOffLarge);
     a.q3 = reinterpret_cast<Q3Entry*>(base + kNaOffQ3);
-    a.q3_binned = reinterpret_cast<uint32_t*>(base + kNaOffBinned);
+    a.q3_next = reinterpret_cast<uint32_t*>(base + kNaOffNext);
     const bool zero = ctx->opt.flags & kFlagZeroQueues;
     a.q2_cap = zero ? 0 : std::min(ctx->opt.q2_capacity, kNaQ2);
     a.large_cap = zero ? 0 : std::min(ctx->opt.large_capacity, kNaLarge);
@@ -1019,10 +1047,14 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
     a.s1_mode = ctx->opt.s1_mode;
     a.part = 0;
     a.compressed_parts = P.compressed_parts;
-    noalloc_descriptor_kernel<<<1, 256, 0, s>>>(d, dd);
-    HIP_TRY(ctx, hipGetLastError());
     const uint64_t shared = P.hdr.shared_batches;
-    return launch_frame(ctx, a, P.total_pixels, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0,
+    auto clear = [&] {
+        const size_t used = offsetof(NaDesc, draws) + sizeof(DrawDesc) * P.draws.size();
+        return used <= sizeof(uint32_t) * kBlockWordsSmall
+                   ? frame_begin<kBlockWordsSmall>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s)
+                   : frame_begin<kBlockWords>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s);
+    };
+    return launch_frame(ctx, a, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0,
                         s, nullptr);
 }
 
@@ -1225,9 +1257,9 @@ int curast_destroy(curast_ctx* ctx)
     for (hipEvent_t ev : ctx->event_pool) hipEventDestroy(ev);
     if (ctx->q2) hipFree(ctx->q2);
     if (ctx->q3) hipFree(ctx->q3);
-    if (ctx->q3_binned) hipFree(ctx->q3_binned);
-    if (ctx->tile_count) hipFree(ctx->tile_count);
-    if (ctx->tile_offset) hipFree(ctx->tile_offset);
+    if (ctx->q3_next) hipFree(ctx->q3_next);
+    if (ctx->tile_head) hipFree(ctx->tile_head);
+    if (ctx->tile_list) hipFree(ctx->tile_list);
     if (ctx->large) hipFree(ctx->large);
     if (ctx->counters) hipFree(ctx->counters);
     if (ctx->stats) hipFree(ctx->stats);
@@ -1491,7 +1523,7 @@ int curast_compress_prepare(curast_ctx* ctx, const curast_mesh* mesh, curast_com
     if (rc) return rc;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!ctx->range_parts) HIP_TRY(ctx, hipMalloc(&ctx->range_parts, compress_range_words() * sizeof(uint32_t)));
+    if (!ctx->range_parts) HIP_TRY(ctx, hipMalloc(&ctx->range_parts, kRangeWords * sizeof(uint32_t)));
     if (!ctx->ranges) HIP_TRY(ctx, hipHostMalloc(&ctx->ranges, 8 * sizeof(uint32_t), hipHostMallocDefault));
     const uint64_t n_idx = 3ull * mesh->num_triangles;
     HIP_TRY(ctx, launch_compress_ranges(mesh->indices, n_idx, mesh->vertices, mesh->num_vertices, ctx->range_parts,
