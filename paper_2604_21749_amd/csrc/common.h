@@ -196,11 +196,23 @@ struct ResolveArgs {
     uint32_t C;
     float* out;                   // [H][W][C], or [H/ss][W/ss][C] when supersampled
     uint32_t ss;                  // samples per axis and output pixel (1: no supersampling)
+    uint32_t textured;            // the textured resolve, with:
     const TexDesc* tex;           // [M] textures of the textured resolve (attrs are then the UVs)
     const float* grad_out;        // backward input [H][W][C]
     float* const* grad_attrs;     // [M] per-mesh attribute gradients [V][C] (accumulated), entries may be null
     float* const* grad_pos;       // [M] per-mesh window-position gradients [V][3], or null (one-instance meshes)
 };
+
+// A resolve's descriptor block (bases | mesh_pair | pairs | meshes | attrs | textures) as part of the
+// kernel argument, or its device pointers in `a` (words 0).
+constexpr int kResolveWords = 880, kResolveWordsOne = 96;   // the latter holds one mesh's block
+template <int WORDS>
+struct ResolveBlock {
+    alignas(16) uint32_t w[WORDS];
+    uint32_t words, off_mpair, off_pairs, off_meshes, off_attrs, off_tex;   // byte offsets into w
+    ResolveArgs a;
+};
+static_assert(sizeof(ResolveBlock<kResolveWords>) <= 4096 - 128, "fits a kernel argument");
 
 struct ScreenArgs {
     const unsigned long long* vis;

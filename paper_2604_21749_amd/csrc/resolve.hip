@@ -9,6 +9,8 @@
 // differentiates that expression with visibility held fixed.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device.h"
 
 namespace curast {
@@ -42,15 +44,53 @@ __device__ __forceinline__ void interp_weights(const float sx[3], const float sy
     r.b[2] = q2 / r.s;
 }
 
-__device__ __forceinline__ void write_interp(const Interp& r, const float* a0, const float* a1, const float* a2,
-                                             uint32_t C, float* o)
+// Calls f with the channel count as a constant for the counts that have kernels of their own, 0 for
+// the others.
+template <class F>
+static auto with_channels(uint32_t C, F&& f)
 {
-    for (uint32_t c = 0; c < C; ++c) o[c] = (r.b[0] * a0[c] + r.b[1] * a1[c]) + r.b[2] * a2[c];
+    switch (C) {
+    case 1: return f(std::integral_constant<int, 1>());
+    case 2: return f(std::integral_constant<int, 2>());
+    case 3: return f(std::integral_constant<int, 3>());
+    case 4: return f(std::integral_constant<int, 4>());
+    case 8: return f(std::integral_constant<int, 8>());
+    case 16: return f(std::integral_constant<int, 16>());
+    default: return f(std::integral_constant<int, 0>());
+    }
 }
 
+// put(c, value) for every interpolated channel (b0 a0 + b1 a1) + b2 a2 of three attribute rows, CC
+// channels (0: C).  The rows' loads are issued up to four channels at a time before any arithmetic.
+template <int CC, class Put>
+__device__ __forceinline__ void blend(const float* const (&a)[3], const float (&b)[3], uint32_t C, Put&& put)
+{
+    constexpr uint32_t G = CC == 0 || CC > 4 ? 4 : CC;
+    const uint32_t n = CC ? (uint32_t)CC : C;
+    auto group = [&](uint32_t c0) __attribute__((always_inline)) {
+        float v[3][G];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (uint32_t c = 0; c < G; ++c) v[k][c] = CC || c0 + c < n ? gl(a[k])[c0 + c] : 0.0f;
+#pragma unroll
+        for (uint32_t c = 0; c < G; ++c)
+            if (CC || c0 + c < n) put(c0 + c, (b[0] * v[0][c] + b[1] * v[1][c]) + b[2] * v[2][c]);
+    };
+    if constexpr (CC != 0) {
+#pragma unroll
+        for (uint32_t c0 = 0; c0 < (uint32_t)CC; c0 += G) group(c0);
+    } else {
+        for (uint32_t c0 = 0; c0 < n; c0 += G) group(c0);
+    }
+}
+
+template <int CC>
 __device__ __forceinline__ void write_zero(uint32_t C, float* o)
 {
-    for (uint32_t c = 0; c < C; ++c) o[c] = 0.0f;
+    const uint32_t n = CC ? (uint32_t)CC : C;
+#pragma unroll
+    for (uint32_t c = 0; c < n; ++c) gl(o)[c] = 0.0f;
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -81,49 +121,122 @@ __global__ void __launch_bounds__(256) project_kernel(ProjectArgs a)
 // ----------------------------------------------------------------------------------------------
 constexpr uint32_t kLdsBases = 2048;   // per-mesh first IDs staged in LDS for the binary search
 
-// The triangle of pixel p of the view (row-major index) and its interpolation weights there;
-// false for an empty pixel or an invalid triangle.
-struct PixelHit {
-    const float* a[3];   // attribute rows of the three vertices
-    float b[3];
+// Where a resolve reads its descriptors: device memory, with the meshes' first IDs staged in LDS when
+// they fit (kDescDevice); an LDS copy of the descriptor block that came with the kernel argument
+// (kDescInline); or the argument itself, through scalar loads, for one mesh with one instance, whose
+// descriptors are the same for every pixel (kDescOne).
+enum DescMode : int { kDescDevice, kDescInline, kDescOne };
+
+struct ResolveDesc {
+    const uint64_t* bases;
+    const uint32_t* mesh_pair;
+    const DrawDesc* pairs;
+    const MeshDesc* meshes;
+    const float* const* attrs;
+    const TexDesc* tex;
 };
+
+template <int MODE>
+struct ResolveLds {
+    uint64_t w[MODE == kDescOne ? 1 : MODE == kDescInline ? kResolveWords / 2 : kLdsBases + 1];
+};
+
+// All threads of the workgroup take part.  The argument's block is read where it lies (the first
+// argument starts the kernel argument segment).
+template <int MODE, int WORDS>
+__device__ __forceinline__ ResolveDesc stage_desc(const ResolveBlock<WORDS>& blk, ResolveLds<MODE>& lds)
+{
+    ResolveDesc d;
+    if constexpr (MODE == kDescDevice) {
+        const ResolveArgs& a = blk.a;
+        const bool staged = a.n_meshes <= kLdsBases;
+        if (staged) {
+            for (uint32_t i = threadIdx.x; i <= a.n_meshes; i += 256) lds.w[i] = gl(a.bases)[i];
+            __syncthreads();
+        }
+        d.bases = staged ? lds.w : a.bases;
+        d.mesh_pair = a.mesh_pair;
+        d.pairs = a.pairs;
+        d.meshes = a.meshes;
+        d.attrs = a.attrs;
+        d.tex = a.tex;
+    } else {
+        using Arg = const __attribute__((address_space(4))) ResolveBlock<WORDS>;
+        Arg* k = (Arg*)__builtin_amdgcn_kernarg_segment_ptr();
+        const char* base;
+        if constexpr (MODE == kDescInline) {
+            uint32_t* dst = reinterpret_cast<uint32_t*>(lds.w);
+            const uint32_t n = k->words;
+            for (uint32_t i = threadIdx.x; i < n; i += 256) dst[i] = k->w[i];
+            __syncthreads();
+            base = reinterpret_cast<const char*>(lds.w);
+        } else {
+            base = (const char*)(const __attribute__((address_space(4))) char*)k->w;
+        }
+        d.bases = reinterpret_cast<const uint64_t*>(base);
+        d.mesh_pair = reinterpret_cast<const uint32_t*>(base + blk.off_mpair);
+        d.pairs = reinterpret_cast<const DrawDesc*>(base + blk.off_pairs);
+        d.meshes = reinterpret_cast<const MeshDesc*>(base + blk.off_meshes);
+        d.attrs = reinterpret_cast<const float* const*>(base + blk.off_attrs);
+        d.tex = reinterpret_cast<const TexDesc*>(base + blk.off_tex);
+    }
+    return d;
+}
+
+// floor(off / T) for T >= 1, off / T < 2^36: an approximate reciprocal with one Newton step (relative
+// error below 2^-40) gives it to within one; a 64-bit division takes four times the instructions.
+__device__ __forceinline__ uint64_t instance_of(uint64_t off, uint64_t T)
+{
+    const double t = (double)T;
+    double r = __builtin_amdgcn_rcp(t);
+    r = __builtin_fma(__builtin_fma(-t, r, 1.0), r, r);
+    uint64_t q = (uint64_t)((double)off * r);
+    if (q * T > off) --q;
+    else if ((q + 1) * T <= off) ++q;
+    return q;
+}
 
 // The (mesh, instance) pair and vertex indices of the triangle stored at pixel p; false for an
 // empty pixel or an invalid triangle.
-__device__ __forceinline__ bool pixel_triangle(const ResolveArgs& a, const uint64_t* B, const DrawDesc* __restrict__ pairs,
-                                               const MeshDesc* __restrict__ meshes, uint64_t p, uint32_t& pair,
+template <int MODE>
+__device__ __forceinline__ bool pixel_triangle(const ResolveArgs& a, const ResolveDesc& d, uint32_t p, uint32_t& pair,
                                                uint32_t (&vi)[3])
 {
+    if constexpr (MODE == kDescOne) {
+        const MeshDesc& M = d.meshes[0];
+        const unsigned long long key = gl(a.vis)[p];
+        const uint64_t id = key & kIdMask;
+        if (key == kEmptyKey || id >= M.T) return false;
+        mesh_triangle(M, id, vi);
+        pair = 0;
+        return vi[0] < M.V && vi[1] < M.V && vi[2] < M.V;
+    }
     // the int64 prefix of triangle counts over (mesh, instance) pairs (Sec. 4.4) is searched at
     // mesh granularity: the instances of mesh m hold IDs B[m] + i T_m .. B[m] + (i + 1) T_m - 1,
     // so the instance is one exact integer division (the last mesh with B[m] <= id has T_m > 0)
     const uint32_t nm = a.n_meshes;
     const unsigned long long key = gl(a.vis)[p];
     const uint64_t id = key & kIdMask;
-    if (key == kEmptyKey || id >= B[nm]) return false;
+    if (key == kEmptyKey || id >= d.bases[nm]) return false;
     uint32_t lo = 0, hi = nm;
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
-        if (B[mid] <= id) lo = mid;
+        if (d.bases[mid] <= id) lo = mid;
         else hi = mid;
     }
-    const MeshDesc& M = meshes[lo];
-    const uint64_t off = id - B[lo];
-    const uint64_t inst = off >= M.T ? off / M.T : 0;
+    const MeshDesc& M = d.meshes[lo];
+    const uint64_t off = id - d.bases[lo];
+    const uint64_t inst = off >= M.T ? instance_of(off, M.T) : 0;
     mesh_triangle(M, off - inst * M.T, vi);
-    pair = a.mesh_pair[lo] + (uint32_t)inst;
+    pair = d.mesh_pair[lo] + (uint32_t)inst;
     return vi[0] < M.V && vi[1] < M.V && vi[2] < M.V;
 }
 
-__device__ __forceinline__ bool resolve_hit(const ResolveArgs& a, const uint64_t* B, const DrawDesc* __restrict__ pairs,
-                                            const MeshDesc* __restrict__ meshes, const float* const* __restrict__ attrs,
-                                            uint64_t p, PixelHit& h)
+// Window positions of a triangle's vertices under a pair's draw matrix, in the rasterizer's fp32
+// operations before snapping.
+__device__ __forceinline__ void pixel_windows(const ResolveArgs& a, const DrawDesc& D, const MeshDesc& M,
+                                              const uint32_t (&vi)[3], float (&sx)[3], float (&sy)[3], float (&w)[3])
 {
-    uint32_t lo, vi[3];
-    if (!pixel_triangle(a, B, pairs, meshes, p, lo, vi)) return false;
-    const DrawDesc& D = pairs[lo];
-    const MeshDesc& M = meshes[D.mesh];
-    float sx[3], sy[3], w[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         float q[3];
@@ -134,83 +247,83 @@ __device__ __forceinline__ bool resolve_hit(const ResolveArgs& a, const uint64_t
         sy[k] = __builtin_fmaf(c.y * zI, a.hH, a.hH);
         w[k] = c.w;
     }
-    const int32_t px = (int32_t)(p % (uint64_t)a.W), py = (int32_t)(p / (uint64_t)a.W);
-    Interp r;
-    interp_weights(sx, sy, w, px, py, r);
-    const float* at = attrs[D.mesh];
+}
+
+// put(c, value) for every channel of pixel p of the view (row-major index); false for an empty pixel
+// or an invalid triangle.
+template <int CC, int MODE, class Put>
+__device__ __forceinline__ bool resolve_pixel(const ResolveArgs& a, const ResolveDesc& d, uint32_t p, Put&& put)
+{
+    uint32_t pair, vi[3];
+    if (!pixel_triangle<MODE>(a, d, p, pair, vi)) return false;
+    const DrawDesc& D = d.pairs[pair];
+    const uint32_t m = MODE == kDescOne ? 0u : D.mesh;
+    const float* at = d.attrs[m];
+    const float* rows[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        h.a[k] = at + (size_t)vi[k] * a.C;
-        h.b[k] = r.b[k];
-    }
+    for (int k = 0; k < 3; ++k) rows[k] = at + (size_t)vi[k] * (CC ? (uint32_t)CC : a.C);
+    float sx[3], sy[3], w[3];
+    pixel_windows(a, D, d.meshes[m], vi, sx, sy, w);
+    Interp r;
+    interp_weights(sx, sy, w, (int32_t)(p % (uint32_t)a.W), (int32_t)(p / (uint32_t)a.W), r);
+    blend<CC>(rows, r.b, a.C, put);
     return true;
 }
 
-// Stage the prefix of triangle counts in LDS when it fits (all threads of the block take part).
-__device__ __forceinline__ const uint64_t* stage_bases(const ResolveArgs& a, const uint64_t* __restrict__ bases,
-                                                       uint64_t* s_bases)
+// Bound by gathering, through a chain of three dependent loads (key, indices, vertices and attribute
+// rows), from triangles that neighbouring pixels of a dense mesh do not share.  The channel count is
+// a constant for the usual counts, so that the attribute rows load together with the vertices instead
+// of one channel per round trip (RESOLVE_NOTE).
+template <int CC, int MODE, int WORDS>
+__global__ void __launch_bounds__(256) resolve_kernel(ResolveBlock<WORDS> blk)
 {
-    const bool staged = a.n_meshes <= kLdsBases;
-    if (staged) {
-        for (uint32_t i = threadIdx.x; i <= a.n_meshes; i += blockDim.x) s_bases[i] = bases[i];
-        __syncthreads();
-    }
-    return staged ? s_bases : bases;
-}
-
-__global__ void __launch_bounds__(256) resolve_kernel(ResolveArgs a, const uint64_t* __restrict__ bases,
-                                                      const DrawDesc* __restrict__ pairs,
-                                                      const MeshDesc* __restrict__ meshes,
-                                                      const float* const* __restrict__ attrs)
-{
-    __shared__ uint64_t s_bases[kLdsBases + 1];
-    const uint64_t* B = stage_bases(a, bases, s_bases);
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t npix = (uint64_t)a.W * (uint64_t)a.H;
-    if (p >= npix) return;
-    float* o = a.out + p * a.C;
-    PixelHit h;
-    if (!resolve_hit(a, B, pairs, meshes, attrs, p, h)) {
-        write_zero(a.C, o);
-        return;
-    }
-    for (uint32_t c = 0; c < a.C; ++c) o[c] = (h.b[0] * h.a[0][c] + h.b[1] * h.a[1][c]) + h.b[2] * h.a[2][c];
+    __shared__ ResolveLds<MODE> lds;
+    const ResolveDesc d = stage_desc<MODE>(blk, lds);
+    const ResolveArgs& a = blk.a;
+    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= (uint32_t)a.W * (uint32_t)a.H) return;
+    float* o = a.out + (size_t)p * (CC ? (uint32_t)CC : a.C);
+    if (!resolve_pixel<CC, MODE>(a, d, p, [&](uint32_t c, float v) { gl(o)[c] = v; })) write_zero<CC>(a.C, o);
 }
 
 // Supersampled resolve: the view holds ss x ss samples per output pixel (a visibility buffer of
-// ss W_out x ss H_out); each lane resolves the samples of one output pixel, sums them in fp32 row
-// by row (empty samples add 0) and scales by 1 / ss^2 (exact).
+// ss W_out x ss H_out).  One lane per sample (a pixel's samples are neighbouring lanes: SS_NOTE); the
+// samples' channels meet in LDS, where one lane per (pixel, channel) sums them in fp32 row by row
+// (empty samples add 0) and scales by 1 / ss^2 (exact).
 constexpr uint32_t kMaxChannels = 16;
 
-__global__ void __launch_bounds__(256) resolve_ss_kernel(ResolveArgs a, const uint64_t* __restrict__ bases,
-                                                         const DrawDesc* __restrict__ pairs,
-                                                         const MeshDesc* __restrict__ meshes,
-                                                         const float* const* __restrict__ attrs)
+template <int CC, int MODE, int WORDS>
+__global__ void __launch_bounds__(256) resolve_ss_kernel(ResolveBlock<WORDS> blk)
 {
-    __shared__ uint64_t s_bases[kLdsBases + 1];
-    const uint64_t* B = stage_bases(a, bases, s_bases);
-    const uint32_t k = a.ss;
-    const uint32_t Wo = (uint32_t)a.W / k, Ho = (uint32_t)a.H / k;
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= (uint64_t)Wo * Ho) return;
-    const uint32_t px = (uint32_t)(p % Wo), py = (uint32_t)(p / Wo);
-    float acc[kMaxChannels];
-#pragma unroll
-    for (uint32_t c = 0; c < kMaxChannels; ++c) acc[c] = 0.0f;
-    for (uint32_t sy = 0; sy < k; ++sy)
-        for (uint32_t sx = 0; sx < k; ++sx) {
-            const uint64_t q = (uint64_t)(py * k + sy) * (uint64_t)a.W + (px * k + sx);
-            PixelHit h;
-            if (!resolve_hit(a, B, pairs, meshes, attrs, q, h)) continue;
-#pragma unroll
-            for (uint32_t c = 0; c < kMaxChannels; ++c)
-                if (c < a.C) acc[c] += (h.b[0] * h.a[0][c] + h.b[1] * h.a[1][c]) + h.b[2] * h.a[2][c];
-        }
-    const float scale = 1.0f / (float)(k * k);
-    float* o = a.out + p * a.C;
-#pragma unroll
-    for (uint32_t c = 0; c < kMaxChannels; ++c)
-        if (c < a.C) o[c] = acc[c] * scale;
+    constexpr uint32_t kStride = (CC ? (uint32_t)CC : kMaxChannels) | 1u;   // odd: no bank conflicts
+    __shared__ ResolveLds<MODE> lds;
+    __shared__ float s_val[256 * kStride];
+    const ResolveDesc d = stage_desc<MODE>(blk, lds);
+    const ResolveArgs& a = blk.a;
+    const uint32_t C = CC ? (uint32_t)CC : a.C;
+    const uint32_t ls = a.ss == 2 ? 1u : 2u, k = a.ss, kk = k * k;          // 2 x 2 or 4 x 4 samples
+    const uint32_t Wo = (uint32_t)a.W >> ls, Ho = (uint32_t)a.H >> ls, npix = Wo * Ho;
+    const uint32_t first = blockIdx.x << (8 - 2 * ls);                      // output pixels of this workgroup
+    const uint32_t op = first + (threadIdx.x >> (2 * ls));
+    float* mine = s_val + threadIdx.x * kStride;
+    bool hit = false;
+    if (op < npix) {
+        const uint32_t py = op / Wo, px = op - py * Wo, s = threadIdx.x & (kk - 1);
+        hit = resolve_pixel<CC, MODE>(a, d, ((py << ls) + (s >> ls)) * (uint32_t)a.W + (px << ls) + (s & (k - 1)),
+                                [&](uint32_t c, float v) { mine[c] = v; });
+    }
+    if (!hit)
+        for (uint32_t c = 0; c < C; ++c) mine[c] = 0.0f;
+    __syncthreads();
+    const float scale = 1.0f / (float)kk;
+    const uint32_t items = min(256u >> (2 * ls), npix - min(first, npix)) * C;
+    for (uint32_t it = threadIdx.x; it < items; it += 256) {
+        const uint32_t q = it / C, c = it - q * C;
+        const float* v = s_val + (q << (2 * ls)) * kStride + c;
+        float acc = 0.0f;
+        for (uint32_t s = 0; s < kk; ++s) acc += v[s * kStride];
+        gl(a.out)[(size_t)first * C + it] = acc * scale;
+    }
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -223,53 +336,66 @@ __global__ void __launch_bounds__(256) resolve_ss_kernel(ResolveArgs a, const ui
 // lod = log2 of the larger UV extent of the four hits in texels, clamped to the chain; the colour
 // is the trilinear, wrap-around sample at the pixel's own hit.
 // ----------------------------------------------------------------------------------------------
-__device__ __forceinline__ float4 bilinear(const TexDesc& T, uint32_t l, float u, float v)
+struct Footprint {
+    uint32_t t00, t10, t01, t11;   // the four texels
+    float ax, ay;                  // their weights
+};
+
+__device__ __forceinline__ Footprint texels_at(const TexDesc& T, uint32_t l, float u, float v)
 {
     const uint32_t wl = max(1u, T.w >> l), hl = max(1u, T.h >> l);
     const CURAST_GLOBAL uint32_t* L = gl(T.texels) + T.off[l];
     const float fu = u - floorf(u), fv = v - floorf(v);
     const float x = fu * (float)wl - 0.5f, y = fv * (float)hl - 0.5f;
     const float x0 = floorf(x), y0 = floorf(y);
-    const float ax = x - x0, ay = y - y0;
     // x0 lies in [-1, wl - 1] and y0 in [-1, hl - 1]; the clamps only guard the addressing
     const int32_t ix = (int32_t)x0, iy = (int32_t)y0;
     const uint32_t i0 = min(ix < 0 ? wl - 1 : (uint32_t)ix, wl - 1), i1 = ix + 1 >= (int32_t)wl ? 0u : (uint32_t)(ix + 1);
     const uint32_t j0 = min(iy < 0 ? hl - 1 : (uint32_t)iy, hl - 1), j1 = iy + 1 >= (int32_t)hl ? 0u : (uint32_t)(iy + 1);
-    const uint32_t t00 = L[(size_t)j0 * wl + i0], t10 = L[(size_t)j0 * wl + min(i1, wl - 1)];
-    const uint32_t t01 = L[(size_t)min(j1, hl - 1) * wl + i0], t11 = L[(size_t)min(j1, hl - 1) * wl + min(i1, wl - 1)];
+    Footprint f;
+    f.t00 = L[(size_t)j0 * wl + i0];
+    f.t10 = L[(size_t)j0 * wl + min(i1, wl - 1)];
+    f.t01 = L[(size_t)min(j1, hl - 1) * wl + i0];
+    f.t11 = L[(size_t)min(j1, hl - 1) * wl + min(i1, wl - 1)];
+    f.ax = x - x0;
+    f.ay = y - y0;
+    return f;
+}
+
+__device__ __forceinline__ float4 bilinear(const Footprint& f)
+{
     const float k = 1.0f / 255.0f;
     float r[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const float c00 = (float)((t00 >> (8 * c)) & 0xFFu) * k, c10 = (float)((t10 >> (8 * c)) & 0xFFu) * k;
-        const float c01 = (float)((t01 >> (8 * c)) & 0xFFu) * k, c11 = (float)((t11 >> (8 * c)) & 0xFFu) * k;
-        const float r0 = c00 + ax * (c10 - c00);
-        const float r1 = c01 + ax * (c11 - c01);
-        r[c] = r0 + ay * (r1 - r0);
+        const float c00 = (float)((f.t00 >> (8 * c)) & 0xFFu) * k, c10 = (float)((f.t10 >> (8 * c)) & 0xFFu) * k;
+        const float c01 = (float)((f.t01 >> (8 * c)) & 0xFFu) * k, c11 = (float)((f.t11 >> (8 * c)) & 0xFFu) * k;
+        const float r0 = c00 + f.ax * (c10 - c00);
+        const float r1 = c01 + f.ax * (c11 - c01);
+        r[c] = r0 + f.ay * (r1 - r0);
     }
     return make_float4(r[0], r[1], r[2], r[3]);
 }
 
-__global__ void __launch_bounds__(256) resolve_textured_kernel(ResolveArgs a, const uint64_t* __restrict__ bases,
-                                                               const DrawDesc* __restrict__ pairs,
-                                                               const MeshDesc* __restrict__ meshes,
-                                                               const float* const* __restrict__ uvs,
-                                                               const TexDesc* __restrict__ texs)
+template <int MODE, int WORDS>
+__global__ void __launch_bounds__(256) resolve_textured_kernel(ResolveBlock<WORDS> blk)
 {
-    __shared__ uint64_t s_bases[kLdsBases + 1];
-    const uint64_t* B = stage_bases(a, bases, s_bases);
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= (uint64_t)a.W * (uint64_t)a.H) return;
+    __shared__ ResolveLds<MODE> lds;
+    const ResolveDesc d = stage_desc<MODE>(blk, lds);
+    const ResolveArgs& a = blk.a;
+    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= (uint32_t)a.W * (uint32_t)a.H) return;
     CURAST_GLOBAL float4* o = (CURAST_GLOBAL float4*)gl(a.out) + p;
     uint32_t pr, vi[3];
-    if (!pixel_triangle(a, B, pairs, meshes, p, pr, vi)) {
+    if (!pixel_triangle<MODE>(a, d, p, pr, vi)) {
         *o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         return;
     }
-    const DrawDesc& D = pairs[pr];
-    const MeshDesc& M = meshes[D.mesh];
+    const DrawDesc& D = d.pairs[pr];
+    const uint32_t m = MODE == kDescOne ? 0u : D.mesh;
+    const MeshDesc& M = d.meshes[m];
     float cx[3], cy[3], cw[3], tu[3], tv[3];
-    const CURAST_GLOBAL float* uv = gl(uvs[D.mesh]);
+    const CURAST_GLOBAL float* uv = gl(d.attrs[m]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         float q[3];
@@ -281,7 +407,7 @@ __global__ void __launch_bounds__(256) resolve_textured_kernel(ResolveArgs a, co
         tu[k] = uv[2 * (size_t)vi[k]];
         tv[k] = uv[2 * (size_t)vi[k] + 1];
     }
-    const int32_t px = (int32_t)(p % (uint64_t)a.W), py = (int32_t)(p / (uint64_t)a.W);
+    const int32_t px = (int32_t)(p % (uint32_t)a.W), py = (int32_t)(p / (uint32_t)a.W);
     float su[4], sv[4];
     bool finite = true;
 #pragma unroll
@@ -306,7 +432,7 @@ __global__ void __launch_bounds__(256) resolve_textured_kernel(ResolveArgs a, co
         *o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         return;
     }
-    const TexDesc& T = texs[D.mesh];
+    const TexDesc& T = d.tex[m];
     const float top = (float)(T.levels - 1);
     float lod = top;
     if (finite) {
@@ -325,9 +451,14 @@ __global__ void __launch_bounds__(256) resolve_textured_kernel(ResolveArgs a, co
     }
     const uint32_t l0 = (uint32_t)floorf(lod);
     const float t = lod - (float)l0;
-    float4 c = bilinear(T, l0, su[0], sv[0]);
-    if (t > 0.0f && l0 + 1 < T.levels) {
-        const float4 c1 = bilinear(T, l0 + 1, su[0], sv[0]);
+    // the texels of both levels are loaded before either is filtered
+    const bool two = t > 0.0f && l0 + 1 < T.levels;
+    const Footprint f0 = texels_at(T, l0, su[0], sv[0]);
+    Footprint f1 = f0;
+    if (two) f1 = texels_at(T, l0 + 1, su[0], sv[0]);
+    float4 c = bilinear(f0);
+    if (two) {
+        const float4 c1 = bilinear(f1);
         c.x = c.x + t * (c1.x - c.x);
         c.y = c.y + t * (c1.y - c.y);
         c.z = c.z + t * (c1.z - c.z);
@@ -361,39 +492,49 @@ __global__ void __launch_bounds__(256) mip_kernel(const uint32_t* __restrict__ s
 // ----------------------------------------------------------------------------------------------
 // Screen-space (differentiable) resolve of one mesh and its backward pass
 // ----------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool screen_tri(const ScreenArgs& a, uint64_t p, uint32_t vi[3])
+__device__ __forceinline__ bool screen_tri(const ScreenArgs& a, uint32_t p, uint32_t (&vi)[3])
 {
-    const unsigned long long key = a.vis[p];
+    const unsigned long long key = gl(a.vis)[p];
     if (key == kEmptyKey) return false;
     const uint64_t id = key & kIdMask;
     if (id < a.id_base || id - a.id_base >= a.T) return false;
-    const uint64_t t = id - a.id_base;
-    vi[0] = a.idx[3 * t];
-    vi[1] = a.idx[3 * t + 1];
-    vi[2] = a.idx[3 * t + 2];
+    const CURAST_GLOBAL uint32_t* ip = gl(a.idx) + 3 * (id - a.id_base);
+    vi[0] = ip[0];
+    vi[1] = ip[1];
+    vi[2] = ip[2];
     return vi[0] < a.V && vi[1] < a.V && vi[2] < a.V;
 }
 
-__global__ void __launch_bounds__(256) resolve_screen_kernel(ScreenArgs a)
+__device__ __forceinline__ void screen_windows(const ScreenArgs& a, const uint32_t (&vi)[3], float (&sx)[3],
+                                               float (&sy)[3], float (&w)[3])
 {
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= (uint64_t)a.W * (uint64_t)a.H) return;
-    float* o = a.out + p * a.C;
-    uint32_t vi[3];
-    if (!screen_tri(a, p, vi)) {
-        write_zero(a.C, o);
-        return;
-    }
-    float sx[3], sy[3], w[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        sx[k] = a.pos_ss[3 * (size_t)vi[k]];
-        sy[k] = a.pos_ss[3 * (size_t)vi[k] + 1];
-        w[k] = a.pos_ss[3 * (size_t)vi[k] + 2];
+        const CURAST_GLOBAL float* q = gl(a.pos_ss) + 3 * (size_t)vi[k];
+        sx[k] = q[0];
+        sy[k] = q[1];
+        w[k] = q[2];
     }
+}
+
+template <int CC>
+__global__ void __launch_bounds__(256) resolve_screen_kernel(ScreenArgs a)
+{
+    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= (uint32_t)a.W * (uint32_t)a.H) return;
+    const uint32_t C = CC ? (uint32_t)CC : a.C;
+    float* o = a.out + (size_t)p * C;
+    uint32_t vi[3];
+    if (!screen_tri(a, p, vi)) {
+        write_zero<CC>(C, o);
+        return;
+    }
+    const float* rows[3] = {a.attrs + (size_t)vi[0] * C, a.attrs + (size_t)vi[1] * C, a.attrs + (size_t)vi[2] * C};
+    float sx[3], sy[3], w[3];
+    screen_windows(a, vi, sx, sy, w);
     Interp r;
-    interp_weights(sx, sy, w, (int32_t)(p % (uint64_t)a.W), (int32_t)(p / (uint64_t)a.W), r);
-    write_interp(r, a.attrs + (size_t)vi[0] * a.C, a.attrs + (size_t)vi[1] * a.C, a.attrs + (size_t)vi[2] * a.C, a.C, o);
+    interp_weights(sx, sy, w, (int32_t)(p % (uint32_t)a.W), (int32_t)(p / (uint32_t)a.W), r);
+    blend<CC>(rows, r.b, C, [&](uint32_t c, float v) { gl(o)[c] = v; });
 }
 
 // Backward with visibility held fixed.  The chain rule of one pixel has cancelling terms
@@ -481,23 +622,18 @@ __global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
     const uint32_t tiles_x = ((uint32_t)a.W + 15u) / 16u;
     const uint32_t x = (blockIdx.x % tiles_x) * 16u + (threadIdx.x & 15u);
     const uint32_t y = (blockIdx.x / tiles_x) * 16u + (threadIdx.x >> 4);
-    const uint64_t p = (uint64_t)y * (uint64_t)a.W + x;
+    const uint32_t p = y * (uint32_t)a.W + x;
     uint32_t vi[3] = {~0u, ~0u, ~0u};
     const bool have = x < (uint32_t)a.W && y < (uint32_t)a.H && screen_tri(a, p, vi);
     BwdTerms t = {};
     double G[3] = {0.0, 0.0, 0.0};
     if (have) {
         float sx[3], sy[3], w[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            sx[k] = a.pos_ss[3 * (size_t)vi[k]];
-            sy[k] = a.pos_ss[3 * (size_t)vi[k] + 1];
-            w[k] = a.pos_ss[3 * (size_t)vi[k] + 2];
-        }
+        screen_windows(a, vi, sx, sy, w);
         bwd_terms(sx, sy, w, x, y, t);
     }
     // attribute gradients g b_k, and G_k = g . a_k
-    const float* g = a.grad_out + (have ? p : 0) * a.C;
+    const float* g = a.grad_out + (size_t)(have ? p : 0) * a.C;
     for (uint32_t c = 0; c < a.C; ++c) {
         const double gc = have ? (double)g[c] : 0.0;
 #pragma unroll
@@ -546,38 +682,26 @@ __global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
 // with the same fp32 operations, and applies the chain rule above; attribute gradients of every
 // instance of a mesh add into the mesh's rows, position gradients (to the unsnapped window
 // positions of one-instance meshes) where the mesh has a gradient buffer.  One atomic per value.
-__global__ void __launch_bounds__(256) resolve_backward_meshes_kernel(ResolveArgs a, const uint64_t* __restrict__ bases,
-                                                                      const DrawDesc* __restrict__ pairs,
-                                                                      const MeshDesc* __restrict__ meshes,
-                                                                      const float* const* __restrict__ attrs)
+__global__ void __launch_bounds__(256) resolve_backward_meshes_kernel(ResolveBlock<kResolveWordsOne> blk)
 {
-    __shared__ uint64_t s_bases[kLdsBases + 1];
-    const uint64_t* B = stage_bases(a, bases, s_bases);
-    const uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= (uint64_t)a.W * (uint64_t)a.H) return;
+    __shared__ ResolveLds<kDescDevice> lds;
+    const ResolveDesc d = stage_desc<kDescDevice>(blk, lds);
+    const ResolveArgs& a = blk.a;
+    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= (uint32_t)a.W * (uint32_t)a.H) return;
     uint32_t pair, vi[3];
-    if (!pixel_triangle(a, B, pairs, meshes, p, pair, vi)) return;
-    const DrawDesc& D = pairs[pair];
+    if (!pixel_triangle<kDescDevice>(a, d, p, pair, vi)) return;
+    const DrawDesc& D = d.pairs[pair];
     const uint32_t m = D.mesh;
-    const MeshDesc& M = meshes[m];
     float sx[3], sy[3], w[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        float q[3];
-        mesh_vertex(M, vi[k], q);
-        const Clip c = transform(D.A, q[0], q[1], q[2]);
-        const float zI = 1.0f / c.w;
-        sx[k] = __builtin_fmaf(c.x * zI, a.hW, a.hW);
-        sy[k] = __builtin_fmaf(c.y * zI, a.hH, a.hH);
-        w[k] = c.w;
-    }
-    const uint32_t x = (uint32_t)(p % (uint64_t)a.W), y = (uint32_t)(p / (uint64_t)a.W);
+    pixel_windows(a, D, d.meshes[m], vi, sx, sy, w);
+    const uint32_t x = p % (uint32_t)a.W, y = p / (uint32_t)a.W;
     BwdTerms t;
     bwd_terms(sx, sy, w, x, y, t);
-    const float* at = attrs[m];
+    const float* at = d.attrs[m];
     float* ga = a.grad_attrs[m];
     float* gp = a.grad_pos ? a.grad_pos[m] : nullptr;
-    const float* g = a.grad_out + p * a.C;
+    const float* g = a.grad_out + (size_t)p * a.C;
     double G[3] = {0.0, 0.0, 0.0};
     for (uint32_t c = 0; c < a.C; ++c) {
         const double gc = (double)g[c];
@@ -615,23 +739,40 @@ hipError_t launch_project(const MeshDesc& mesh, const float A[12], float hW, flo
     return hipGetLastError();
 }
 
-hipError_t launch_resolve(const ResolveArgs& a, hipStream_t s)
+// Pixels fit 32 bits: views are at most 16384 x 16384.
+static uint32_t pixels(const ResolveArgs& a) { return (uint32_t)a.W * (uint32_t)a.H; }
+
+template <int MODE, int WORDS>
+static hipError_t resolve_any(const ResolveBlock<WORDS>& b, hipStream_t s)
 {
-    if (a.ss > 1) {
-        const uint64_t out_pixels = (uint64_t)(a.W / a.ss) * (uint64_t)(a.H / a.ss);
-        resolve_ss_kernel<<<blocks_for(out_pixels), 256, 0, s>>>(a, a.bases, a.pairs, a.meshes, a.attrs);
+    const ResolveArgs& a = b.a;
+    if (a.textured) {
+        resolve_textured_kernel<MODE, WORDS><<<blocks_for(pixels(a)), 256, 0, s>>>(b);
     } else {
-        resolve_kernel<<<blocks_for((uint64_t)a.W * (uint64_t)a.H), 256, 0, s>>>(a, a.bases, a.pairs, a.meshes,
-                                                                                 a.attrs);
+        with_channels(a.C, [&](auto cc) {
+            constexpr int CC = decltype(cc)::value;
+            if (a.ss > 1) resolve_ss_kernel<CC, MODE, WORDS><<<blocks_for(pixels(a)), 256, 0, s>>>(b);
+            else resolve_kernel<CC, MODE, WORDS><<<blocks_for(pixels(a)), 256, 0, s>>>(b);
+        });
     }
     return hipGetLastError();
 }
 
-hipError_t launch_resolve_textured(const ResolveArgs& a, hipStream_t s)
+// Descriptors in device memory (`words` 0) or as part of the argument.
+hipError_t launch_resolve(const ResolveBlock<kResolveWords>& b, hipStream_t s)
 {
-    resolve_textured_kernel<<<blocks_for((uint64_t)a.W * (uint64_t)a.H), 256, 0, s>>>(a, a.bases, a.pairs, a.meshes,
-                                                                                      a.attrs, a.tex);
-    return hipGetLastError();
+    if (b.words && !(b.a.n_meshes == 1 && b.a.n_pairs == 1)) return resolve_any<kDescInline>(b, s);
+    ResolveBlock<kResolveWordsOne> o;
+    if (b.words > (uint32_t)kResolveWordsOne) return hipErrorInvalidValue;
+    for (uint32_t i = 0; i < b.words; ++i) o.w[i] = b.w[i];
+    o.words = b.words;
+    o.off_mpair = b.off_mpair;
+    o.off_pairs = b.off_pairs;
+    o.off_meshes = b.off_meshes;
+    o.off_attrs = b.off_attrs;
+    o.off_tex = b.off_tex;
+    o.a = b.a;
+    return b.words ? resolve_any<kDescOne>(o, s) : resolve_any<kDescDevice>(o, s);
 }
 
 // Levels 1 .. levels - 1 from level 0, one launch per level (each reads the previous one).
@@ -649,7 +790,9 @@ hipError_t launch_build_mips(uint32_t* texels, uint32_t w, uint32_t h, uint32_t 
 
 hipError_t launch_resolve_screen(const ScreenArgs& a, hipStream_t s)
 {
-    resolve_screen_kernel<<<blocks_for((uint64_t)a.W * (uint64_t)a.H), 256, 0, s>>>(a);
+    with_channels(a.C, [&](auto cc) {
+        resolve_screen_kernel<decltype(cc)::value><<<blocks_for((uint64_t)a.W * (uint64_t)a.H), 256, 0, s>>>(a);
+    });
     return hipGetLastError();
 }
 
@@ -660,10 +803,9 @@ hipError_t launch_resolve_backward(const ScreenArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_resolve_backward_meshes(const ResolveArgs& a, hipStream_t s)
+hipError_t launch_resolve_backward_meshes(const ResolveBlock<kResolveWordsOne>& b, hipStream_t s)
 {
-    resolve_backward_meshes_kernel<<<blocks_for((uint64_t)a.W * (uint64_t)a.H), 256, 0, s>>>(a, a.bases, a.pairs,
-                                                                                             a.meshes, a.attrs);
+    resolve_backward_meshes_kernel<<<blocks_for(pixels(b.a)), 256, 0, s>>>(b);
     return hipGetLastError();
 }
 

@@ -41,12 +41,11 @@ hipError_t launch_compress_ranges(const uint32_t* idx, uint64_t n_idx, const flo
 hipError_t launch_compress(const uint32_t* idx, uint64_t n_idx, uint32_t bits, uint32_t base, uint32_t* packed,
                            uint64_t words, const float* pos, uint32_t V, const float lo[3], const float scale[3],
                            uint16_t* qpos, hipStream_t s);
-hipError_t launch_resolve(const ResolveArgs& a, hipStream_t s);
-hipError_t launch_resolve_textured(const ResolveArgs& a, hipStream_t s);
+hipError_t launch_resolve(const ResolveBlock<kResolveWords>& b, hipStream_t s);
 hipError_t launch_build_mips(uint32_t* texels, uint32_t w, uint32_t h, uint32_t levels, hipStream_t s);
 hipError_t launch_resolve_screen(const ScreenArgs& a, hipStream_t s);
 hipError_t launch_resolve_backward(const ScreenArgs& a, hipStream_t s);
-hipError_t launch_resolve_backward_meshes(const ResolveArgs& a, hipStream_t s);
+hipError_t launch_resolve_backward_meshes(const ResolveBlock<kResolveWordsOne>& b, hipStream_t s);
 }  // namespace curast
 
 using namespace curast;
@@ -1085,23 +1084,35 @@ void collect_timings(curast_ctx* ctx)
 }
 
 int build_resolve_desc(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const curast_view& view,
-                       const float* const* attrs, const curast_texture* textures, ResolveArgs& a, size_t& bytes_out,
-                       float* const* grad_attrs = nullptr, float* const* grad_pos = nullptr)
+                       const float* const* attrs, const curast_texture* textures, ResolveBlock<kResolveWords>& blk,
+                       size_t& bytes_out, float* const* grad_attrs = nullptr, float* const* grad_pos = nullptr)
 {
+    ResolveArgs& a = blk.a;
+    a = ResolveArgs{};
     uint64_t np = 0;
     for (uint32_t m = 0; m < M; ++m) np += n_inst(meshes[m]);
     if (np > 0xFFFFFFF0ull) return fail(ctx, CURAST_E_INVALID, "too many (mesh, instance) pairs");
     const size_t off_bases = 0;
-    const size_t off_mpair = align_up(sizeof(uint64_t) * ((size_t)M + 1), 256);
-    const size_t off_pairs = align_up(off_mpair + sizeof(uint32_t) * std::max<uint32_t>(M, 1), 256);
-    const size_t off_meshes = align_up(off_pairs + sizeof(DrawDesc) * std::max<uint64_t>(np, 1), 256);
-    const size_t off_attrs = align_up(off_meshes + sizeof(MeshDesc) * std::max<uint32_t>(M, 1), 256);
-    const size_t off_tex = align_up(off_attrs + sizeof(float*) * std::max<uint32_t>(M, 1), 256);
-    const size_t off_grad = textures ? align_up(off_tex + sizeof(TexDesc) * std::max<uint32_t>(M, 1), 256) : off_tex;
-    const size_t bytes = grad_attrs ? align_up(off_grad + 2 * sizeof(float*) * std::max<uint32_t>(M, 1), 256) : off_grad;
-    int rc = ensure_staging(ctx, ctx->resolve_stage, bytes);
-    if (rc) return rc;
-    char* h = static_cast<char*>(ctx->resolve_stage.host);
+    const size_t off_mpair = align_up(sizeof(uint64_t) * ((size_t)M + 1), 16);
+    const size_t off_pairs = align_up(off_mpair + sizeof(uint32_t) * std::max<uint32_t>(M, 1), 16);
+    const size_t off_meshes = align_up(off_pairs + sizeof(DrawDesc) * std::max<uint64_t>(np, 1), 16);
+    const size_t off_attrs = align_up(off_meshes + sizeof(MeshDesc) * std::max<uint32_t>(M, 1), 16);
+    const size_t off_tex = align_up(off_attrs + sizeof(float*) * std::max<uint32_t>(M, 1), 16);
+    const size_t off_grad = textures ? align_up(off_tex + sizeof(TexDesc) * std::max<uint32_t>(M, 1), 16) : off_tex;
+    const size_t bytes = grad_attrs ? align_up(off_grad + 2 * sizeof(float*) * std::max<uint32_t>(M, 1), 16) : off_grad;
+    // small blocks travel in the kernel argument (the forward resolves)
+    const bool inl = !grad_attrs && bytes <= sizeof(blk.w);
+    if (!inl) {
+        const int rc = ensure_staging(ctx, ctx->resolve_stage, bytes);
+        if (rc) return rc;
+    }
+    blk.words = inl ? (uint32_t)((bytes + 3) / 4) : 0;
+    blk.off_mpair = (uint32_t)off_mpair;
+    blk.off_pairs = (uint32_t)off_pairs;
+    blk.off_meshes = (uint32_t)off_meshes;
+    blk.off_attrs = (uint32_t)off_attrs;
+    blk.off_tex = (uint32_t)off_tex;
+    char* h = inl ? reinterpret_cast<char*>(blk.w) : static_cast<char*>(ctx->resolve_stage.host);
     uint64_t* bases = reinterpret_cast<uint64_t*>(h + off_bases);
     uint32_t* mpair = reinterpret_cast<uint32_t*>(h + off_mpair);
     DrawDesc* pairs = reinterpret_cast<DrawDesc*>(h + off_pairs);
@@ -1142,7 +1153,7 @@ int build_resolve_desc(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, c
         }
     }
     bases[M] = base;
-    char* d = static_cast<char*>(ctx->resolve_stage.dev);
+    char* d = inl ? nullptr : static_cast<char*>(ctx->resolve_stage.dev);
     a.vis = reinterpret_cast<const unsigned long long*>(view.visbuffer);
     a.W = view.width;
     a.H = view.height;
@@ -1371,6 +1382,32 @@ int curast_project(curast_ctx* ctx, const curast_mesh* mesh, uint32_t instance, 
 }
 
 namespace {
+// Uploads a descriptor block that does not travel in the kernel argument.
+int upload_resolve_desc(curast_ctx* ctx, size_t bytes, hipStream_t s)
+{
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->resolve_stage.dev, ctx->resolve_stage.host, bytes, hipMemcpyHostToDevice, s));
+    HIP_TRY(ctx, hipEventRecord(ctx->resolve_stage.ev, s));
+    ctx->resolve_stage.pending = true;
+    return CURAST_OK;
+}
+
+// Launches a forward resolve of either kind.
+int enqueue_resolve(curast_ctx* ctx, const ResolveBlock<kResolveWords>& blk, size_t bytes, hipStream_t s)
+{
+    if (!blk.words) {
+        const int rc = upload_resolve_desc(ctx, bytes, s);
+        if (rc) return rc;
+    }
+    TimedFrame* tf = begin_timing(ctx);
+    if (tf) hipEventRecord(tf->ev[7], s);
+    HIP_TRY(ctx, launch_resolve(blk, s));
+    if (tf) {
+        hipEventRecord(tf->ev[8], s);
+        tf->used[kTResolve] = 1;
+    }
+    return CURAST_OK;
+}
+
 int resolve_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const curast_view* view,
                  const float* const* attrs, uint32_t C, float* out, uint32_t ss, void* stream)
 {
@@ -1392,24 +1429,14 @@ int resolve_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const c
     }
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ResolveArgs a{};
+    ResolveBlock<kResolveWords> blk;
     size_t bytes = 0;
-    rc = build_resolve_desc(ctx, meshes, M, *view, attrs, nullptr, a, bytes);
+    rc = build_resolve_desc(ctx, meshes, M, *view, attrs, nullptr, blk, bytes);
     if (rc) return rc;
-    a.C = C;
-    a.out = out;
-    a.ss = ss;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->resolve_stage.dev, ctx->resolve_stage.host, bytes, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->resolve_stage.ev, s));
-    ctx->resolve_stage.pending = true;
-    TimedFrame* tf = begin_timing(ctx);
-    if (tf) hipEventRecord(tf->ev[7], s);
-    HIP_TRY(ctx, launch_resolve(a, s));
-    if (tf) {
-        hipEventRecord(tf->ev[8], s);
-        tf->used[kTResolve] = 1;
-    }
-    return CURAST_OK;
+    blk.a.C = C;
+    blk.a.out = out;
+    blk.a.ss = ss;
+    return enqueue_resolve(ctx, blk, bytes, s);
 }
 }  // namespace
 
@@ -1470,24 +1497,15 @@ int curast_resolve_textured(curast_ctx* ctx, const curast_mesh* meshes, uint32_t
     }
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ResolveArgs a{};
+    ResolveBlock<kResolveWords> blk;
     size_t bytes = 0;
-    rc = build_resolve_desc(ctx, meshes, M, *view, uvs, textures, a, bytes);
+    rc = build_resolve_desc(ctx, meshes, M, *view, uvs, textures, blk, bytes);
     if (rc) return rc;
-    a.C = 2;
-    a.out = out;
-    a.ss = 1;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->resolve_stage.dev, ctx->resolve_stage.host, bytes, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->resolve_stage.ev, s));
-    ctx->resolve_stage.pending = true;
-    TimedFrame* tf = begin_timing(ctx);
-    if (tf) hipEventRecord(tf->ev[7], s);
-    HIP_TRY(ctx, launch_resolve_textured(a, s));
-    if (tf) {
-        hipEventRecord(tf->ev[8], s);
-        tf->used[kTResolve] = 1;
-    }
-    return CURAST_OK;
+    blk.a.textured = 1;
+    blk.a.C = 2;
+    blk.a.out = out;
+    blk.a.ss = 1;
+    return enqueue_resolve(ctx, blk, bytes, s);
 }
 
 namespace {
@@ -1653,18 +1671,19 @@ int curast_resolve_backward_meshes(curast_ctx* ctx, const curast_mesh* meshes, u
     }
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ResolveArgs a{};
+    ResolveBlock<kResolveWords> blk;
     size_t bytes = 0;
-    rc = build_resolve_desc(ctx, meshes, M, *view, attrs, nullptr, a, bytes, grad_attrs, grad_pos);
+    rc = build_resolve_desc(ctx, meshes, M, *view, attrs, nullptr, blk, bytes, grad_attrs, grad_pos);
     if (rc) return rc;
-    a.C = C;
-    a.grad_out = grad_out;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->resolve_stage.dev, ctx->resolve_stage.host, bytes, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->resolve_stage.ev, s));
-    ctx->resolve_stage.pending = true;
+    blk.a.C = C;
+    blk.a.grad_out = grad_out;
+    ResolveBlock<kResolveWordsOne> dev{};
+    dev.a = blk.a;
+    rc = upload_resolve_desc(ctx, bytes, s);
+    if (rc) return rc;
     TimedFrame* tf = begin_timing(ctx);
     if (tf) hipEventRecord(tf->ev[7], s);
-    HIP_TRY(ctx, launch_resolve_backward_meshes(a, s));
+    HIP_TRY(ctx, launch_resolve_backward_meshes(dev, s));
     if (tf) {
         hipEventRecord(tf->ev[8], s);
         tf->used[kTResolveBwd] = 1;
