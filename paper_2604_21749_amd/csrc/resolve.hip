@@ -559,19 +559,21 @@ __global__ void __launch_bounds__(256) resolve_screen_kernel(ScreenArgs a)
 
 // Backward with visibility held fixed.  The chain rule of one pixel has cancelling terms
 // (G_j - sum_k G_k b_k, the cross-product partials of sliver triangles), so it is evaluated in
-// fp64 from the fp32 inputs and each contribution is rounded once into the fp32 atomic sums:
+// fp64 from the fp32 inputs:
 //   dL/da_k = g b_k;  G_k = g . a_k;  dL/dq_j = (G_j - sum_k G_k b_k) / s;
 //   dL/dlambda_j = dL/dq_j zI_j;  dL/dw_j = -(dL/dq_j lambda_j) zI_j^2;
 //   lambda_0 = d1 x d2, lambda_1 = d2 x d0, lambda_2 = d0 x d1 with d_k = s_k - pixel centre.
 //
-// Workgroups take 16 x 16 pixel tiles: neighbouring pixels reach neighbouring vertices of a dense
-// mesh, so the atomics a workgroup issues close together in time fall on fewer cache lines.  The
-// atomics themselves are performed at the memory side, one request per cache-line sector and
-// instruction, so each wavefront stages the rows its 64 pixels add to (3 vertices x (C + 3) values)
-// in LDS and issues them with neighbouring lanes on neighbouring components of one row: the three
-// adds of a row then travel as one request instead of three (C <= kBwdStageC; more channels take
-// one atomic per lane and value).
-constexpr uint32_t kBwdStageC = 4;
+// Each contribution is rounded once to fp32.  Device-scope fp32 atomics are performed at the memory
+// side, one request per 64-byte sector and instruction, about 16 G requests/s: that rate bounds the
+// kernels, not the bytes.  So a workgroup adds the contributions of its 16 x 16 pixel tile in LDS first,
+// one table row (C attribute and 3 position components) per vertex, and then issues one atomic per
+// touched row and component, neighbouring lanes on neighbouring components and rows.  Vertices hash to
+// their low bits, so that the rows of neighbouring vertices, which share sectors, stay neighbours in
+// the table.  1.85 M requests (2.25 M with one staged row per pixel and vertex) for 0.46 M pixels of a
+// 10M-triangle mesh take 105 us, 143 before; 0.2 M pixels of coarser meshes, 4 channels and positions,
+// 269 us with an atomic per value and 57 here.
+constexpr uint32_t kBwdSlots = 1024;           // at most 3 x 256 vertices per tile: never full
 
 // The fp64 terms of one pixel's chain rule, from the fp32 window positions (sx, sy, w) of its
 // triangle's vertices and the pixel (x, y).
@@ -625,75 +627,148 @@ __device__ __forceinline__ void bwd_pos(const BwdTerms& t, const double (&G)[3],
     }
 }
 
-__device__ __forceinline__ void wave_sync()
+// Table row of a vertex, inserted when it is new (`first`).  Colliding vertices step by an odd distance
+// taken from their high bits.
+template <class Key>
+__device__ __forceinline__ uint32_t bwd_slot(Key* keys, Key key, uint32_t v, bool& first)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t h = v & (kBwdSlots - 1);
+    const uint32_t step = ((v / kBwdSlots) * 2654435761u >> 20) | 1u;
+    while (true) {
+        const Key prev = atomicCAS(keys + h, (Key)~(Key)0, key);
+        first = prev == (Key)~(Key)0;
+        if (first || prev == key) return h;
+        h = (h + step) & (kBwdSlots - 1);
+    }
 }
 
-__global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
-{
-    __shared__ uint32_t s_vid[4][192];
-    __shared__ float s_att[4][192 * kBwdStageC];
-    __shared__ float s_pos[4][192 * 3];
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const bool staged = a.C <= kBwdStageC;
-    const uint32_t tiles_x = ((uint32_t)a.W + 15u) / 16u;
-    const uint32_t x = (blockIdx.x % tiles_x) * 16u + (threadIdx.x & 15u);
-    const uint32_t y = (blockIdx.x / tiles_x) * 16u + (threadIdx.x >> 4);
-    const uint32_t p = y * (uint32_t)a.W + x;
-    uint32_t vi[3] = {~0u, ~0u, ~0u};
-    const bool have = x < (uint32_t)a.W && y < (uint32_t)a.H && screen_tri(a, p, vi);
-    BwdTerms t = {};
-    double G[3] = {0.0, 0.0, 0.0};
-    if (have) {
-        float sx[3], sy[3], w[3];
-        screen_windows(a, vi, sx, sy, w);
-        bwd_terms(sx, sy, w, x, y, t);
-    }
-    // attribute gradients g b_k, and G_k = g . a_k
-    const float* g = a.grad_out + (size_t)(have ? p : 0) * a.C;
-    for (uint32_t c = 0; c < a.C; ++c) {
-        const double gc = have ? (double)g[c] : 0.0;
+// A pixel's upstream gradient and the attribute rows of its three vertices, G channels from c0 on,
+// loaded together.
+template <int CC, bool POS>
+struct BwdChannels {
+    static constexpr uint32_t G = CC == 0 || CC > 4 ? 4 : CC;
+    float g[G], at[3][G];
+    __device__ __forceinline__ void load(const float* const (&rows)[3], const float* grad, uint32_t c0, uint32_t n)
+    {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            if (have) G[k] += gc * (double)a.attrs[(size_t)vi[k] * a.C + c];
-            const float v = (float)(gc * t.b[k]);
-            if (staged) s_att[wave][(3 * lane + k) * a.C + c] = v;
-            else if (have) unsafeAtomicAdd(a.grad_attr + (size_t)vi[k] * a.C + c, v);
+        for (uint32_t c = 0; c < G; ++c) {
+            const bool in = CC || c0 + c < n;
+            g[c] = in ? gl(grad)[c0 + c] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) at[k][c] = POS && in ? gl(rows[k])[c0 + c] : 0.0f;
         }
     }
-    // position gradients
-    float gpos[3][3] = {};
-    if (a.grad_pos && have) bwd_pos(t, G, gpos);
-    if (!staged) {
-        if (a.grad_pos && have)
+};
+
+// The table rows of one pixel's vertices, and the contributions it adds to them: attribute gradients
+// g b_k and, with POS and `pos`, the position gradients.  The pixel that inserted a row stores into it
+// (`store`, which also makes clearing the rows unnecessary), then, after a barrier, the others add
+// (`add`): LDS float atomics are slow, and most rows of a dense mesh have one pixel.
+template <int CC, bool POS>
+struct BwdPixel {
+    static constexpr uint32_t G4 = BwdChannels<CC, POS>::G;
+    static constexpr bool kKeep = CC >= 1 && CC <= 4;   // attribute gradients kept in registers until `add`
+    uint32_t slot[3];
+    bool first[3], pos;
+    double b[3];
+    float gatt[kKeep ? 3 : 1][G4], gpos[3][3];
+
+    __device__ __forceinline__ void store(const BwdTerms& t, const float* const (&rows)[3], const float* grad,
+                                          uint32_t C, BwdChannels<CC, POS> ch, float* val)
+    {
+        const uint32_t n = CC ? (uint32_t)CC : C, S = n + 3;
+        double G[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (uint32_t c0 = 0; c0 < n; c0 += G4) {
+            if (c0) ch.load(rows, grad, c0, n);
+#pragma unroll
+            for (uint32_t c = 0; c < G4; ++c)
+                if (CC || c0 + c < n)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        G[k] += (double)ch.g[c] * (double)ch.at[k][c];
+                        const float v = (float)((double)ch.g[c] * t.b[k]);
+                        if constexpr (kKeep) gatt[k][c] = v;
+                        if (first[k]) val[slot[k] * S + c0 + c] = v;
+                    }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) b[k] = t.b[k];
+        if constexpr (POS) {
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int j = 0; j < 3; ++j) unsafeAtomicAdd(a.grad_pos + 3 * (size_t)vi[k] + j, gpos[k][j]);
-        return;
-    }
+                for (int j = 0; j < 3; ++j) gpos[k][j] = 0.0f;
+            if (pos) bwd_pos(t, G, gpos);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        s_vid[wave][3 * lane + k] = have ? vi[k] : ~0u;
+            for (int k = 0; k < 3; ++k)
+                if (first[k])
 #pragma unroll
-        for (int j = 0; j < 3; ++j) s_pos[wave][(3 * lane + k) * 3 + j] = gpos[k][j];
+                    for (int j = 0; j < 3; ++j) val[slot[k] * S + n + j] = gpos[k][j];
+        }
     }
-    wave_sync();
-    // item it = (row, component) in row-major order, row = 3 lane + k of the staging lane
-    const uint32_t n_att = 192u * a.C;
-    for (uint32_t it = lane; it < n_att; it += 64u) {
-        const uint32_t row = it / a.C;
-        const uint32_t v = s_vid[wave][row];
-        if (v != ~0u) unsafeAtomicAdd(a.grad_attr + (size_t)v * a.C + (it - row * a.C), s_att[wave][it]);
+
+    __device__ __forceinline__ void add(const float* grad, uint32_t C, float* val) const
+    {
+        const uint32_t n = CC ? (uint32_t)CC : C, S = n + 3;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (!first[k]) {
+                float* row = val + slot[k] * S;
+                if constexpr (kKeep) {
+#pragma unroll
+                    for (uint32_t c = 0; c < n; ++c) unsafeAtomicAdd(row + c, gatt[k][c]);
+                } else {
+                    for (uint32_t c = 0; c < n; ++c) unsafeAtomicAdd(row + c, (float)((double)gl(grad)[c] * b[k]));
+                }
+                if (POS && pos)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) unsafeAtomicAdd(row + n + j, gpos[k][j]);
+            }
     }
-    if (a.grad_pos)
-        for (uint32_t it = lane; it < 576u; it += 64u) {
-            const uint32_t row = it / 3u;
-            const uint32_t v = s_vid[wave][row];
-            if (v != ~0u) unsafeAtomicAdd(a.grad_pos + 3 * (size_t)v + (it - 3u * row), s_pos[wave][it]);
+};
+
+extern __shared__ __align__(16) unsigned char s_bwd[];   // keys, then kBwdSlots rows of C + 3 floats
+
+template <int CC, bool POS>
+__global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
+{
+    uint32_t* keys = reinterpret_cast<uint32_t*>(s_bwd);
+    float* val = reinterpret_cast<float*>(keys + kBwdSlots);
+    const uint32_t C = CC ? (uint32_t)CC : a.C, S = C + 3;
+    uint32_t x, y, vi[3];
+    const bool in = tile_pixel((uint32_t)a.W, (uint32_t)a.H, x, y);
+    const uint32_t p = in ? y * (uint32_t)a.W + x : 0;
+    const bool have = in && screen_tri(a, p, vi);
+    if (!__syncthreads_or(have)) return;
+    for (uint32_t i = threadIdx.x; i < kBwdSlots; i += 256) keys[i] = ~0u;
+    __syncthreads();
+    BwdPixel<CC, POS> px;
+    const float* grad = a.grad_out + (size_t)p * C;
+    if (have) {
+        float sx[3], sy[3], w[3];
+        screen_windows(a, vi, sx, sy, w);
+        const float* rows[3] = {a.attrs + (size_t)vi[0] * C, a.attrs + (size_t)vi[1] * C, a.attrs + (size_t)vi[2] * C};
+        BwdChannels<CC, POS> ch;
+        ch.load(rows, grad, 0, C);
+        px.pos = true;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) px.slot[k] = bwd_slot(keys, vi[k], vi[k], px.first[k]);
+        BwdTerms t;
+        bwd_terms(sx, sy, w, x, y, t);
+        px.store(t, rows, grad, C, ch, val);
+    }
+    __syncthreads();
+    if (have) px.add(grad, C, val);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kBwdSlots * C; i += 256) {
+        const uint32_t s = i / C, c = i - s * C, v = keys[s];
+        if (v != ~0u) unsafeAtomicAdd(a.grad_attr + (size_t)v * C + c, val[s * S + c]);
+    }
+    if (POS)
+        for (uint32_t i = threadIdx.x; i < kBwdSlots * 3; i += 256) {
+            const uint32_t s = i / 3, c = i - s * 3, v = keys[s];
+            if (v != ~0u) unsafeAtomicAdd(a.grad_pos + 3 * (size_t)v + c, val[s * S + C + c]);
         }
 }
 
@@ -701,44 +776,60 @@ __global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
 // pixel finds the (mesh, instance) and triangle as the forward does, projects its three vertices
 // with the same fp32 operations, and applies the chain rule above; attribute gradients of every
 // instance of a mesh add into the mesh's rows, position gradients (to the unsnapped window
-// positions of one-instance meshes) where the mesh has a gradient buffer.  One atomic per value.
+// positions of one-instance meshes) where the mesh has a gradient buffer.  Table keys are
+// (mesh, vertex).
+template <int CC, bool POS>
 __global__ void __launch_bounds__(256) resolve_backward_meshes_kernel(ResolveBlock<kResolveWordsOne> blk)
 {
-    __shared__ ResolveLds<kDescDevice> lds;
-    const ResolveDesc d = stage_desc<kDescDevice>(blk, lds);
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(s_bwd);
+    float* val = reinterpret_cast<float*>(keys + kBwdSlots);
     const ResolveArgs& a = blk.a;
-    const uint32_t p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= (uint32_t)a.W * (uint32_t)a.H) return;
-    uint32_t pair, vi[3];
-    if (!pixel_triangle<kDescDevice>(a, d, p, pair, vi)) return;
-    const DrawDesc& D = d.pairs[pair];
-    const uint32_t m = D.mesh;
-    float sx[3], sy[3], w[3];
-    pixel_windows(a, D, d.meshes[m], vi, sx, sy, w);
-    const uint32_t x = p % (uint32_t)a.W, y = p / (uint32_t)a.W;
-    BwdTerms t;
-    bwd_terms(sx, sy, w, x, y, t);
-    const float* at = d.attrs[m];
-    float* ga = a.grad_attrs[m];
-    float* gp = a.grad_pos ? a.grad_pos[m] : nullptr;
-    const float* g = a.grad_out + (size_t)p * a.C;
-    double G[3] = {0.0, 0.0, 0.0};
-    for (uint32_t c = 0; c < a.C; ++c) {
-        const double gc = (double)g[c];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            G[k] += gc * (double)at[(size_t)vi[k] * a.C + c];
-            if (ga) unsafeAtomicAdd(ga + (size_t)vi[k] * a.C + c, (float)(gc * t.b[k]));
-        }
-    }
-    if (gp) {
-        float gpos[3][3];
-        bwd_pos(t, G, gpos);
+    const ResolveDesc d = {a.bases, a.mesh_pair, a.pairs, a.meshes, a.attrs, nullptr};
+    const uint32_t C = CC ? (uint32_t)CC : a.C, S = C + 3;
+    uint32_t x, y, pair = 0, vi[3];
+    const bool in = tile_pixel((uint32_t)a.W, (uint32_t)a.H, x, y);
+    const uint32_t p = in ? y * (uint32_t)a.W + x : 0;
+    const bool have = in && pixel_triangle<kDescDevice>(a, d, p, pair, vi);
+    if (!__syncthreads_or(have)) return;
+    for (uint32_t i = threadIdx.x; i < kBwdSlots; i += 256) keys[i] = ~0ull;
+    __syncthreads();
+    BwdPixel<CC, POS> px;
+    const float* grad = a.grad_out + (size_t)p * C;
+    if (have) {
+        const DrawDesc& D = d.pairs[pair];
+        const uint32_t m = D.mesh;
+        float sx[3], sy[3], w[3];
+        pixel_windows(a, D, d.meshes[m], vi, sx, sy, w);
+        const float* at = d.attrs[m];
+        const float* rows[3] = {at + (size_t)vi[0] * C, at + (size_t)vi[1] * C, at + (size_t)vi[2] * C};
+        BwdChannels<CC, POS> ch;
+        ch.load(rows, grad, 0, C);
+        px.pos = POS && a.grad_pos[m] != nullptr;
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) unsafeAtomicAdd(gp + 3 * (size_t)vi[k] + j, gpos[k][j]);
+            px.slot[k] = bwd_slot(keys, (unsigned long long)m << 32 | vi[k], vi[k] + m * 0x9E3779B9u, px.first[k]);
+        BwdTerms t;
+        bwd_terms(sx, sy, w, x, y, t);
+        px.store(t, rows, grad, C, ch, val);
     }
+    __syncthreads();
+    if (have) px.add(grad, C, val);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kBwdSlots * C; i += 256) {
+        const uint32_t s = i / C, c = i - s * C;
+        const unsigned long long key = keys[s];
+        if (key == ~0ull) continue;
+        float* ga = a.grad_attrs[key >> 32];
+        if (ga) unsafeAtomicAdd(ga + (size_t)(uint32_t)key * C + c, val[s * S + c]);
+    }
+    if (POS)
+        for (uint32_t i = threadIdx.x; i < kBwdSlots * 3; i += 256) {
+            const uint32_t s = i / 3, c = i - s * 3;
+            const unsigned long long key = keys[s];
+            if (key == ~0ull) continue;
+            float* gp = a.grad_pos[key >> 32];
+            if (gp) unsafeAtomicAdd(gp + 3 * (size_t)(uint32_t)key + c, val[s * S + C + c]);
+        }
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -816,15 +907,29 @@ hipError_t launch_resolve_screen(const ScreenArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// LDS of a backward workgroup: at most 4 or 8 bytes of key and 19 floats for each of 1024 rows, 84 KB.
+static size_t bwd_lds(uint32_t C, size_t key) { return kBwdSlots * (key + sizeof(float) * (C + 3)); }
+
 hipError_t launch_resolve_backward(const ScreenArgs& a, hipStream_t s)
 {
-    resolve_backward_kernel<<<tiles_for(a.W, a.H), 256, 0, s>>>(a);
+    with_channels(a.C, [&](auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        const size_t lds = bwd_lds(a.C, sizeof(uint32_t));
+        if (a.grad_pos) resolve_backward_kernel<CC, true><<<tiles_for(a.W, a.H), 256, lds, s>>>(a);
+        else resolve_backward_kernel<CC, false><<<tiles_for(a.W, a.H), 256, lds, s>>>(a);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_resolve_backward_meshes(const ResolveBlock<kResolveWordsOne>& b, hipStream_t s)
 {
-    resolve_backward_meshes_kernel<<<blocks_for((uint64_t)b.a.W * (uint64_t)b.a.H), 256, 0, s>>>(b);
+    with_channels(b.a.C, [&](auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        const size_t lds = bwd_lds(b.a.C, sizeof(unsigned long long));
+        const uint32_t tiles = tiles_for(b.a.W, b.a.H);
+        if (b.a.grad_pos) resolve_backward_meshes_kernel<CC, true><<<tiles, 256, lds, s>>>(b);
+        else resolve_backward_meshes_kernel<CC, false><<<tiles, 256, lds, s>>>(b);
+    });
     return hipGetLastError();
 }
 
