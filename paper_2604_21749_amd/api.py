@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
@@ -148,14 +149,16 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _check_cuda(t: torch.Tensor, dtype, name: str, shape_last=None):
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous() and (
+            shape_last is None or (t.dim() == 2 and t.size(1) == shape_last)):
+        return
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
         raise ValueError(f"{name} must have dtype {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape_last is not None and (t.dim() != 2 or t.shape[1] != shape_last):
-        raise ValueError(f"{name} must have shape [N, {shape_last}]")
+    raise ValueError(f"{name} must have shape [N, {shape_last}]")
 
 
 @dataclass
@@ -239,60 +242,104 @@ class CompressedGeometry:
         return c
 
 
+# Descriptors are packed with struct in one call each: setting ctypes fields one by one took most of
+# a small frame's host time (about 10 us per mesh and call).  The formats are the native layouts of
+# curast_mesh and curast_view.
+_MESH = struct.Struct("@PIPQPI4fP")
+_VIEW = struct.Struct("@16ffiiP")
+assert _MESH.size == C.sizeof(MeshStruct) and _VIEW.size == C.sizeof(ViewStruct)
+_NO_SPHERE = (0.0, 0.0, 0.0, 0.0)
+
+
+def _pack_mesh(m: GpuMesh, keep: list, check: bool, buf, at: int):
+    c = m.compressed
+    if c is not None:
+        if check:
+            _check_cuda(c.packed, torch.int32, "packed indices")
+            _check_cuda(c.qpos, torch.int16, "quantized positions")
+            if c.qpos.numel() != 3 * c.num_vertices + 1:
+                raise ValueError("quantized positions must hold 3 V + 1 elements")
+        cs = c.struct()
+        keep.append(cs)
+        cmp, pos, idx, V, T = C.addressof(cs), 0, 0, c.num_vertices, c.num_triangles
+    else:
+        p, i = m.pos, m.idx
+        ps, js = getattr(p, "shape", ()), getattr(i, "shape", ())
+        # the conditions of _check_cuda in one go; it names the one that does not hold
+        if check and not (len(ps) == 2 and ps[1] == 3 and len(js) == 2 and js[1] == 3 and isinstance(p, torch.Tensor)
+                          and isinstance(i, torch.Tensor) and p.is_cuda and i.is_cuda and p.dtype == torch.float32
+                          and i.dtype == torch.int32 and p.is_contiguous() and i.is_contiguous()):
+            _check_cuda(p, torch.float32, "vertices", 3)
+            _check_cuda(i, torch.int32, "indices", 3)
+        V, T = ps[0], js[0]
+        cmp, pos, idx = 0, p.data_ptr() if V else 0, i.data_ptr() if T else 0
+    inst, n = 0, 1
+    if m.inst is not None:
+        a = m.inst
+        if not (type(a) is np.ndarray and a.dtype == np.float32 and a.ndim == 2 and a.shape[1] == 12
+                and a.flags.c_contiguous):
+            a = np.ascontiguousarray(a, np.float32).reshape(-1, 12)
+        keep.append(a)
+        inst, n = a.__array_interface__["data"][0], a.shape[0]
+    bs = _NO_SPHERE if m.bsphere is None else np.asarray(m.bsphere, np.float32).tolist()
+    _MESH.pack_into(buf, at, pos, V, idx, T, inst, n, bs[0], bs[1], bs[2], bs[3], cmp)
+
+
+def _mesh_array(meshes: Sequence[GpuMesh], keep: list, check: bool = True):
+    """curast_mesh[len(meshes)] (at least one entry); `keep` holds what it points to."""
+    arr = (MeshStruct * max(1, len(meshes)))()
+    for k, m in enumerate(meshes):
+        _pack_mesh(m, keep, check, arr, k * _MESH.size)
+    return arr
+
+
 def _mesh_struct(m: GpuMesh, keep: list, check: bool = True) -> MeshStruct:
     s = MeshStruct()
-    if m.compressed is not None:
-        if check:
-            _check_cuda(m.compressed.packed, torch.int32, "packed indices")
-            _check_cuda(m.compressed.qpos, torch.int16, "quantized positions")
-            if m.compressed.qpos.numel() != 3 * m.compressed.num_vertices + 1:
-                raise ValueError("quantized positions must hold 3 V + 1 elements")
-        cs = m.compressed.struct()
-        keep.append(cs)
-        s.compressed = C.addressof(cs)
-        s.vertices = None
-        s.indices = None
-        s.num_vertices = m.compressed.num_vertices
-        s.num_triangles = m.compressed.num_triangles
-    else:
-        if check:
-            _check_cuda(m.pos, torch.float32, "vertices", 3)
-            _check_cuda(m.idx, torch.int32, "indices", 3)
-        s.compressed = None
-        s.vertices = m.pos.data_ptr() if m.pos.numel() else None
-        s.num_vertices = m.pos.shape[0]
-        s.indices = m.idx.data_ptr() if m.idx.numel() else None
-        s.num_triangles = m.idx.shape[0]
-    if m.inst is not None:
-        inst = np.ascontiguousarray(m.inst, np.float32).reshape(-1, 12)
-        keep.append(inst)
-        s.instances = inst.ctypes.data
-        s.num_instances = inst.shape[0]
-    else:
-        s.instances = None
-        s.num_instances = 1
-    bs = np.zeros(4, np.float32) if m.bsphere is None else np.asarray(m.bsphere, np.float32)
-    for k in range(4):
-        s.bsphere[k] = float(bs[k])
+    _pack_mesh(m, keep, check, s, 0)
     return s
+
+
+def _row_pointers(tensors, meshes, width: int, name: str, optional: bool = False):
+    """void*[max(1, len(meshes))] of per-mesh tensors (optional: None entries are NULL), each checked to
+    be a float32 CUDA tensor of shape [V_m, width]."""
+    ptrs = []
+    for t, m in zip(tensors, meshes):
+        if t is None and optional:
+            ptrs.append(None)
+            continue
+        sh = getattr(t, "shape", ())
+        if not (len(sh) == 2 and sh[1] == width and isinstance(t, torch.Tensor) and t.is_cuda
+                and t.dtype == torch.float32 and t.is_contiguous()):
+            _check_cuda(t, torch.float32, name, width)
+        if sh[0] != (m.pos.shape[0] if m.compressed is None else m.compressed.num_vertices):
+            raise ValueError(f"{name}[m] must have one row per vertex of mesh m")
+        ptrs.append(t.data_ptr())
+    return (C.c_void_p * max(1, len(meshes)))(*ptrs)
+
+
+def _pack_view(vp, near, width, height, vis: Optional[torch.Tensor], buf, at: int):
+    w, h = int(width), int(height)
+    ptr = 0
+    if vis is not None:
+        _check_cuda(vis, torch.int64, "visbuffer")
+        if vis.dim() != 2 or vis.size(0) != h or vis.size(1) != w:
+            raise ValueError("visbuffer must have shape [height, width]")
+        ptr = vis.data_ptr()
+    _VIEW.pack_into(buf, at, *np.ascontiguousarray(vp, np.float32).reshape(16).tolist(), C.c_float(near).value,
+                    C.c_int32(w).value, C.c_int32(h).value, ptr)
 
 
 def _view_struct(vp, near, width, height, vis: Optional[torch.Tensor]) -> ViewStruct:
     v = ViewStruct()
-    vp = np.ascontiguousarray(vp, np.float32).reshape(16)
-    for k in range(16):
-        v.view_proj[k] = float(vp[k])
-    v.near_plane = float(near)
-    v.width = int(width)
-    v.height = int(height)
-    if vis is not None:
-        _check_cuda(vis, torch.int64, "visbuffer")
-        if tuple(vis.shape) != (int(height), int(width)):
-            raise ValueError("visbuffer must have shape [height, width]")
-        v.visbuffer = vis.data_ptr()
-    else:
-        v.visbuffer = None
+    _pack_view(vp, near, width, height, vis, v, 0)
     return v
+
+
+def _view_array(views, outs):
+    arr = (ViewStruct * len(views))()
+    for k, (v, o) in enumerate(zip(views, outs)):
+        _pack_view(v.vp, v.near, v.width, v.height, o, arr, k * _VIEW.size)
+    return arr
 
 
 class Context:
@@ -385,7 +432,7 @@ class Context:
     def rasterize_meshes(self, meshes: Sequence[GpuMesh], view, out: Optional[torch.Tensor] = None):
         """curast_rasterize_meshes: a mesh list into one view (view: workloads.View-like)."""
         keep = []
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
+        arr = _mesh_array(meshes, keep)
         dev = meshes[0].device if meshes else torch.device("cuda")
         if out is None:
             out = torch.empty((view.height, view.width), dtype=torch.int64, device=dev)
@@ -396,11 +443,11 @@ class Context:
     def rasterize_batched(self, meshes: Sequence[GpuMesh], views, outs: Optional[List[torch.Tensor]] = None):
         """curast_rasterize_batched: the same meshes into many views in one graph launch."""
         keep = []
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
+        arr = _mesh_array(meshes, keep)
         dev = meshes[0].device if meshes else torch.device("cuda")
         if outs is None:
             outs = [torch.empty((v.height, v.width), dtype=torch.int64, device=dev) for v in views]
-        vs = (ViewStruct * len(views))(*[_view_struct(v.vp, v.near, v.width, v.height, o) for v, o in zip(views, outs)])
+        vs = _view_array(views, outs)
         self._check(lib().curast_rasterize_batched(self._h, arr, len(meshes), vs, len(views), _stream(dev)))
         return outs
 
@@ -442,11 +489,17 @@ class Context:
         output size and the result is [H / s, W / s, C], the mean of each pixel's s x s samples."""
         keep = []
         ss = int(samples_per_axis)
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
+        arr = _mesh_array(meshes, keep)
         Cn = int(attrs[0].shape[1])
-        for a in attrs:
-            _check_cuda(a, torch.float32, "attrs", Cn)
-        ptrs = (C.c_void_p * max(1, len(attrs)))(*[a.data_ptr() for a in attrs])
+        if len(attrs) == len(meshes):
+            ptrs = _row_pointers(attrs, meshes, Cn, "attrs")
+        else:
+            for a in attrs:
+                _check_cuda(a, torch.float32, "attrs", Cn)
+            for m, a in zip(meshes, attrs):
+                if a.shape[0] != m.num_vertices:
+                    raise ValueError("attrs[m] must have one row per vertex of mesh m")
+            ptrs = (C.c_void_p * max(1, len(attrs)))(*[a.data_ptr() for a in attrs])
         if ss < 1 or view.width % ss or view.height % ss:
             raise ValueError("view size must be a multiple of samples_per_axis")
         shape = (view.height // ss, view.width // ss, Cn)
@@ -455,9 +508,6 @@ class Context:
         _check_cuda(out, torch.float32, "out")
         if tuple(out.shape) != shape:
             raise ValueError(f"out must have shape {list(shape)}")
-        for m, a in zip(meshes, attrs):
-            if a.shape[0] != m.num_vertices:
-                raise ValueError("attrs[m] must have one row per vertex of mesh m")
         vs = _view_struct(view.vp, view.near, view.width, view.height, vis)
         if ss == 1:
             rc = lib().curast_resolve(self._h, arr, len(meshes), C.byref(vs), ptrs, Cn, out.data_ptr(),
@@ -500,18 +550,14 @@ class Context:
         if not (len(meshes) == len(uvs) == len(textures)):
             raise ValueError("one UV array and one texture per mesh")
         keep = []
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
-        for m, uv in zip(meshes, uvs):
-            _check_cuda(uv, torch.float32, "uvs", 2)
-            if uv.shape[0] != m.num_vertices:
-                raise ValueError("uvs[m] must have one row per vertex of mesh m")
+        arr = _mesh_array(meshes, keep)
+        ptrs = _row_pointers(uvs, meshes, 2, "uvs")
         for t in textures:
             _check_cuda(t.texels, torch.int32, "texels")
             if not texture_texels(t.width, t.height, t.levels):
                 raise ValueError("texture sizes must be powers of two in [1, 16384] with 1 .. 1 + log2(max) levels")
             if t.texels.numel() < texture_texels(t.width, t.height, t.levels):
                 raise ValueError("texture texels smaller than its mip chain")
-        ptrs = (C.c_void_p * max(1, len(uvs)))(*[u.data_ptr() for u in uvs])
         tex = (TextureStruct * max(1, len(textures)))(*[t.struct() for t in textures])
         shape = (view.height, view.width, 4)
         if out is None:
@@ -577,12 +623,9 @@ class Context:
         accumulates into grad_attrs[m] [V_m, C] and, for one-instance meshes, grad_pos[m] [V_m, 3]
         (gradients to the window positions project() gives)."""
         keep = []
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
+        arr = _mesh_array(meshes, keep)
         Cn = int(attrs[0].shape[1])
-        for m, a in zip(meshes, attrs):
-            _check_cuda(a, torch.float32, "attrs", Cn)
-            if a.shape[0] != m.num_vertices:
-                raise ValueError("attrs[m] must have one row per vertex of mesh m")
+        aptr = _row_pointers(attrs, meshes, Cn, "attrs")
         _check_cuda(vis, torch.int64, "visbuffer")
         _check_cuda(grad_out, torch.float32, "grad_out")
         if tuple(grad_out.shape) != (view.height, view.width, Cn) or tuple(vis.shape) != (view.height, view.width):
@@ -590,21 +633,8 @@ class Context:
         if len(attrs) != len(meshes) or len(grad_attrs) != len(meshes) or (
                 grad_pos is not None and len(grad_pos) != len(meshes)):
             raise ValueError("one attrs, grad_attrs (and grad_pos) entry per mesh")
-        for m, g in zip(meshes, grad_attrs):
-            if g is not None:
-                _check_cuda(g, torch.float32, "grad_attrs", Cn)
-                if g.shape[0] != m.num_vertices:
-                    raise ValueError("grad_attrs[m] must have one row per vertex of mesh m")
-        if grad_pos is not None:
-            for m, g in zip(meshes, grad_pos):
-                if g is not None:
-                    _check_cuda(g, torch.float32, "grad_pos", 3)
-                    if g.shape[0] != m.num_vertices:
-                        raise ValueError("grad_pos[m] must have one row per vertex of mesh m")
-        n = max(1, len(meshes))
-        aptr = (C.c_void_p * n)(*[a.data_ptr() for a in attrs])
-        gaptr = (C.c_void_p * n)(*[_ptr(g) for g in grad_attrs])
-        gpptr = None if grad_pos is None else (C.c_void_p * n)(*[_ptr(g) for g in grad_pos])
+        gaptr = _row_pointers(grad_attrs, meshes, Cn, "grad_attrs", optional=True)
+        gpptr = None if grad_pos is None else _row_pointers(grad_pos, meshes, 3, "grad_pos", optional=True)
         vs = _view_struct(view.vp, view.near, view.width, view.height, vis)
         self._check(lib().curast_resolve_backward_meshes(
             self._h, arr, len(meshes), C.byref(vs), aptr, Cn, grad_out.data_ptr(), gaptr, gpptr,
@@ -614,8 +644,8 @@ class Context:
     def autotune(self, meshes: Sequence[GpuMesh], views, outs: Sequence[torch.Tensor],
                  cache_path: Optional[str] = None) -> dict:
         keep = []
-        arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep) for m in meshes])
-        vs = (ViewStruct * len(views))(*[_view_struct(v.vp, v.near, v.width, v.height, o) for v, o in zip(views, outs)])
+        arr = _mesh_array(meshes, keep)
+        vs = _view_array(views, outs)
         chosen = Options()
         dev = outs[0].device
         self._check(lib().curast_autotune(self._h, arr, len(meshes), vs, len(views),
@@ -649,7 +679,7 @@ class Context:
 def id_bases(meshes: Sequence[GpuMesh]) -> np.ndarray:
     """curast_id_bases (host only): exclusive prefix of triangle counts over (mesh, instance)."""
     keep = []
-    arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep, check=False) for m in meshes])
+    arr = _mesh_array(meshes, keep, check=False)
     n = lib().curast_id_bases(arr, len(meshes), None)
     if n < 0:
         raise CurastError(int(n), lib().curast_status_string(int(n)).decode())
@@ -662,7 +692,7 @@ def plan(meshes: Sequence[GpuMesh], views, **options):
     """curast_plan (host only): (visible [pairs, n_views] uint8: 0 culled, 1 drawn, 2 drawn and
     interior; bases [pairs + 1]; counts dict)."""
     keep = []
-    arr = (MeshStruct * max(1, len(meshes)))(*[_mesh_struct(m, keep, check=False) for m in meshes])
+    arr = _mesh_array(meshes, keep, check=False)
     dummy = (C.c_uint64 * max(1, len(views)))()     # distinct non-NULL buffers, never touched
     vs = (ViewStruct * len(views))()
     for i, v in enumerate(views):

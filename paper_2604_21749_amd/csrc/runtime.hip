@@ -64,14 +64,26 @@ struct TimedFrame {
     int used[kNumSlots];
 };
 
-// Pinned staging buffer + device buffer + event guarding reuse of the host side.
-struct Staging {
-    void* host = nullptr;
-    void* dev = nullptr;
+// Device buffer of descriptor blocks, and the pinned buffers they are uploaded from.  Frames take the
+// pinned buffers in turn, so that the host builds the next blocks while the stream still has to copy
+// the last ones (with one buffer it waited for the whole stream at every upload); a captured graph
+// always copies from buffer 0.  An event guards the reuse of each.
+struct HostBuffer {
+    void* p = nullptr;
     size_t cap = 0;
     hipEvent_t ev = nullptr;
     bool pending = false;
 };
+constexpr int kHostBuffers = 3;
+
+struct Staging {
+    HostBuffer ring[kHostBuffers];
+    HostBuffer* host = &ring[0];   // the one of the current call
+    void* dev = nullptr;
+    size_t cap = 0;
+};
+
+enum class HostSide { kNone, kNext, kFixed };
 
 struct GraphEntry {
     uint64_t key[11];
@@ -218,25 +230,51 @@ int ensure_tiles(curast_ctx* ctx, uint32_t n_tiles)
     return CURAST_OK;
 }
 
-// Room for `bytes` in both buffers; with host_side also waits until the host one may be rewritten.
-int ensure_staging(curast_ctx* ctx, Staging& st, size_t bytes, bool host_side = true)
+// Room for `bytes` in the device buffer and, as asked for, in a pinned buffer that may be rewritten
+// (st.host).
+int ensure_staging(curast_ctx* ctx, Staging& st, size_t bytes, HostSide side)
 {
-    if (st.pending && (host_side || bytes > st.cap)) {
-        HIP_TRY(ctx, hipEventSynchronize(st.ev));
-        st.pending = false;
+    if (bytes > st.cap) {
+        const size_t cap = std::max<size_t>(bytes, std::max<size_t>(st.cap * 2, 64 * 1024));
+        if (st.dev) hipFree(st.dev);
+        st.dev = nullptr;
+        st.cap = 0;
+        if (hipMalloc(&st.dev, cap) != hipSuccess) return fail(ctx, CURAST_E_OOM, "descriptor allocation failed");
+        st.cap = cap;
+        drop_graphs(ctx);   // captured graphs refer to the old buffer
     }
-    if (bytes <= st.cap) return CURAST_OK;
-    size_t cap = std::max<size_t>(bytes, std::max<size_t>(st.cap * 2, 64 * 1024));
-    if (st.host) hipHostFree(st.host);
-    if (st.dev) hipFree(st.dev);
-    st.host = nullptr;
-    st.dev = nullptr;
-    st.cap = 0;
-    if (hipHostMalloc(&st.host, cap, hipHostMallocDefault) != hipSuccess) return fail(ctx, CURAST_E_OOM, "pinned staging allocation failed");
-    if (hipMalloc(&st.dev, cap) != hipSuccess) return fail(ctx, CURAST_E_OOM, "descriptor allocation failed");
-    st.cap = cap;
-    drop_graphs(ctx);   // descriptor buffers moved: captured graphs refer to the old ones
+    if (side == HostSide::kNone) return CURAST_OK;
+    st.host = side == HostSide::kFixed ? &st.ring[0] : &st.ring[(st.host - st.ring + 1) % kHostBuffers];
+    HostBuffer& h = *st.host;
+    if (!h.ev) HIP_TRY(ctx, hipEventCreateWithFlags(&h.ev, hipEventDisableTiming));
+    if (h.pending) {
+        HIP_TRY(ctx, hipEventSynchronize(h.ev));
+        h.pending = false;
+    }
+    if (bytes <= h.cap) return CURAST_OK;
+    const size_t cap = std::max<size_t>(bytes, std::max<size_t>(h.cap * 2, 64 * 1024));
+    if (h.p) hipHostFree(h.p);
+    h.p = nullptr;
+    h.cap = 0;
+    if (hipHostMalloc(&h.p, cap, hipHostMallocDefault) != hipSuccess) return fail(ctx, CURAST_E_OOM, "pinned staging allocation failed");
+    h.cap = cap;
+    if (&h == &st.ring[0]) drop_graphs(ctx);
     return CURAST_OK;
+}
+
+// Marks the current pinned buffer as in use until the stream reaches this point.
+int staging_used(curast_ctx* ctx, Staging& st, hipStream_t s)
+{
+    HIP_TRY(ctx, hipEventRecord(st.host->ev, s));
+    st.host->pending = true;
+    return CURAST_OK;
+}
+
+// Copies the current pinned buffer to the device.
+int upload_staging(curast_ctx* ctx, Staging& st, size_t bytes, hipStream_t s)
+{
+    HIP_TRY(ctx, hipMemcpyAsync(st.dev, st.host->p, bytes, hipMemcpyHostToDevice, s));
+    return staging_used(ctx, st, s);
 }
 
 int ensure_queues(curast_ctx* ctx)
@@ -860,18 +898,18 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     // a small descriptor block travels as a kernel argument; larger ones through pinned memory
     const bool inline_block = !use_graph && bytes <= sizeof(uint32_t) * kBlockWords;
     alignas(16) char block[sizeof(uint32_t) * kBlockWords];
-    rc = ensure_staging(ctx, ctx->raster_stage, bytes, !inline_block);
+    rc = ensure_staging(ctx, ctx->raster_stage, bytes,
+                        inline_block ? HostSide::kNone : use_graph ? HostSide::kFixed : HostSide::kNext);
     if (rc) return rc;
-    write_plan(P, inline_block ? block : ctx->raster_stage.host);
+    write_plan(P, inline_block ? block : ctx->raster_stage.host->p);
     ctx->draws_culled += P.draws_culled;
     log_plan(use_graph ? "batched frame" : "frame", P, M, n_views);
     TimedFrame* tf = begin_timing(ctx);
     if (!use_graph) {
         const RasterArgs a = make_args(ctx, P);
         if (!inline_block) {
-            HIP_TRY(ctx, hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host, P.bytes, hipMemcpyHostToDevice, s));
-            HIP_TRY(ctx, hipEventRecord(ctx->raster_stage.ev, s));
-            ctx->raster_stage.pending = true;
+            rc = upload_staging(ctx, ctx->raster_stage, P.bytes, s);
+            if (rc) return rc;
         }
         const uint64_t shared = P.hdr.shared_batches;
         auto clear = [&] {
@@ -902,7 +940,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
         GraphEntry g;
         std::memcpy(g.key, key, sizeof key);
         HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
-        hipError_t e = hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host, P.max_bytes, hipMemcpyHostToDevice,
+        hipError_t e = hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host->p, P.max_bytes, hipMemcpyHostToDevice,
                                       ctx->capture_stream);
         const RasterArgs a = make_args(ctx, P);
         auto clear = [&] { return launch_clear(a, clear_grid(ctx, P.total_pixels), ctx->capture_stream); };
@@ -927,8 +965,8 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     }
     if (tf) HIP_TRY(ctx, hipEventRecord(tf->ev[0], s));
     HIP_TRY(ctx, hipGraphLaunch(ge->exec, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->raster_stage.ev, s));
-    ctx->raster_stage.pending = true;
+    rc = staging_used(ctx, ctx->raster_stage, s);
+    if (rc) return rc;
     if (tf) {
         HIP_TRY(ctx, hipEventRecord(tf->ev[kNumSlots], s));
         tf->used[kTFrame] = 1;
@@ -1103,7 +1141,7 @@ int build_resolve_desc(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, c
     // small blocks travel in the kernel argument (the forward resolves)
     const bool inl = !grad_attrs && bytes <= sizeof(blk.w);
     if (!inl) {
-        const int rc = ensure_staging(ctx, ctx->resolve_stage, bytes);
+        const int rc = ensure_staging(ctx, ctx->resolve_stage, bytes, HostSide::kNext);
         if (rc) return rc;
     }
     blk.words = inl ? (uint32_t)((bytes + 3) / 4) : 0;
@@ -1112,7 +1150,7 @@ int build_resolve_desc(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, c
     blk.off_meshes = (uint32_t)off_meshes;
     blk.off_attrs = (uint32_t)off_attrs;
     blk.off_tex = (uint32_t)off_tex;
-    char* h = inl ? reinterpret_cast<char*>(blk.w) : static_cast<char*>(ctx->resolve_stage.host);
+    char* h = inl ? reinterpret_cast<char*>(blk.w) : static_cast<char*>(ctx->resolve_stage.host->p);
     uint64_t* bases = reinterpret_cast<uint64_t*>(h + off_bases);
     uint32_t* mpair = reinterpret_cast<uint32_t*>(h + off_mpair);
     DrawDesc* pairs = reinterpret_cast<DrawDesc*>(h + off_pairs);
@@ -1235,8 +1273,6 @@ int curast_create(const curast_options* opt, curast_ctx** out)
     if (hipStreamCreateWithFlags(&ctx->side_stream, hipStreamNonBlocking) != hipSuccess) return cleanup(CURAST_E_HIP);
     if (hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) != hipSuccess) return cleanup(CURAST_E_HIP);
     if (hipEventCreateWithFlags(&ctx->join_ev, hipEventDisableTiming) != hipSuccess) return cleanup(CURAST_E_HIP);
-    if (hipEventCreateWithFlags(&ctx->raster_stage.ev, hipEventDisableTiming) != hipSuccess) return cleanup(CURAST_E_HIP);
-    if (hipEventCreateWithFlags(&ctx->resolve_stage.ev, hipEventDisableTiming) != hipSuccess) return cleanup(CURAST_E_HIP);
     if (ensure_queues(ctx)) return cleanup(CURAST_E_OOM);
     // device address of the allocation-free form's scratch array (looked up once per device)
     const hipError_t se = scratch_address(ctx->device, &ctx->na_scratch);
@@ -1261,9 +1297,11 @@ int curast_destroy(curast_ctx* ctx)
     collect_timings(ctx);
     drop_graphs(ctx);
     for (Staging* st : {&ctx->raster_stage, &ctx->resolve_stage}) {
-        if (st->host) hipHostFree(st->host);
+        for (HostBuffer& h : st->ring) {
+            if (h.p) hipHostFree(h.p);
+            if (h.ev) hipEventDestroy(h.ev);
+        }
         if (st->dev) hipFree(st->dev);
-        if (st->ev) hipEventDestroy(st->ev);
     }
     for (hipEvent_t ev : ctx->event_pool) hipEventDestroy(ev);
     if (ctx->q2) hipFree(ctx->q2);
@@ -1382,20 +1420,11 @@ int curast_project(curast_ctx* ctx, const curast_mesh* mesh, uint32_t instance, 
 }
 
 namespace {
-// Uploads a descriptor block that does not travel in the kernel argument.
-int upload_resolve_desc(curast_ctx* ctx, size_t bytes, hipStream_t s)
-{
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->resolve_stage.dev, ctx->resolve_stage.host, bytes, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, hipEventRecord(ctx->resolve_stage.ev, s));
-    ctx->resolve_stage.pending = true;
-    return CURAST_OK;
-}
-
 // Launches a forward resolve of either kind.
 int enqueue_resolve(curast_ctx* ctx, const ResolveBlock<kResolveWords>& blk, size_t bytes, hipStream_t s)
 {
     if (!blk.words) {
-        const int rc = upload_resolve_desc(ctx, bytes, s);
+        const int rc = upload_staging(ctx, ctx->resolve_stage, bytes, s);
         if (rc) return rc;
     }
     TimedFrame* tf = begin_timing(ctx);
@@ -1679,7 +1708,7 @@ int curast_resolve_backward_meshes(curast_ctx* ctx, const curast_mesh* meshes, u
     blk.a.grad_out = grad_out;
     ResolveBlock<kResolveWordsOne> dev{};
     dev.a = blk.a;
-    rc = upload_resolve_desc(ctx, bytes, s);
+    rc = upload_staging(ctx, ctx->resolve_stage, bytes, s);
     if (rc) return rc;
     TimedFrame* tf = begin_timing(ctx);
     if (tf) hipEventRecord(tf->ev[7], s);
