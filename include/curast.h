@@ -92,12 +92,12 @@ typedef enum {
                                             and the rest of stage 1 as stage1_single */
 #define CURAST_FLAG_EARLY_OUT_ALL 0x800u /* read the stored key before each atomic minimum and skip the
                                             atomic when the key is not smaller, in every stage; by
-                                            default only the stage-1 launch over single-draw meshes,
-                                            stage 3 and the overflow passes read first, while the
-                                            stage-1 launch over multi-draw meshes and stage 2 issue
-                                            the atomic directly as the paper does (Sec. 4.1), which
-                                            measured faster there; CURAST_FLAG_NO_EARLY_OUT, when
-                                            also set, wins (no stage reads first) */
+                                            default only the stage-1 launch over single-draw meshes
+                                            does, and only with 32 or more triangles per pixel, while
+                                            everything else issues the atomic directly as the paper
+                                            does (Sec. 4.1), which measured faster there;
+                                            CURAST_FLAG_NO_EARLY_OUT, when also set, wins (no stage
+                                            reads first) */
 #define CURAST_FLAG_ZERO_QUEUES   0x80000000u /* testing aid: run with stage queues of capacity 0, so
                                                  every forwarded triangle takes the overflow paths */
 
@@ -113,7 +113,8 @@ typedef struct {
     uint32_t medium_px;         /* stage-2 limit (default 4096, Sec. 4) */
     uint32_t s1_block;          /* stage-1 workgroup size: 64, 128, 256 or 512 (default 64, Sec. 4.1) */
     uint32_t s1_tris_per_thread;/* triangles per thread per stage-1 work item of a mesh drawn once:
-                                   1, 2, 4 or 8 (default 4) */
+                                   1, 2, 4 or 8 (default 4; with 0 a launch of fewer
+                                   than 7M triangles takes 2, of fewer than 0.7M 1) */
     uint32_t s1_draws_per_item; /* (instance x view) draws per stage-1 work item (default 64, Sec. 4.5) */
     uint32_t s2_waves;          /* persistent stage-2 wavefronts (default 16 per CU) */
     uint32_t s3_blocks;         /* persistent stage-3 workgroups (default 2 per CU) */

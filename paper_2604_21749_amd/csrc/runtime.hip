@@ -560,6 +560,8 @@ struct PlanT {
     uint64_t pair_count = 0;
     bool compressed = false;         // some mesh is compressed
     uint32_t compressed_parts = 0;   // RasterArgs::compressed_parts of this frame's stage-1 parts
+    uint32_t tpt_single = 0;         // triangles per lane of the single-draw stage-1 launch
+    bool read_first = false;         // that launch reads the stored key before each atomic
     size_t max_draws = 0;            // without any culling
     size_t off_views = 0, off_meshes = 0, off_segs = 0, off_draws = 0, bytes = 0, max_bytes = 0;
     bool full() const;
@@ -574,8 +576,22 @@ bool PlanT<FixVec>::full() const
 }
 using Plan = PlanT<HeapVec>;
 
+// Triangles per lane of the single-draw launch when the option is left at its default: 4 keep most
+// loads in flight per wavefront, but a launch too small to fill the chip gains more from more
+// wavefronts (256 compute units hold about 5000 of them).  Measured with 1 / 2 / 4: 0.26 M triangles
+// 10.6 / 11.6 / 18.7 us, 1.0 M 23.5 / 23.4 / 28.8, 3.4 M 42 / 34 / 44, 8.4 M 87 / 67.5 / 66.8,
+// 10 M 99 / 64 / 56.
+uint32_t default_single_tpt(uint64_t tris) { return tris < 700000 ? 1u : tris < 7000000 ? 2u : 4u; }
+
+// Triangles per pixel from which the single-draw launch reads the stored key before each atomic.  The
+// read saves atomics at the memory side, which counts only where the launch streams far more
+// triangles than it writes fragments (65 per pixel: 2291 us with the read, 2363 without); elsewhere it
+// costs a round trip per fragment (16 per pixel: 192 and 161 us, 2.3: 137 and 67 us, 0.5: 81 and 29).
+constexpr uint64_t kReadFirstDensity = 32;
+
+// auto_tpt: the caller left s1_tris_per_thread at its default.
 template <template <class> class Vec>
-int build_plan(curast_ctx* ctx, const curast_options& o, const curast_mesh* meshes, uint32_t M,
+int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const curast_mesh* meshes, uint32_t M,
                const curast_view* views, uint32_t n_views, PlanT<Vec>& P, uint8_t* visible = nullptr)
 {
     if (M && !meshes) return fail(ctx, CURAST_E_INVALID, "meshes is NULL");
@@ -595,7 +611,6 @@ int build_plan(curast_ctx* ctx, const curast_options& o, const curast_mesh* mesh
         if (total_ids > kMaxIds) return fail(ctx, CURAST_E_ID_RANGE, "more than 2^36 triangle instances");
     }
     const bool cull = !(o.flags & kFlagNoMeshCull);
-    const uint32_t bt = o.s1_block * o.s1_tris_per_thread;   // triangles per stage-1 work item
     const uint32_t dpi = o.s1_draws_per_item;
     P.views.resize(n_views);
     for (uint32_t v = 0; v < n_views; ++v) {
@@ -618,6 +633,8 @@ int build_plan(curast_ctx* ctx, const curast_options& o, const curast_mesh* mesh
     // triangles per work item of the first stage-1 launch (the vertex-sharing kernel runs 64-lane
     // workgroups)
     const uint32_t bt_multi = (o.s1_mode == 3 ? 64u : o.s1_block) * o.s1_multi_tris_per_thread;
+    // smallest batch of either launch (the default single-draw batch depends on the surviving draws)
+    const uint32_t bt_min = std::min(bt_multi, o.s1_block * (auto_tpt ? 1u : o.s1_tris_per_thread));
     P.mesh_draw_begin.resize(M);
     P.mesh_draw_count.resize(M);
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "too many meshes or views for the allocation-free form");
@@ -665,13 +682,19 @@ int build_plan(curast_ctx* ctx, const curast_options& o, const curast_mesh* mesh
             const uint64_t all = (uint64_t)ni * n_views;
             const uint64_t groups = (all + dpi - 1) / dpi;
             P.max_draws += all;
-            P.max_batches += ((me.num_triangles + std::min(bt, bt_multi) - 1) / std::min(bt, bt_multi)) * groups;
+            P.max_batches += ((me.num_triangles + bt_min - 1) / bt_min) * groups;
         }
     }
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes at most 32 instances");
     // stage-1 segments: meshes drawn more than once first (their own launch, whose lanes reuse each
     // loaded triangle over many draws), then the rest; mode 3 sends every mesh to the first
     auto shared_mesh = [&](uint32_t m) { return o.s1_mode == 3 || mesh_draw_count[m] >= 2; };
+    uint64_t single_tris = 0;
+    for (uint32_t m = 0; m < M; ++m)
+        if (mesh_draw_count[m] && !shared_mesh(m)) single_tris += meshes[m].num_triangles;
+    P.tpt_single = auto_tpt ? default_single_tpt(single_tris) : o.s1_tris_per_thread;
+    P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
+    const uint32_t bt = o.s1_block * P.tpt_single;   // triangles per work item of the single-draw launch
     for (int pass = 0; pass < 2; ++pass) {
         bool any_cmp = false, all_cmp = true;
         for (uint32_t m = 0; m < M; ++m) {
@@ -799,12 +822,13 @@ hipError_t frame_begin(const curast_ctx* ctx, const RasterArgs& a, const void* b
 // Launch the device part of a frame over the buffers in `a` (descriptors, queues, counters):
 // clear, stage 1, stage 2 (with stage 1's overflow pass), stage 3.  Options other than a.flags come from ctx.
 // `clear` launches the first one.
-template <class Clear>
-int launch_frame(curast_ctx* ctx, const RasterArgs& a, Clear clear, uint32_t grid1, uint32_t grid_share,
-                 hipStream_t s, TimedFrame* tf)
+template <class PlanType, class Clear>
+int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear clear, uint32_t grid1,
+                 uint32_t grid_share, hipStream_t s, TimedFrame* tf)
 {
     const bool stats = a.flags & kFlagStats;
     const uint32_t cus = (uint32_t)ctx->cus;
+    const uint32_t atomic_alone = a.flags & kFlagEarlyOutAll ? 0u : kFlagNoEarlyOut;
     hipError_t e;
     if (tf) hipEventRecord(tf->ev[0], s);
     e = clear();
@@ -819,14 +843,13 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, Clear clear, uint32_t gri
         // launches fewer workgroups (one per item measured slower on the HBM-bound launch)
         const uint32_t mode = ctx->opt.s1_mode, blk = ctx->opt.s1_block;
         const uint32_t grid_cap = (uint32_t)std::min<uint64_t>((uint64_t)cus * ctx->opt.s1_blocks_per_cu, 1ull << 24);
+        // a fragment is written by the atomic alone, without reading the stored key first (a memory
+        // round trip per fragment), except in dense single-draw launches (kReadFirstDensity)
         auto launch_part = [&](uint32_t part, uint32_t tpt, uint32_t grid, hipStream_t st) {
             grid = std::min(grid, grid_cap);
             RasterArgs a1 = a;
             a1.part = part;
-            // the multi-draw launch writes with the atomic alone: its fragments come from small
-            // instanced triangles, and a read before each atomic cost a memory round trip per
-            // fragment there; the single-draw launch, bound by memory, gains from skipping atomics
-            if (part == 1 && !(a.flags & kFlagEarlyOutAll)) a1.flags |= kFlagNoEarlyOut;
+            if (part == 1 || !P.read_first) a1.flags |= atomic_alone;
             if (part == 1 && mode == 3) return launch_stage1_share(a1, tpt, stats, grid, st);
             if (mode == 1) return launch_stage1(a1, blk, tpt, stats, grid, st);
             const bool strips = !(a.flags & kFlagNoStrips) && tpt >= 2 &&
@@ -842,7 +865,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, Clear clear, uint32_t gri
             e = hipEventRecord(ctx->fork_ev, s);
             if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side_stream, ctx->fork_ev, 0);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 stream fork");
-            e = launch_part(2, ctx->opt.s1_tris_per_thread, std::max<uint32_t>(grid1, 1), ctx->side_stream);
+            e = launch_part(2, P.tpt_single, std::max<uint32_t>(grid1, 1), ctx->side_stream);
             if (e == hipSuccess) e = hipEventRecord(ctx->join_ev, ctx->side_stream);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch");
             e = launch_part(1, ctx->opt.s1_multi_tris_per_thread, grid_share, s);
@@ -856,22 +879,25 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, Clear clear, uint32_t gri
                 if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch (multi-draw meshes)");
             }
             if (tf) hipEventRecord(tf->ev[2], s);
-            e = launch_part(2, ctx->opt.s1_tris_per_thread, std::max<uint32_t>(grid1, 1), s);
+            e = launch_part(2, P.tpt_single, std::max<uint32_t>(grid1, 1), s);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch");
         }
     }
     if (tf) hipEventRecord(tf->ev[3], s);
     if (tf) hipEventRecord(tf->ev[4], s);   // the overflow pass is part of the stage-2 launch
     {
-        // stage 2 writes with the atomic alone as well (see the stage-1 launches)
         RasterArgs a2 = a;
-        if (!(a.flags & kFlagEarlyOutAll)) a2.flags |= kFlagNoEarlyOut;
+        a2.flags |= atomic_alone;
         e = launch_stage2(a2, std::max<uint32_t>(1, ctx->opt.s2_waves / 4), stats, s);
     }
     if (e != hipSuccess) return hip_fail(ctx, e, "stage-2 kernel launch");
     if (tf) hipEventRecord(tf->ev[5], s);
-    e = (a.flags & kFlagS3PerPart) ? launch_stage3(a, std::max<uint32_t>(1, ctx->opt.s3_blocks), stats, s)
-                                          : launch_stage3_binned(a, std::max<uint32_t>(1, ctx->opt.s3_blocks), stats, s);
+    {
+        RasterArgs a3 = a;
+        a3.flags |= atomic_alone;
+        const uint32_t grid3 = std::max<uint32_t>(1, ctx->opt.s3_blocks);
+        e = (a.flags & kFlagS3PerPart) ? launch_stage3(a3, grid3, stats, s) : launch_stage3_binned(a3, grid3, stats, s);
+    }
     if (e != hipSuccess) return hip_fail(ctx, e, "stage-3 kernel launch");
     if (tf) {
         hipEventRecord(tf->ev[6], s);
@@ -888,7 +914,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     if (!ctx) return CURAST_E_INVALID;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     Plan P;
-    int rc = build_plan(ctx, ctx->opt, meshes, M, views, n_views, P);
+    int rc = build_plan(ctx, ctx->opt, !ctx->user.s1_tris_per_thread, meshes, M, views, n_views, P);
     if (rc) return rc;
     rc = ensure_queues(ctx);
     if (rc) return rc;
@@ -918,14 +944,14 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
                        ? frame_begin<kBlockWordsSmall>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s)
                        : frame_begin<kBlockWords>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s);
         };
-        return launch_frame(ctx, a, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0, s, tf);
+        return launch_frame(ctx, a, P, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0, s, tf);
     }
     // graph path: one captured sequence per structure (sizes of the descriptor block, grid bound,
     // options); replays copy the new descriptor contents from the same pinned buffer
     const uint32_t grid1 = grid_for(P.max_batches);
     // the queue capacities are kernel arguments of the captured launches, so they are part of the key
     uint64_t key[11] = {(uint64_t)M, (uint64_t)n_views, (uint64_t)P.max_bytes, (uint64_t)grid1,
-                       ((uint64_t)ctx->opt.s1_block << 32) | (ctx->opt.s1_tris_per_thread << 8) |
+                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.read_first << 16) | (P.tpt_single << 8) |
                            (ctx->opt.s1_multi_tris_per_thread << 4) | ctx->opt.s1_mode,
                        ((uint64_t)ctx->opt.s2_waves << 32) | ctx->opt.s3_blocks,
                        ((uint64_t)ctx->opt.flags << 32) | ctx->opt.small_px,
@@ -944,7 +970,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
                                       ctx->capture_stream);
         const RasterArgs a = make_args(ctx, P);
         auto clear = [&] { return launch_clear(a, clear_grid(ctx, P.total_pixels), ctx->capture_stream); };
-        int lrc = e == hipSuccess ? launch_frame(ctx, a, clear, grid1, grid1, ctx->capture_stream, nullptr)
+        int lrc = e == hipSuccess ? launch_frame(ctx, a, P, clear, grid1, grid1, ctx->capture_stream, nullptr)
                                   : hip_fail(ctx, e, "capture memcpy");
         hipGraph_t graph = nullptr;
         hipError_t e2 = hipStreamEndCapture(ctx->capture_stream, &graph);
@@ -1048,7 +1074,7 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
     if (mesh.instances && mesh.num_instances > kFixedDraws)
         return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes at most 32 instances");
     PlanT<FixVec> P;
-    int rc = build_plan(ctx, ctx->opt, &mesh, 1, &view, 1, P);
+    int rc = build_plan(ctx, ctx->opt, !ctx->user.s1_tris_per_thread, &mesh, 1, &view, 1, P);
     if (rc) return rc;
     NaDesc d;
     std::memset(&d, 0, sizeof d);
@@ -1091,7 +1117,7 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
                    ? frame_begin<kBlockWordsSmall>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s)
                    : frame_begin<kBlockWords>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s);
     };
-    return launch_frame(ctx, a, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0,
+    return launch_frame(ctx, a, P, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0,
                         s, nullptr);
 }
 
@@ -1785,7 +1811,7 @@ int curast_plan(const curast_mesh* meshes, uint32_t M, const curast_view* views,
     if (validate_options(u, msg)) return CURAST_E_INVALID;
     const curast_options o = resolve_defaults(u, 256);
     Plan P;
-    int rc = build_plan(nullptr, o, meshes, M, views, n_views, P, visible);
+    int rc = build_plan(nullptr, o, !u.s1_tris_per_thread, meshes, M, views, n_views, P, visible);
     if (rc) return rc;
     log_plan("plan", P, M, n_views);
     if (bases) {
