@@ -13,10 +13,11 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-# Translation units: (source, object name, macros).  The stage-1 fast kernel's variants of one
-# workgroup size and triangles per lane are a unit each, so that they compile in parallel.
-UNITS = [("raster.hip", f"raster_{b}_{t}", [f"-DCURAST_FAST_BLOCK={b}", f"-DCURAST_FAST_TPT={t}"])
-         for t in (8, 4, 2, 1) for b in (64, 128, 256, 512)]
+# Translation units: (source, object name, macros).  The variants of the stage-1 kernels are units of
+# their own, so that they compile in parallel.
+UNITS = [("raster.hip", f"raster_strips_{t}", [f"-DCURAST_STRIPS_TPT={t}"]) for t in (8, 4, 2)]
+UNITS += [("raster.hip", f"raster_{b}_{t}", [f"-DCURAST_FAST_BLOCK={b}", f"-DCURAST_FAST_TPT={t}"])
+          for t in (8, 4, 2, 1) for b in (64, 128, 256, 512)]
 UNITS += [(f, f[:-4], []) for f in ("raster.hip", "resolve.hip", "runtime.hip", "autotune.hip", "compress.hip")]
 LIB = os.path.join(HERE, "libcurast.so")
 ARCH = os.environ.get("CURAST_OFFLOAD_ARCH", "gfx950")

@@ -74,7 +74,7 @@ struct Segment {                  // 32 B
 // Bit 31 of `view` (kDrawInterior) marks draws whose bounding sphere the host proved to lie in
 // front of the near plane and inside |x|, |y| <= 1.99 w: no vertex of such a draw needs the
 // per-vertex near/guard tests of the fast stage-1 path.
-struct DrawDesc {                 // 112 B
+struct DrawDesc {                 // 128 B: one cache line holds all that a fragment of the draw needs
     float A[12];                  // rows x, y, w of VP * X (the exact transform)
     float R[8];                   // interior draws: hW (row x + row w), hH (row y + row w)
     uint64_t id_base;
@@ -82,8 +82,12 @@ struct DrawDesc {                 // 112 B
     uint32_t mesh;
     float wnorm;                  // interior draws: |(A[8], A[9], A[10])| rounded up (strip spheres)
     float slack;                  // interior draws: pixels added to a strip sphere's projected radius
-    float wmax, hmax;             // W - 1, H - 1 of the view (copied, so the sphere test reads one record)
+    float wmax, hmax;             // W - 1, H - 1 of the view (exact)
+    unsigned long long* vis;      // visibility buffer of the view
+    float near_plane;             // of the view
+    uint32_t pad;
 };
+static_assert(sizeof(DrawDesc) == 128, "one cache line");
 constexpr uint32_t kDrawInterior = 0x80000000u;
 constexpr uint32_t kDrawViewMask = 0x7FFFFFFFu;
 

@@ -115,6 +115,22 @@ __device__ __forceinline__ int classify(const Clip c[3], const ViewDesc& V, uint
     return kRouteSmall;
 }
 
+// The view fields that a draw record carries.
+__device__ __forceinline__ ViewDesc draw_view(const DrawDesc& D)
+{
+    ViewDesc V;
+    V.vis = D.vis;
+    V.wmax = D.wmax;
+    V.hmax = D.hmax;
+    const float w = D.wmax + 1.0f, h = D.hmax + 1.0f;   // exact: at most 16384
+    V.W = (int32_t)w;
+    V.H = (int32_t)h;
+    V.hW = 0.5f * w;
+    V.hH = 0.5f * h;
+    V.near_plane = D.near_plane;
+    return V;
+}
+
 // One lane rasterizes a small triangle over its bounding box (Sec. 4.1): y outer, x inner,
 // incremental int32 edge values (see kSmallExtent for the range argument).
 template <bool STATS>
@@ -185,7 +201,7 @@ __device__ inline void raster_any_thread(const Clip c[3], uint64_t id, const Vie
     }
 }
 
-#ifndef CURAST_FAST_BLOCK
+#if !defined(CURAST_FAST_BLOCK) && !defined(CURAST_STRIPS_TPT)
 // ----------------------------------------------------------------------------------------------
 // Clear (also resets the queue counters of the frame)
 // ----------------------------------------------------------------------------------------------
@@ -241,7 +257,7 @@ __global__ void __launch_bounds__(256) frame_begin_kernel(FrameBlock<WORDS> b)
     for (uint32_t v = 0; v < nv; ++v)
         clear_view(views[v].vis, (uint64_t)views[v].W * (uint64_t)views[v].H, tid, stride);
 }
-#endif  // CURAST_FAST_BLOCK
+#endif
 
 // ----------------------------------------------------------------------------------------------
 // Stage 1: one lane per triangle, looping over the draws (instances x views) of its work item
@@ -691,16 +707,6 @@ __device__ __forceinline__ bool fast_reject_strip(const float2 (&w)[N], bool any
 // the strip's vertices up to kFastMargin, so the extent test of the union box applies to it.  The
 // radius itself is inflated by 2^-10 in relative terms, which covers the few roundings in r, the
 // norms, the reciprocal and the products below.  A rejected strip covers no pixel centre.
-// A strip whose union box may hold a pixel centre, waiting for its per-triangle tests: the
-// window positions of its N vertices for one draw, the draw and its first triangle.
-template <int N>
-struct StripEntry {
-    float2 w[N];
-    uint32_t draw, tri;
-    uint32_t even;                // bit k: triangle k's own vertex order is an even permutation of
-                                  // strip vertices k, k + 1, k + 2 (same winding)
-};
-
 // Provably back-facing from fast window positions p0, p1, p2 (in the strip's vertex order, `even`
 // when that order has the triangle's own winding): each fast position is within m = kFastMargin of
 // its snapped position, so the snapped signed area differs from the one of the fast positions by at
@@ -718,12 +724,6 @@ __device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2
                     8.0f * m * m + (1.0f / 1048576.0f) * (__builtin_fabsf(P) + __builtin_fabsf(Q));
     return A < -(B * (1.0f + 1.0f / 65536.0f));
 }
-
-// A (draw, lane) pair of the stage-1 strip path whose sphere test could not reject the strip of
-// that lane of the wavefront: it waits in LDS for the union-box and per-triangle tests.
-struct StripPair {
-    uint32_t draw, lane;
-};
 
 // What the sphere test reads of a draw and its view (one record, so one batch of loads per draw).
 struct SphereDraw {
@@ -800,32 +800,13 @@ __device__ __forceinline__ void strip_sphere(const float (&q)[N][3], float (&c)[
     r = __builtin_amdgcn_sqrtf(r2) * (1.0f + 1.0f / 1024.0f);
 }
 
-template <int BLOCK, int TPT, bool STRIPS, bool STATS, int CMP, bool SPH>
+// The fast kernel without strips: the single-draw launch, and the multi-draw one with
+// s1_multi_tris_per_thread = 1 or CURAST_FLAG_NO_STRIPS.
+template <int BLOCK, int TPT, bool STATS, int CMP>
 __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST_DESC_PARAMS)
 {
-    static_assert(!STRIPS || TPT == 2 || TPT == 4 || TPT == 8, "strips of 2, 4 or 8 triangles per lane");
-    static_assert(STRIPS || !SPH, "strip spheres need strips");
     constexpr int WAVES = BLOCK / 64;
-    using Entry = typename std::conditional<STRIPS, IdEntry, ClipEntry>::type;
-    constexpr int NV = TPT + 2;   // vertices of a strip
-    __shared__ Entry s_ring[WAVES][kRing];
-    // Strips that a per-draw test could not reject gather in LDS, 64 at a time, so that their
-    // per-triangle tests run with every lane busy instead of on the few failing lanes of a draw.
-    // Union-box strips keep their window positions (StripRing).  Sphere strips (SPH) keep (draw,
-    // lane) pairs and every lane's strip vertices for the work item, so the lane that drains a pair
-    // projects another lane's strip (StripStore).
-    struct StripRing {
-        StripEntry<NV> e[kRing];
-    };
-    struct StripStore {
-        float q[64][3 * NV];
-        StripPair ring[kRing];
-    };
-    using StripLds =
-        typename std::conditional<!STRIPS, char, typename std::conditional<SPH, StripStore, StripRing>::type>::type;
-    __shared__ StripLds s_strip[WAVES];
-    StripLds& slds = s_strip[threadIdx.x >> 6];
-    uint32_t shead = 0, stail = 0;   // wave-uniform (union-box strips)
+    __shared__ ClipEntry s_ring[WAVES][kRing];
     const FrameHeader hdr = *d_hdr;
     uint64_t first, total;
     work_range(hdr, a.part, first, total);
@@ -833,7 +814,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
     const uint32_t dpi = uni(hdr.draws_per_item);
     const bool early_out = !(a.flags & kFlagNoEarlyOut);
     const bool tiny_cull = !(a.flags & kFlagNoTinyCull);
-    Entry* ring = s_ring[threadIdx.x >> 6];
+    ClipEntry* ring = s_ring[threadIdx.x >> 6];
     uint32_t head = 0, tail = 0;   // wave-uniform
     StatAcc<STATS> st;
     // append (draw d, triangle t) where `need`; fill(e) writes the rest of the entry
@@ -841,7 +822,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
         const unsigned long long m = __ballot(need);
         if (m) {
             if (need) {
-                Entry& e = ring[(tail + rank_in(m)) & (kRing - 1)];
+                ClipEntry& e = ring[(tail + rank_in(m)) & (kRing - 1)];
                 e.draw = d;
                 e.tri = t;
                 fill(e);
@@ -861,92 +842,12 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
             if (rejected) st.add(kStCulledTiny);
         }
     };
-    // window position of one vertex and the per-triangle test, for interior draws (prescaled rows,
-    // no range tests) or general ones (exact transform, range tests, NaN for an undecidable vertex)
-    // clip-plane bits for strips in the kernels without strip spheres (the union-box strips, whose
-    // launches see general draws of meshes reaching past the view: many views of a large mesh)
-    constexpr bool BITS = STRIPS && !SPH;
-    auto window = [&](auto interior_tag, const DrawDesc& D, const ViewDesc& V, const float* q) -> float2 {
-        if constexpr (decltype(interior_tag)::value) return fast_window_prescaled(D.R, D.A + 8, q[0], q[1], q[2]);
-        else return fast_window<BITS>(transform(D.A, q[0], q[1], q[2]), V);
-    };
-    auto reject = [&](auto interior_tag, float2 x, float2 y, float2 z, const ViewDesc& V) -> bool {
-        if constexpr (decltype(interior_tag)::value) return fast_reject_box(x, y, z, V, tiny_cull);
-        else return fast_reject(x, y, z, V, tiny_cull);
-    };
-    // per-triangle tests of n gathered union-box strips, one strip per lane; survivors go to the
-    // exact path
-    auto drain_strips = [&](uint32_t n) __attribute__((always_inline)) {
-        if constexpr (STRIPS && !SPH) {
-            const uint32_t lane = threadIdx.x & 63;
-            const bool have = lane < n;
-            const StripEntry<NV> e = slds.e[(shead + lane) & (kRing - 1)];
-            const uint32_t dd = have ? e.draw : 0u;
-            const DrawDesc& D = d_draws[dd];
-            const ViewDesc V = d_views[D.view & kDrawViewMask];
-            const bool interior = (D.view & kDrawInterior) != 0;
-            const uint32_t dmesh = D.mesh;
-            auto fill_mesh = [&](IdEntry& x) { x.mesh = dmesh; };
-#pragma unroll
-            for (int k = 0; k < TPT; ++k) {
-                const bool rej = interior ? fast_reject_box(e.w[k], e.w[k + 1], e.w[k + 2], V, tiny_cull)
-                                          : fast_reject(e.w[k], e.w[k + 1], e.w[k + 2], V, tiny_cull);
-                const bool back = !rej && fast_back_facing(e.w[k], e.w[k + 1], e.w[k + 2], (e.even >> k) & 1u);
-                if (have && rej) st.add(kStCulledTiny);
-                if (have && back) st.add(kStCulledBack);
-                push(have && !rej && !back, dd, e.tri + (uint32_t)k, fill_mesh);
-            }
-        }
-    };
-    // the union-box and per-triangle tests of n gathered (draw, lane) pairs of sphere strips, one per
-    // lane: the lane projects the strip of lane `src` of its wavefront for draw `dd` (interior or
-    // general); survivors go to the exact path
-    auto drain_pairs = [&](uint32_t head, uint32_t n, uint64_t tb, uint32_t mesh_id, uint32_t d_any)
-        __attribute__((always_inline)) {
-        if constexpr (SPH) {
-            const uint32_t lane = threadIdx.x & 63;
-            const bool have = lane < n;
-            const StripPair e = slds.ring[(head + lane) & (kRing - 1)];
-            const uint32_t dd = have ? e.draw : d_any;
-            const uint32_t src = have ? e.lane : 0u;
-            const DrawDesc& D = d_draws[dd];
-            const ViewDesc V = d_views[D.view & kDrawViewMask];
-            const bool interior = (D.view & kDrawInterior) != 0;
-            float2 w[NV];
-            bool any_nan = false;
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const float* qq = &slds.q[src][3 * i];
-                const float q0 = qq[0], q1 = qq[1], q2 = qq[2];
-                w[i] = interior ? fast_window_prescaled(D.R, D.A + 8, q0, q1, q2)
-                                : fast_window(transform(D.A, q0, q1, q2), V);
-                any_nan |= __builtin_isnan(w[i].x);
-            }
-            const bool all_out = !any_nan && fast_reject_union<NV>(w, V, tiny_cull);
-            if (have) {
-                if (all_out) st.add(kStCulledTiny, TPT);
-                else st.add(kStStripPass);
-            }
-            const bool pass = have && !all_out;
-            const uint32_t tri0 =
-                (uint32_t)(tb * (uint64_t)(BLOCK * TPT) + (uint64_t)(((threadIdx.x & ~63u) + src) * TPT));
-            auto fill_mesh = [&](IdEntry& x) { x.mesh = mesh_id; };
-#pragma unroll
-            for (int k = 0; k < TPT; ++k) {
-                const bool rej = interior ? fast_reject_box(w[k], w[k + 1], w[k + 2], V, tiny_cull)
-                                          : fast_reject(w[k], w[k + 1], w[k + 2], V, tiny_cull);
-                if (pass && rej) st.add(kStCulledTiny);
-                push(pass && !rej, dd, tri0 + (uint32_t)k, fill_mesh);
-            }
-        }
-    };
     for (uint64_t b = first + blockIdx.x; b < total; b += gridDim.x) {
         const WorkItem wi = locate_work(d_segs, n_segs, dpi, b);
         const uint64_t tb = wi.tri_batch;
         const uint32_t d0 = wi.d0, d1 = wi.d1;
         const MeshDesc mesh = d_meshes[wi.mesh];
-        // issue every index load before any use (memory parallelism); with STRIPS lane l owns
-        // triangles TPT l .. TPT l + TPT - 1 of the batch, else l + k BLOCK
+        // issue every index load before any use (memory parallelism); lane l owns triangles l + k BLOCK
         uint32_t vi[TPT][3];
         bool valid[TPT];
         uint32_t tri[TPT];
@@ -957,7 +858,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
         const uint64_t ubit = CMP == 1 ? 3u * t0 * (uint64_t)mesh.idx_bits : 0u;
 #pragma unroll
         for (int k = 0; k < TPT; ++k) {
-            const uint32_t j = STRIPS ? threadIdx.x * TPT + k : k * BLOCK + threadIdx.x;
+            const uint32_t j = k * BLOCK + threadIdx.x;
             const uint64_t t = t0 + j;
             tri[k] = (uint32_t)t;
             valid[k] = t < mesh.T;
@@ -970,203 +871,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
 #pragma unroll
         for (int k = 0; k < TPT; ++k)
             valid[k] = valid[k] && vi[k][0] < mesh.V && vi[k][1] < mesh.V && vi[k][2] < mesh.V;
-        if constexpr (STRIPS) {
-            auto fill_id = [&](IdEntry& e) { e.mesh = wi.mesh; };
-            // strip mode when every lane with a valid triangle has TPT valid triangles forming a
-            // strip: TPT + 2 window positions per draw, and one test of their union box rejects
-            // all TPT triangles at once (it holds each triangle's box)
-            uint32_t sv[TPT + 2];
-            bool all_valid = true, any_valid = false;
-#pragma unroll
-            for (int k = 0; k < TPT; ++k) {
-                all_valid &= valid[k];
-                any_valid |= valid[k];
-            }
-            const bool lane_strip = build_strip<TPT>(vi, sv) && all_valid;
-            // winding of each strip triangle against its own vertex order (union-box strips)
-            uint32_t even = 0;
-            if constexpr (!SPH) {
-#pragma unroll
-                for (int k = 0; k < TPT; ++k) {
-                    const uint32_t a0 = vi[k][0], a1 = vi[k][1];
-                    const bool ev = (a0 == sv[k] && a1 == sv[k + 1]) || (a0 == sv[k + 1] && a1 == sv[k + 2]) ||
-                                    (a0 == sv[k + 2] && a1 == sv[k]);
-                    even |= (uint32_t)ev << k;
-                }
-            }
-            if (__ballot(!any_valid || lane_strip) == __ballot(1)) {
-                float q[TPT + 2][3];
-#pragma unroll
-                for (int i = 0; i < TPT + 2; ++i) {
-                    mesh_vertex<CMP>(mesh, any_valid ? sv[i] : 0u, q[i]);
-                }
-                if constexpr (SPH) {
-                    // this lane's strip vertices, for the lane that drains one of its (draw, lane) pairs
-                    const uint32_t lane = threadIdx.x & 63;
-#pragma unroll
-                    for (int i = 0; i < NV; ++i) {
-                        slds.q[lane][3 * i] = q[i][0];
-                        slds.q[lane][3 * i + 1] = q[i][1];
-                        slds.q[lane][3 * i + 2] = q[i][2];
-                    }
-                    float sc[3], sr;
-                    strip_sphere<NV>(q, sc, sr);
-                    uint32_t phead = 0, ptail = 0;   // wave-uniform
-                    // pairs of draws dbase + j for the set bits j of `bits` go to the ring, a few rounds of
-                    // compaction per 32 draws instead of one per draw
-                    auto flush = [&](uint32_t bits, uint32_t dbase) __attribute__((always_inline)) {
-                        while (__ballot(bits != 0u)) {
-                            const bool has = bits != 0u;
-                            const uint32_t j = has ? (uint32_t)__builtin_ctz(bits) : 0u;
-                            bits &= bits - 1u;
-                            const unsigned long long m = __ballot(has);
-                            if (has) {
-                                StripPair& pe = slds.ring[(ptail + rank_in(m)) & (kRing - 1)];
-                                pe.draw = dbase + j;
-                                pe.lane = lane;
-                            }
-                            ptail += (uint32_t)__popcll(m);
-                            if (ptail - phead >= 64) {
-                                wave_lds_sync();
-                                drain_pairs(phead, 64, tb, wi.mesh, d0);
-                                phead += 64;
-                                wave_lds_sync();
-                            }
-                        }
-                    };
-#pragma unroll 1
-                    for (uint32_t dc = d0; dc < d1; dc += 32) {
-                        const uint32_t dn = min(32u, d1 - dc);
-                        uint32_t bits = 0;
-#pragma unroll 1
-                        for (uint32_t j = 0; j < dn; ++j) {
-                            const uint32_t d = dc + j;
-                            const DrawDesc& D = d_draws[d];
-                            // the view word with the sphere test's fields: one batch of scalar loads per draw
-                            const SphereDraw sd = sphere_draw(d_draws, d);
-                            bool pass;
-                            if (sd.view & kDrawInterior) {
-                                // the strip's bounding sphere first (see sphere_reject)
-                                pass = any_valid && !sphere_reject(sd, sc, sr, tiny_cull);
-                                if (any_valid && pass) st.add(kStSpherePass);
-                            } else {
-                                const ViewDesc V = d_views[D.view & kDrawViewMask];
-                                // the box around the strip's TPT + 2 window positions holds each triangle's box
-                                auto body = [&](auto tag) {
-                                    constexpr bool INTERIOR = decltype(tag)::value;
-                                    float2 w[NV];
-                                    bool any_nan = false;
-#pragma unroll
-                                    for (int i = 0; i < NV; ++i) {
-                                        w[i] = window(tag, D, V, q[i]);
-                                        if constexpr (!INTERIOR) any_nan |= __builtin_isnan(w[i].x);
-                                    }
-                                    return !any_nan && fast_reject_union<NV>(w, V, tiny_cull);
-                                };
-                                const bool all_out =
-                                    (D.view & kDrawInterior) ? body(std::true_type{}) : body(std::false_type{});
-                                pass = any_valid && !all_out;
-                            }
-                            if (any_valid) {
-                                st.add(kStTriDraws, TPT);
-                                st.add(kStStripDraws);
-                                if (!pass) st.add(kStCulledTiny, TPT);
-                            }
-                            bits |= (uint32_t)pass << j;
-                        }
-                        flush(bits, dc);
-                    }
-                    wave_lds_sync();
-                    if (ptail != phead) drain_pairs(phead, ptail - phead, tb, wi.mesh, d0);
-                    wave_lds_sync();
-                } else {
-#pragma unroll 1
-                    for (uint32_t d = d0; d < d1; ++d) {
-                        const DrawDesc& D = d_draws[d];
-                        const ViewDesc V = d_views[D.view & kDrawViewMask];
-                        auto body = [&](auto tag) {
-                            constexpr bool INTERIOR = decltype(tag)::value;
-                            float2 w[TPT + 2];
-                            bool any_nan = false;
-#pragma unroll
-                            for (int i = 0; i < TPT + 2; ++i) {
-                                w[i] = window(tag, D, V, q[i]);
-                                if constexpr (!INTERIOR) any_nan |= __builtin_isnan(w[i].x);
-                            }
-                            const bool all_out = fast_reject_strip<TPT + 2, BITS>(w, any_nan, V, tiny_cull);
-                            if (any_valid) {
-                                st.add(kStTriDraws, TPT);
-                                st.add(kStStripDraws);
-                                if (all_out) st.add(kStCulledTiny, TPT);
-                                else st.add(kStStripPass);
-                            }
-                            const bool pass = any_valid && !all_out;
-                            const unsigned long long m = __ballot(pass);
-                            if (m) {
-                                if (pass) {
-                                    StripEntry<TPT + 2>& se = slds.e[(stail + rank_in(m)) & (kRing - 1)];
-#pragma unroll
-                                    for (int i = 0; i < TPT + 2; ++i) se.w[i] = w[i];
-                                    se.draw = d;
-                                    se.tri = tri[0];
-                                    se.even = even;
-                                }
-                                stail += (uint32_t)__popcll(m);
-                                if (stail - shead >= 64) {
-                                    wave_lds_sync();
-                                    drain_strips(64);
-                                    shead += 64;
-                                    wave_lds_sync();
-                                }
-                            }
-                        };
-                        if (D.view & kDrawInterior) body(std::true_type{});
-                        else body(std::false_type{});
-                    }
-                }
-                continue;
-            }
-            // not a strip everywhere: one triangle at a time over all draws (its index, validity
-            // and id picked by value, so the per-lane arrays stay in registers)
-#pragma unroll 1
-            for (int k = 0; k < TPT; ++k) {
-                uint32_t i3[3] = {vi[0][0], vi[0][1], vi[0][2]};
-                bool vk = valid[0];
-                uint32_t tk = tri[0];
-#pragma unroll
-                for (int j = 1; j < TPT; ++j) {
-                    const uint32_t a0 = vi[j][0], a1 = vi[j][1], a2 = vi[j][2], tj = tri[j];
-                    const bool vj = valid[j];
-                    i3[0] = k == j ? a0 : i3[0];
-                    i3[1] = k == j ? a1 : i3[1];
-                    i3[2] = k == j ? a2 : i3[2];
-                    vk = k == j ? vj : vk;
-                    tk = k == j ? tj : tk;
-                }
-                float p[9];
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    float src[3];
-                    mesh_vertex<CMP>(mesh, vk ? i3[v] : 0u, src);
-                    p[3 * v + 0] = src[0];
-                    p[3 * v + 1] = src[1];
-                    p[3 * v + 2] = src[2];
-                }
-#pragma unroll 1
-                for (uint32_t d = d0; d < d1; ++d) {
-                    const DrawDesc& D = d_draws[d];
-                    const ViewDesc V = d_views[D.view & kDrawViewMask];
-                    auto body = [&](auto tag) {
-                        const bool rej = reject(tag, window(tag, D, V, p), window(tag, D, V, p + 3),
-                                                window(tag, D, V, p + 6), V);
-                        count(vk, rej);
-                        push(vk && !rej, d, tk, fill_id);
-                    };
-                    if (D.view & kDrawInterior) body(std::true_type{});
-                    else body(std::false_type{});
-                }
-            }
-        } else {
+        {
             float p[TPT][9];
 #pragma unroll
             for (int k = 0; k < TPT; ++k)
@@ -1193,13 +898,14 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
 #pragma unroll
                         for (int v = 0; v < 3; ++v) {
                             if constexpr (INTERIOR) {
-                                w[v] = window(tag, D, V, p[k] + 3 * v);
+                                w[v] = fast_window_prescaled(D.R, D.A + 8, p[k][3 * v], p[k][3 * v + 1], p[k][3 * v + 2]);
                             } else {
                                 c[v] = transform(D.A, p[k][3 * v], p[k][3 * v + 1], p[k][3 * v + 2]);
                                 w[v] = fast_window(c[v], V);
                             }
                         }
-                        const bool rej = reject(tag, w[0], w[1], w[2], V);
+                        const bool rej = INTERIOR ? fast_reject_box(w[0], w[1], w[2], V, tiny_cull)
+                                              : fast_reject(w[0], w[1], w[2], V, tiny_cull);
                         count(valid[k], rej);
                         push(valid[k] && !rej, d, tri[k], [&](ClipEntry& e) {
 #pragma unroll
@@ -1218,13 +924,6 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
             }
         }
     }
-    if constexpr (STRIPS && !SPH) {
-        if (stail != shead) {
-            wave_lds_sync();
-            drain_strips(stail - shead);
-            shead = stail;
-        }
-    }
     if (tail != head) {
         wave_lds_sync();
         drain_ring<STATS>(a, d_views, d_meshes, d_draws, ring, head, tail - head, tiny_cull, early_out, st);
@@ -1232,40 +931,369 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
     st.flush(a.stats);
 }
 
-// The fast kernel's variants of one workgroup size and triangles per lane are a translation unit of
-// their own (this file compiled with CURAST_FAST_BLOCK and CURAST_FAST_TPT set), so that the sixteen of
-// them compile in parallel; the unit without the two macros holds everything else.
-template <int BLOCK, int TPT>
-hipError_t stage1_fast_strips(const RasterArgs& a, bool strips, bool spheres, bool stats, uint32_t grid,
-                              hipStream_t s);
+// Stage 1 with triangle strips: meshes with several draws (instances x views), and the single-draw launch
+// under CURAST_FLAG_SINGLE_STRIPS.  One wavefront per workgroup.  A lane keeps the vertices of its TPT
+// consecutive triangles in LDS for the whole work item, as a strip of TPT + 2 vertices when every lane's
+// triangles form one, so that all that waits between the steps below is a 32-bit word:
+//   1. per draw, every lane tests its strip (SPH: its bounding sphere; else the box around its vertices'
+//      window positions); what cannot be rejected is a bit per draw;
+//   2. the (draw, lane) pairs of 32 draws are compacted, and 64 at a time their strips are projected and
+//      tested triangle by triangle (box, back face), the lane reading another lane's vertices;
+//   3. the (draw, lane, triangle) words that survive are compacted again and drained 64 at a time
+//      through the exact classification and small rasterization.
+// Both compactions keep every lane busy, and neither reloads a triangle: the exact path took
+// 8.0 of 29.6 ms (spheres) and 3.7 of 22.8 ms (boxes) for its index, vertex, mesh and view loads on 64
+// views of 512 meshes when it did; it reads one 128-byte draw record
+// now (spheres of 4 29.6 -> 21.0 ms, boxes of 4 22.8 -> 19.5, back faces and clip bits tested in both).
+// A work item whose lanes do not all have strips takes its triangles in groups, through steps 1 (box per
+// triangle) and 3.
+// Without spheres the vertices stay in registers for step 1, and the compiler is held to the registers of
+// 6, 5 or 4 wavefronts per SIMD (64 views: strips of 4 21.3 -> 19.5 ms, of 8 25.7 -> 22.4); the sphere
+// variants get as many by themselves, and are slower when held (3.92 -> 4.19 ms on 4096 instances).
+template <int TPT, bool SPH>
+constexpr int kStripWaves = SPH ? 1 : TPT == 8 ? 4 : TPT == 4 ? 5 : 6;
 
-#ifdef CURAST_FAST_BLOCK
-// Launches whose meshes are all plain or all compressed use a kernel without the per-mesh
-// compression branch (Sec. 4.6 notes the same for its kernels); mixed launches decide per mesh.
-template <int BLOCK, int TPT, bool STRIPS, bool SPH>
-static hipError_t stage1_fast_dispatch(const RasterArgs& a, bool stats, uint32_t grid, hipStream_t s)
+template <int TPT, bool SPH, bool STATS, int CMP>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStripWaves<TPT, SPH>)))
+stage1_strips_kernel(RasterArgs a, CURAST_DESC_PARAMS)
 {
-    // the statistics variants (a measurement aid) decide per mesh, which is right for any launch
+    static_assert(TPT == 2 || TPT == 4 || TPT == 8, "strips of 2, 4 or 8 triangles");
+    constexpr int NV = TPT + 2;              // vertices of a strip
+    constexpr int QS = 3 * NV | 1;           // floats of a lane's vertices, odd against bank conflicts
+    constexpr int GT = NV / 3;               // triangles of a group without strips
+    __shared__ float s_q[64][QS];
+    __shared__ uint32_t s_order[64];         // 4 bits per strip triangle: its vertex order in the strip
+    __shared__ uint32_t s_pair[kRing];       // draw (from d0) << 6 | lane
+    __shared__ uint32_t s_tri[kRing];        // draw (from d0) << 9 | lane << 3 | triangle
+    const FrameHeader hdr = *d_hdr;
+    uint64_t first, total;
+    work_range(hdr, a.part, first, total);
+    const uint32_t n_segs = uni(hdr.n_segs);
+    const uint32_t dpi = uni(hdr.draws_per_item);
+    const bool early_out = !(a.flags & kFlagNoEarlyOut);
+    const bool tiny_cull = !(a.flags & kFlagNoTinyCull);
+    const uint32_t lane = threadIdx.x;
+    StatAcc<STATS> st;
+    for (uint64_t b = first + blockIdx.x; b < total; b += gridDim.x) {
+        const WorkItem wi = locate_work(d_segs, n_segs, dpi, b);
+        const uint32_t d0 = wi.d0, d1 = wi.d1;
+        const MeshDesc mesh = d_meshes[wi.mesh];
+        const uint64_t t0 = wi.tri_batch * (uint64_t)(64 * TPT);
+        const uint32_t tri0 = (uint32_t)t0;
+        // issue every index load before any use; compressed indices: the bit offset of the work item's
+        // first triangle once per wavefront (64-bit), the lane's triangles relative to it (32-bit); an
+        // invalid lane reads the item's first triangle, which exists
+        uint32_t vi[TPT][3];
+        bool valid[TPT];
+        const uint64_t ubit = CMP == 1 ? 3u * t0 * (uint64_t)mesh.idx_bits : 0u;
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+            const uint32_t j = lane * TPT + k;
+            valid[k] = t0 + j < mesh.T;
+            if constexpr (CMP == 1)
+                packed_triangle_at(mesh, ubit >> 5, (uint32_t)(ubit & 31u) + (valid[k] ? 3u * j * mesh.idx_bits : 0u),
+                                   vi[k]);
+            else
+                mesh_triangle<CMP>(mesh, valid[k] ? t0 + j : 0, vi[k]);
+        }
+        bool all_valid = true, any_valid = false;
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+            valid[k] = valid[k] && vi[k][0] < mesh.V && vi[k][1] < mesh.V && vi[k][2] < mesh.V;
+            all_valid &= valid[k];
+            any_valid |= valid[k];
+        }
+        uint32_t sv[NV];
+        const bool lane_strip = build_strip<TPT>(vi, sv) && all_valid;
+        const bool strips = __ballot(!any_valid || lane_strip) == __ballot(1);
+        uint32_t head = 0, tail = 0;         // of s_tri, wave-uniform
+        // exact path of s_tri[head .. head + n), one per lane: triangle k of lane `src` has its vertices at
+        // q[per k + 3 v], v in the order `order` gives
+        auto drain_tris = [&](uint32_t n, uint32_t per, uint32_t k0) {
+            const bool have = lane < n;
+            const uint32_t e = s_tri[(head + lane) & (kRing - 1)];
+            const uint32_t k = e & 7, src = (e >> 3) & 63;
+            const uint32_t dd = d0 + (have ? e >> 9 : 0u);
+            Clip c[3] = {};
+            ViewDesc V;
+            uint64_t idb = 0;
+            if (have) {
+                const DrawDesc& D = d_draws[dd];
+                const uint32_t order = strips ? s_order[src] >> (4 * k) : 4u;
+                const float* q = s_q[src] + per * (k - k0);
+                const uint32_t o0 = order & 3, o1 = (order >> 2) & 3, o2 = 3 - o0 - o1;
+                c[0] = transform(D.A, q[3 * o0], q[3 * o0 + 1], q[3 * o0 + 2]);
+                c[1] = transform(D.A, q[3 * o1], q[3 * o1 + 1], q[3 * o1 + 2]);
+                c[2] = transform(D.A, q[3 * o2], q[3 * o2 + 1], q[3 * o2 + 2]);
+                V = draw_view(D);
+                idb = D.id_base;
+            }
+            exact_route<STATS>(a, have, c, V, dd, tri0 + src * TPT + k, idb, tiny_cull, early_out, st);
+        };
+        // (draw `d` from d0, this lane or `src`, triangles of `bits`) to s_tri, draining when 64 wait
+        auto push_tris = [&](uint32_t bits, auto&& word, uint32_t per, uint32_t k0) {
+            while (true) {
+                if (tail - head < 64) {
+                    const unsigned long long m = __ballot(bits != 0u);
+                    if (!m) break;
+                    if (bits != 0u) s_tri[(tail + rank_in(m)) & (kRing - 1)] = word((uint32_t)__builtin_ctz(bits));
+                    bits &= bits - 1u;
+                    tail += (uint32_t)__popcll(m);
+                } else {
+                    wave_lds_sync();
+                    drain_tris(64, per, k0);
+                    head += 64;
+                    wave_lds_sync();
+                }
+            }
+        };
+        if (!strips) {
+#pragma unroll 1
+            for (int g = 0; g < TPT; g += GT) {
+                // the group's vertices to LDS (its indices are read again, not kept: registers)
+                bool gv[GT];
+                float p[GT][9];
+#pragma unroll
+                for (int h = 0; h < GT; ++h) {
+                    const uint64_t t = t0 + lane * TPT + (uint32_t)(g + h);
+                    gv[h] = g + h < TPT && t < mesh.T;
+                    uint32_t i3[3];
+                    mesh_triangle<CMP>(mesh, gv[h] ? t : 0, i3);
+                    gv[h] = gv[h] && i3[0] < mesh.V && i3[1] < mesh.V && i3[2] < mesh.V;
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) {
+                        float src[3];
+                        mesh_vertex<CMP>(mesh, gv[h] ? i3[v] : 0u, src);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) p[h][3 * v + c] = s_q[lane][9 * h + 3 * v + c] = src[c];
+                    }
+                }
+#pragma unroll 1
+                for (uint32_t d = d0; d < d1; ++d) {
+                    const DrawDesc& D = d_draws[d];
+                    const ViewDesc V = draw_view(D);
+                    uint32_t bits = 0;
+                    auto body = [&](auto tag) {
+                        constexpr bool INTERIOR = decltype(tag)::value;
+#pragma unroll
+                        for (int h = 0; h < GT; ++h) {
+                            float2 w[3];
+#pragma unroll
+                            for (int v = 0; v < 3; ++v) {
+                                const float* q = p[h] + 3 * v;
+                                w[v] = INTERIOR ? fast_window_prescaled(D.R, D.A + 8, q[0], q[1], q[2])
+                                                : fast_window(transform(D.A, q[0], q[1], q[2]), V);
+                            }
+                            const bool rej = INTERIOR ? fast_reject_box(w[0], w[1], w[2], V, tiny_cull)
+                                                      : fast_reject(w[0], w[1], w[2], V, tiny_cull);
+                            if (gv[h]) {
+                                st.add(kStTriDraws);
+                                if (rej) st.add(kStCulledTiny);
+                            }
+                            bits |= (uint32_t)(gv[h] && !rej) << h;
+                        }
+                    };
+                    if (D.view & kDrawInterior) body(std::true_type{});
+                    else body(std::false_type{});
+                    push_tris(bits, [&](uint32_t h) { return (d - d0) << 9 | lane << 3 | ((uint32_t)g + h); }, 9,
+                              (uint32_t)g);
+                }
+                wave_lds_sync();
+                if (tail != head) drain_tris(tail - head, 9, (uint32_t)g);
+                head = tail;
+                wave_lds_sync();
+            }
+            continue;
+        }
+        float sc[3], sr = 0.0f;              // the strip's bounding sphere (SPH)
+        float q[NV][3];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            mesh_vertex<CMP>(mesh, any_valid ? sv[i] : 0u, q[i]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s_q[lane][3 * i + c] = q[i][c];
+        }
+        uint32_t order = 0;
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+            // strip vertices k, k + 1, k + 2 that are the triangle's first and second
+            const uint32_t o0 = vi[k][0] == sv[k] ? 0u : vi[k][0] == sv[k + 1] ? 1u : 2u;
+            const uint32_t o1 = vi[k][1] == sv[k] ? 0u : vi[k][1] == sv[k + 1] ? 1u : 2u;
+            order |= (o0 | o1 << 2) << (4 * k);
+        }
+        s_order[lane] = order;
+        if constexpr (SPH) strip_sphere<NV>(q, sc, sr);
+        wave_lds_sync();
+        uint32_t phead = 0, ptail = 0;       // of s_pair, wave-uniform
+        // per-triangle tests of s_pair[phead .. phead + n), one strip per lane
+        auto drain_pairs = [&](uint32_t n) {
+            const bool have = lane < n;
+            const uint32_t e = have ? s_pair[(phead + lane) & (kRing - 1)] : 0u;
+            const uint32_t src = e & 63;
+            const DrawDesc& D = d_draws[d0 + (e >> 6)];
+            const ViewDesc V = draw_view(D);
+            const bool interior = (D.view & kDrawInterior) != 0;
+            const uint32_t ord = s_order[src];
+            float2 w[NV];
+            bool any_nan = false;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const float* qq = s_q[src] + 3 * i;
+                const float q0 = qq[0], q1 = qq[1], q2 = qq[2];
+                w[i] = interior ? fast_window_prescaled(D.R, D.A + 8, q0, q1, q2)
+                                : fast_window<true>(transform(D.A, q0, q1, q2), V);
+                any_nan |= __builtin_isnan(w[i].x);
+            }
+            // the boxes have had their union test already
+            const bool all_out = SPH && fast_reject_strip<NV, true>(w, any_nan, V, tiny_cull);
+            if (have) {
+                if (all_out) st.add(kStCulledTiny, TPT);
+                else st.add(kStStripPass);
+            }
+            uint32_t bits = 0;
+#pragma unroll
+            for (int k = 0; k < TPT; ++k) {
+                const bool rej = fast_reject(w[k], w[k + 1], w[k + 2], V, tiny_cull);
+                // even permutations of the strip's order: first and second vertex (0, 1), (1, 2) or (2, 0)
+                const uint32_t o = (ord >> (4 * k)) & 15;
+                const bool back = fast_back_facing(w[k], w[k + 1], w[k + 2], o == 4u || o == 9u || o == 2u);
+                if (have && !all_out) {
+                    if (rej) st.add(kStCulledTiny);
+                    else if (back) st.add(kStCulledBack);
+                }
+                bits |= (uint32_t)(!rej && !back) << k;
+            }
+            push_tris(have && !all_out ? bits : 0u, [&](uint32_t k) { return e >> 6 << 9 | src << 3 | k; }, 3, 0);
+        };
+#pragma unroll 1
+        for (uint32_t dc = d0;; dc += 32) {
+            const bool last = dc >= d1;
+            const uint32_t dn = last ? 0u : min(32u, d1 - dc);
+            uint32_t bits = 0;
+#pragma unroll 1
+            for (uint32_t j = 0; j < dn; ++j) {
+                const DrawDesc& D = d_draws[dc + j];
+                bool pass;
+                if constexpr (SPH) {
+                    // the view word with the sphere test's fields: one batch of scalar loads per draw
+                    const SphereDraw sd = sphere_draw(d_draws, dc + j);
+                    if (sd.view & kDrawInterior) {
+                        pass = any_valid && !sphere_reject(sd, sc, sr, tiny_cull);
+                        if (pass) st.add(kStSpherePass);
+                    } else {
+                        const ViewDesc V = draw_view(D);
+                        float2 w[NV];
+                        bool any_nan = false;
+#pragma unroll
+                        for (int i = 0; i < NV; ++i) {
+                            const float* qq = s_q[lane] + 3 * i;
+                            w[i] = fast_window<true>(transform(D.A, qq[0], qq[1], qq[2]), V);
+                            any_nan |= __builtin_isnan(w[i].x);
+                        }
+                        pass = any_valid && !fast_reject_strip<NV, true>(w, any_nan, V, tiny_cull);
+                    }
+                } else {
+                    const ViewDesc V = draw_view(D);
+                    auto body = [&](auto tag) {
+                        constexpr bool INTERIOR = decltype(tag)::value;
+                        float2 w[NV];
+                        bool any_nan = false;
+#pragma unroll
+                        for (int i = 0; i < NV; ++i) {
+                            w[i] = INTERIOR ? fast_window_prescaled(D.R, D.A + 8, q[i][0], q[i][1], q[i][2])
+                                            : fast_window<true>(transform(D.A, q[i][0], q[i][1], q[i][2]), V);
+                            if constexpr (!INTERIOR) any_nan |= __builtin_isnan(w[i].x);
+                        }
+                        pass = any_valid && !fast_reject_strip<NV, true>(w, any_nan, V, tiny_cull);
+                    };
+                    if (D.view & kDrawInterior) body(std::true_type{});
+                    else body(std::false_type{});
+                }
+                if (any_valid) {
+                    st.add(kStTriDraws, TPT);
+                    st.add(kStStripDraws);
+                    if (!pass) st.add(kStCulledTiny, TPT);
+                }
+                bits |= (uint32_t)pass << j;
+            }
+            // the 32 draws' pairs to the ring in a few rounds, 64 drained whenever they wait
+            while (true) {
+                if (ptail - phead < 64) {
+                    const unsigned long long m = __ballot(bits != 0u);
+                    if (m) {
+                        if (bits != 0u)
+                            s_pair[(ptail + rank_in(m)) & (kRing - 1)] =
+                                (dc - d0 + (uint32_t)__builtin_ctz(bits)) << 6 | lane;
+                        bits &= bits - 1u;
+                        ptail += (uint32_t)__popcll(m);
+                        continue;
+                    }
+                    if (!last || ptail == phead) break;
+                }
+                const uint32_t n = min(64u, ptail - phead);
+                wave_lds_sync();
+                drain_pairs(n);
+                phead += n;
+                wave_lds_sync();
+            }
+            if (last) break;
+        }
+        if (tail != head) drain_tris(tail - head, 3, 0);
+        wave_lds_sync();                     // before the next item's vertices
+    }
+    st.flush(a.stats);
+}
+
+// The variants of the two kernels above are translation units of their own, so that they compile in
+// parallel: this file with CURAST_FAST_BLOCK and CURAST_FAST_TPT set (the fast kernel of one workgroup
+// size and triangles per lane) or CURAST_STRIPS_TPT (the strip kernel of one strip length).  The unit
+// without these macros holds everything else.
+template <int BLOCK, int TPT>
+hipError_t stage1_fast_unit(const RasterArgs& a, bool stats, uint32_t grid, hipStream_t s);
+template <int TPT>
+hipError_t stage1_strips_unit(const RasterArgs& a, bool spheres, bool stats, uint32_t grid, hipStream_t s);
+
+#if defined(CURAST_FAST_BLOCK) || defined(CURAST_STRIPS_TPT)
+// Launches whose meshes are all plain or all compressed use a kernel without the per-mesh
+// compression branch (Sec. 4.6 notes the same for its kernels); mixed launches decide per mesh, and
+// so do the statistics variants (a measurement aid), which is right for any launch.
+template <class F>
+static hipError_t by_compression(const RasterArgs& a, bool stats, F&& launch)
+{
     const bool any = (a.compressed_parts >> a.part) & 1u, all = (a.compressed_parts >> (a.part + 8)) & 1u;
-    if (stats) stage1_fast_kernel<BLOCK, TPT, STRIPS, true, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else if (all) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else if (any) stage1_fast_kernel<BLOCK, TPT, STRIPS, false, -1, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
-    else stage1_fast_kernel<BLOCK, TPT, STRIPS, false, 0, SPH><<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    if (stats) launch(std::true_type{}, std::integral_constant<int, -1>{});
+    else if (all) launch(std::false_type{}, std::integral_constant<int, 1>{});
+    else if (any) launch(std::false_type{}, std::integral_constant<int, -1>{});
+    else launch(std::false_type{}, std::integral_constant<int, 0>{});
     return hipGetLastError();
 }
+#endif
+
+#if defined(CURAST_FAST_BLOCK)
 
 template <int BLOCK, int TPT>
-hipError_t stage1_fast_strips(const RasterArgs& a, bool strips, bool spheres, bool stats, uint32_t grid,
-                                     hipStream_t s)
+hipError_t stage1_fast_unit(const RasterArgs& a, bool stats, uint32_t grid, hipStream_t s)
 {
-    if constexpr (TPT == 1) return stage1_fast_dispatch<BLOCK, TPT, false, false>(a, stats, grid, s);
-    else if (!strips) return stage1_fast_dispatch<BLOCK, TPT, false, false>(a, stats, grid, s);
-    else return spheres ? stage1_fast_dispatch<BLOCK, TPT, true, true>(a, stats, grid, s)
-                   : stage1_fast_dispatch<BLOCK, TPT, true, false>(a, stats, grid, s);
+    return by_compression(a, stats, [&](auto st, auto cmp) {
+        stage1_fast_kernel<BLOCK, TPT, decltype(st)::value, decltype(cmp)::value>
+            <<<grid, BLOCK, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    });
 }
+template hipError_t stage1_fast_unit<CURAST_FAST_BLOCK, CURAST_FAST_TPT>(const RasterArgs&, bool, uint32_t, hipStream_t);
 
-template hipError_t stage1_fast_strips<CURAST_FAST_BLOCK, CURAST_FAST_TPT>(const RasterArgs&, bool, bool, bool, uint32_t,
-                                                                          hipStream_t);
+#elif defined(CURAST_STRIPS_TPT)
+
+template <int TPT>
+hipError_t stage1_strips_unit(const RasterArgs& a, bool spheres, bool stats, uint32_t grid, hipStream_t s)
+{
+    return by_compression(a, stats, [&](auto st, auto cmp) {
+        constexpr bool ST = decltype(st)::value;
+        constexpr int CMP = decltype(cmp)::value;
+        if (spheres) stage1_strips_kernel<TPT, true, ST, CMP><<<grid, 64, 0, s>>>(a, CURAST_DESC_ARGS(a));
+        else stage1_strips_kernel<TPT, false, ST, CMP><<<grid, 64, 0, s>>>(a, CURAST_DESC_ARGS(a));
+    });
+}
+template hipError_t stage1_strips_unit<CURAST_STRIPS_TPT>(const RasterArgs&, bool, bool, uint32_t, hipStream_t);
 
 #else
 
@@ -1808,26 +1836,34 @@ hipError_t launch_stage1(const RasterArgs& a, uint32_t block, uint32_t tpt, bool
 }
 
 template <int BLOCK>
-static hipError_t stage1_fast_tpt(const RasterArgs& a, uint32_t tpt, bool strips, bool spheres, bool stats,
-                                  uint32_t grid, hipStream_t s)
+static hipError_t stage1_fast_tpt(const RasterArgs& a, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s)
 {
     switch (tpt) {
-    case 1: return stage1_fast_strips<BLOCK, 1>(a, strips, spheres, stats, grid, s);
-    case 2: return stage1_fast_strips<BLOCK, 2>(a, strips, spheres, stats, grid, s);
-    case 4: return stage1_fast_strips<BLOCK, 4>(a, strips, spheres, stats, grid, s);
-    case 8: return stage1_fast_strips<BLOCK, 8>(a, strips, spheres, stats, grid, s);
+    case 1: return stage1_fast_unit<BLOCK, 1>(a, stats, grid, s);
+    case 2: return stage1_fast_unit<BLOCK, 2>(a, stats, grid, s);
+    case 4: return stage1_fast_unit<BLOCK, 4>(a, stats, grid, s);
+    case 8: return stage1_fast_unit<BLOCK, 8>(a, stats, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_stage1_fast(const RasterArgs& a, uint32_t block, uint32_t tpt, bool strips, bool spheres, bool stats,
-                              uint32_t grid, hipStream_t s)
+hipError_t launch_stage1_fast(const RasterArgs& a, uint32_t block, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s)
 {
     switch (block) {
-    case 64: return stage1_fast_tpt<64>(a, tpt, strips, spheres, stats, grid, s);
-    case 128: return stage1_fast_tpt<128>(a, tpt, strips, spheres, stats, grid, s);
-    case 256: return stage1_fast_tpt<256>(a, tpt, strips, spheres, stats, grid, s);
-    case 512: return stage1_fast_tpt<512>(a, tpt, strips, spheres, stats, grid, s);
+    case 64: return stage1_fast_tpt<64>(a, tpt, stats, grid, s);
+    case 128: return stage1_fast_tpt<128>(a, tpt, stats, grid, s);
+    case 256: return stage1_fast_tpt<256>(a, tpt, stats, grid, s);
+    case 512: return stage1_fast_tpt<512>(a, tpt, stats, grid, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_stage1_strips(const RasterArgs& a, uint32_t tpt, bool spheres, bool stats, uint32_t grid, hipStream_t s)
+{
+    switch (tpt) {
+    case 2: return stage1_strips_unit<2>(a, spheres, stats, grid, s);
+    case 4: return stage1_strips_unit<4>(a, spheres, stats, grid, s);
+    case 8: return stage1_strips_unit<8>(a, spheres, stats, grid, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1871,6 +1907,6 @@ hipError_t launch_stage3(const RasterArgs& a, uint32_t grid, bool stats, hipStre
     return hipGetLastError();
 }
 
-#endif  // CURAST_FAST_BLOCK
+#endif  // CURAST_FAST_BLOCK, CURAST_STRIPS_TPT
 
 }  // namespace curast

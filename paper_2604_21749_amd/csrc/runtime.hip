@@ -29,8 +29,8 @@ hipError_t launch_clear(const RasterArgs& a, uint32_t grid, hipStream_t s);
 hipError_t launch_frame_begin(const FrameBlock<kBlockWordsSmall>& b, uint32_t grid, hipStream_t s);
 hipError_t launch_frame_begin(const FrameBlock<kBlockWords>& b, uint32_t grid, hipStream_t s);
 hipError_t launch_stage1(const RasterArgs& a, uint32_t block, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s);
-hipError_t launch_stage1_fast(const RasterArgs& a, uint32_t block, uint32_t tpt, bool strips, bool spheres, bool stats,
-                              uint32_t grid, hipStream_t s);
+hipError_t launch_stage1_fast(const RasterArgs& a, uint32_t block, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s);
+hipError_t launch_stage1_strips(const RasterArgs& a, uint32_t tpt, bool spheres, bool stats, uint32_t grid, hipStream_t s);
 hipError_t launch_stage1_share(const RasterArgs& a, uint32_t tpt, bool stats, uint32_t grid, hipStream_t s);
 hipError_t launch_stage2(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
 hipError_t launch_stage3(const RasterArgs& a, uint32_t grid, bool stats, hipStream_t s);
@@ -576,6 +576,13 @@ bool PlanT<FixVec>::full() const
 }
 using Plan = PlanT<HeapVec>;
 
+// Whether the launch over `part` (1: meshes with several draws, 2: the others) looks for triangle strips.
+bool uses_strips(const curast_options& o, uint32_t part, uint32_t tpt)
+{
+    return o.s1_mode != 1 && !(part == 1 && o.s1_mode == 3) && !(o.flags & kFlagNoStrips) && tpt >= 2 &&
+           (part == 1 || (o.flags & kFlagSingleStrips));
+}
+
 // Triangles per lane of the single-draw launch when the option is left at its default: 4 keep most
 // loads in flight per wavefront, but a launch too small to fill the chip gains more from more
 // wavefronts (256 compute units hold about 5000 of them).  Measured with 1 / 2 / 4: 0.26 M triangles
@@ -630,11 +637,12 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
     }
     P.meshes.resize(M);
     uint64_t base = 0;
-    // triangles per work item of the first stage-1 launch (the vertex-sharing kernel runs 64-lane
-    // workgroups)
-    const uint32_t bt_multi = (o.s1_mode == 3 ? 64u : o.s1_block) * o.s1_multi_tris_per_thread;
+    // triangles per work item of the first stage-1 launch (the strip and vertex-sharing kernels run
+    // 64-lane workgroups)
+    const uint32_t bt_multi =
+        (o.s1_mode == 3 || uses_strips(o, 1, o.s1_multi_tris_per_thread) ? 64u : o.s1_block) * o.s1_multi_tris_per_thread;
     // smallest batch of either launch (the default single-draw batch depends on the surviving draws)
-    const uint32_t bt_min = std::min(bt_multi, o.s1_block * (auto_tpt ? 1u : o.s1_tris_per_thread));
+    const uint32_t bt_min = std::min(bt_multi, auto_tpt ? 64u : 64u * o.s1_tris_per_thread);
     P.mesh_draw_begin.resize(M);
     P.mesh_draw_count.resize(M);
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "too many meshes or views for the allocation-free form");
@@ -660,6 +668,9 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
                 D.wnorm = D.slack = 0.0f;
                 D.wmax = (float)(views[v].width - 1);
                 D.hmax = (float)(views[v].height - 1);
+                D.vis = reinterpret_cast<unsigned long long*>(views[v].visbuffer);
+                D.near_plane = views[v].near_plane;
+                D.pad = 0;
                 const bool inner = !out && !(o.flags & kFlagNoFastInterior) &&
                                    sphere_interior(D.A, me.bsphere, views[v].near_plane) &&
                                    prescaled_rows(D.A, me.bsphere, 0.5f * (float)views[v].width,
@@ -694,7 +705,8 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
         if (mesh_draw_count[m] && !shared_mesh(m)) single_tris += meshes[m].num_triangles;
     P.tpt_single = auto_tpt ? default_single_tpt(single_tris) : o.s1_tris_per_thread;
     P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
-    const uint32_t bt = o.s1_block * P.tpt_single;   // triangles per work item of the single-draw launch
+    // triangles per work item of the single-draw launch
+    const uint32_t bt = (uses_strips(o, 2, P.tpt_single) ? 64u : o.s1_block) * P.tpt_single;
     for (int pass = 0; pass < 2; ++pass) {
         bool any_cmp = false, all_cmp = true;
         for (uint32_t m = 0; m < M; ++m) {
@@ -852,11 +864,9 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
             if (part == 1 || !P.read_first) a1.flags |= atomic_alone;
             if (part == 1 && mode == 3) return launch_stage1_share(a1, tpt, stats, grid, st);
             if (mode == 1) return launch_stage1(a1, blk, tpt, stats, grid, st);
-            const bool strips = !(a.flags & kFlagNoStrips) && tpt >= 2 &&
-                                (part == 1 || (a.flags & kFlagSingleStrips));
+            if (!uses_strips(ctx->opt, part, tpt)) return launch_stage1_fast(a1, blk, tpt, stats, grid, st);
             // strip spheres in the multi-draw launch, s1_mode 0 and 2 (s1_mode 4: union boxes only)
-            const bool spheres = strips && part == 1 && mode != 4;
-            return launch_stage1_fast(a1, blk, tpt, strips, spheres, stats, grid, st);
+            return launch_stage1_strips(a1, tpt, part == 1 && mode != 4, stats, grid, st);
         };
         if (grid_share && (a.flags & kFlagS1Overlap)) {
             // the single-draw launch (bound by memory) on the side stream next to the multi-draw one
@@ -1026,8 +1036,8 @@ struct NaDesc {
     Segment segs[2];
     DrawDesc draws[kFixedDraws];
 };
-static_assert(sizeof(NaDesc) % 4 == 0 && sizeof(NaDesc) <= sizeof(uint32_t) * kBlockWords,
-              "descriptor block fits one kernel argument");
+static_assert(sizeof(NaDesc) % 4 == 0 && sizeof(NaDesc) <= 2 * sizeof(uint32_t) * kBlockWords,
+              "descriptor block fits two kernel arguments");
 
 constexpr size_t kNaOffCounters = align_up(sizeof(NaDesc), 256);
 constexpr size_t kNaOffStats = kNaOffCounters + 256;
@@ -1113,9 +1123,19 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
     const uint64_t shared = P.hdr.shared_batches;
     auto clear = [&] {
         const size_t used = offsetof(NaDesc, draws) + sizeof(DrawDesc) * P.draws.size();
-        return used <= sizeof(uint32_t) * kBlockWordsSmall
-                   ? frame_begin<kBlockWordsSmall>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s)
-                   : frame_begin<kBlockWords>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s);
+        constexpr size_t kMost = sizeof(uint32_t) * kBlockWords;
+        if (used <= sizeof(uint32_t) * kBlockWordsSmall)
+            return frame_begin<kBlockWordsSmall>(ctx, a, &d, used, offsetof(NaDesc, view), P.hdr, P.total_pixels, s);
+        hipError_t e = frame_begin<kBlockWords>(ctx, a, &d, std::min(used, kMost), offsetof(NaDesc, view), P.hdr,
+                                                P.total_pixels, s);
+        if (e == hipSuccess && used > kMost) {
+            // the last draws of a call with many instances, in a second argument (nothing left to clear)
+            RasterArgs rest = a;
+            rest.hdr = reinterpret_cast<const FrameHeader*>(base + kMost);
+            e = frame_begin<kBlockWords>(ctx, rest, reinterpret_cast<const char*>(&d) + kMost, used - kMost, 0,
+                                         FrameHeader{}, 0, s);
+        }
+        return e;
     };
     return launch_frame(ctx, a, P, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0,
                         s, nullptr);
