@@ -42,7 +42,8 @@ struct ViewDesc {                 // 48 B
     float near_plane;
     uint32_t tile_base;           // first stage-3 tile of this view; its tiles are row-major
     float wmax, hmax;             // W - 1, H - 1 (exact)
-    uint32_t pad[2];
+    float reach;                  // on the device only: DrawDesc::reach of the current draw
+    uint32_t pad;
 };
 
 struct MeshDesc {                 // 80 B
@@ -85,7 +86,7 @@ struct DrawDesc {                 // 128 B: one cache line holds all that a frag
     float wmax, hmax;             // W - 1, H - 1 of the view (exact)
     unsigned long long* vis;      // visibility buffer of the view
     float near_plane;             // of the view
-    uint32_t pad;
+    float reach;                  // 1/2 px + the fast positions' error bound (see the stage-1 kernels)
 };
 static_assert(sizeof(DrawDesc) == 128, "one cache line");
 constexpr uint32_t kDrawInterior = 0x80000000u;

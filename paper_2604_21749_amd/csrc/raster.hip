@@ -128,6 +128,7 @@ __device__ __forceinline__ ViewDesc draw_view(const DrawDesc& D)
     V.hW = 0.5f * w;
     V.hH = 0.5f * h;
     V.near_plane = D.near_plane;
+    V.reach = D.reach;
     return V;
 }
 
@@ -403,7 +404,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_kernel(RasterArgs a, CURAST_DESC
 // Stage 1, fast variant.  Changes to the lane-per-triangle loop, none of which changes a single
 // fragment:
 //  (1) a conservative reject with approximate window positions (v_rcp_f32 instead of the correctly
-//      rounded 1/w) and a bounding box widened by kFastMargin pixels: when the widened box holds no
+//      rounded 1/w) and a bounding box widened by a margin m in pixels: when the widened box holds no
 //      pixel centre inside the view, the exact box cannot hold one either, so the triangle is
 //      culled without the exact arithmetic (almost every triangle of a dense mesh ends here);
 //  (2) the few undecided (triangle, draw) pairs are appended to a list in LDS and run through the
@@ -426,9 +427,13 @@ __global__ void __launch_bounds__(BLOCK) stage1_kernel(RasterArgs a, CURAST_DESC
 //      4u hW (S_x + S_w), the reciprocal of the same w adds 9u S_w hW / w, and rcp with the
 //      multiply 9u hW, so the fast position is within hW u ((7 S_x + 19 S_w) / w + 16) of the
 //      exact one; the host enables the path for a draw only when this bound over its bounding
-//      sphere, plus 2^-9 px of snapping and 3.1u hW of box arithmetic, is below kFastMargin.
+//      sphere, plus 2^-9 px of snapping and 3.1u hW of box arithmetic, is below 1/32 px.
+// The margin m of a draw is its own bound (DrawDesc::reach = m + 1/2, from the host in binary64), 0.002 to
+// 0.02 px for views of 256 to 16384 pixels.  A fixed margin of 1/32 px, which every bound stays under, sent
+// several times as many triangles of 0.05 to 0.3 px through the exact path: with strips of 8, 49 -> 24 M
+// of 2.1 G strip-draws past the sphere and 26 -> 8 M past the boxes, 3.92 -> 3.08 ms (4096 instances of a
+// 2.1M-triangle mesh at 4K); 64 views of 513 meshes 21.0 -> 17.6 ms with spheres, 19.5 -> 16.6 with boxes.
 // ----------------------------------------------------------------------------------------------
-constexpr float kFastMargin = 1.0f / 32.0f;
 constexpr float kFastGuard = 2.0f;
 
 // Clip-plane bits of a vertex: 1 x > w, 2 x < -w, 4 y > w, 8 y < -w, 16 w < near.  A bit that all
@@ -478,11 +483,13 @@ __device__ __forceinline__ float2 fast_window_prescaled(const float* R, const fl
 __device__ __forceinline__ bool fast_reject_extent(float xmin, float xmax, float ymin, float ymax, const ViewDesc& V,
                                                    bool tiny_cull)
 {
-    const float lx = xmin - (kFastMargin + 0.5f);
-    const float fx = __builtin_floorf(xmax + (kFastMargin - 0.5f));
-    const float ly = ymin - (kFastMargin + 0.5f);
-    const float fy = __builtin_floorf(ymax + (kFastMargin - 0.5f));
-    const bool outside = (fx < 0.0f) | (lx > V.wmax) | (fy < 0.0f) | (ly > V.hmax);
+    // everything moved up by one pixel, so that one operation each takes the margin and the half
+    const float back = 1.0f - V.reach;
+    const float lx = xmin + back;
+    const float fx = __builtin_floorf(xmax + V.reach);
+    const float ly = ymin + back;
+    const float fy = __builtin_floorf(ymax + V.reach);
+    const bool outside = (fx < 1.0f) | (lx > V.wmax + 1.0f) | (fy < 1.0f) | (ly > V.hmax + 1.0f);
     const bool empty = (fx < lx) | (fy < ly);
     return outside | (tiny_cull & empty);
 }
@@ -571,7 +578,7 @@ __device__ __forceinline__ void drain_ring(const RasterArgs& a, const ViewDesc* 
 #pragma unroll
         for (int k = 0; k < 3; ++k) c[k] = Clip{e.c[3 * k], e.c[3 * k + 1], e.c[3 * k + 2]};
         const DrawDesc& D = d_draws[dd];
-        V = d_views[D.view & kDrawViewMask];
+        V = draw_view(D);
         idb = D.id_base;
     }
     exact_route<STATS>(a, have, c, V, dd, tt, idb, tiny_cull, early_out, st);
@@ -602,7 +609,7 @@ __device__ __forceinline__ void drain_ring(const RasterArgs& a, const ViewDesc* 
             mesh_vertex(M, iv[k], q);
             c[k] = transform(D.A, q[0], q[1], q[2]);
         }
-        V = d_views[D.view & kDrawViewMask];
+        V = draw_view(D);
         idb = D.id_base;
     }
     exact_route<STATS>(a, have, c, V, dd, tt, idb, tiny_cull, early_out, st);
@@ -672,12 +679,13 @@ __device__ __forceinline__ bool fast_reject_union(const float2 (&w)[N], const Vi
 
 // Clip-plane bits of a fast_window<true> output: exact for a vertex outside the fast range; for a
 // finite position only the bits its distance past a view border proves (the position is within
-// kFastMargin of the exact one, and w > 0, so past W means x > w).
+// the margin of the exact one, and w > 0, so past W means x > w).
 __device__ __forceinline__ uint32_t window_bits(float2 v, const ViewDesc& V)
 {
     if (__builtin_isnan(v.x)) return __builtin_bit_cast(uint32_t, v.y);
-    return (uint32_t)(v.x > (V.wmax + 1.0f) + kFastMargin) | (uint32_t)(v.x < -kFastMargin) << 1 |
-           (uint32_t)(v.y > (V.hmax + 1.0f) + kFastMargin) << 2 | (uint32_t)(v.y < -kFastMargin) << 3;
+    const float m = V.reach - 0.5f;
+    return (uint32_t)(v.x > (V.wmax + 1.0f) + m) | (uint32_t)(v.x < -m) << 1 |
+           (uint32_t)(v.y > (V.hmax + 1.0f) + m) << 2 | (uint32_t)(v.y < -m) << 3;
 }
 
 // The union test of a strip's N window positions; with BITS (positions from fast_window<true>) a
@@ -704,22 +712,21 @@ __device__ __forceinline__ bool fast_reject_strip(const float2 (&w)[N], bool any
 // (and likewise y), provided w(c) - |b| r > 0; the test requires at least w(c) / 2.  The box
 // x(c) +- that bound, widened by the per-draw slack the host derived for the binary32 error of the
 // projected centre and of the box arithmetic (DrawDesc::slack), holds every exact window position of
-// the strip's vertices up to kFastMargin, so the extent test of the union box applies to it.  The
+// the strip's vertices up to the draw's margin, so the extent test of the union box applies to it.  The
 // radius itself is inflated by 2^-10 in relative terms, which covers the few roundings in r, the
 // norms, the reciprocal and the products below.  A rejected strip covers no pixel centre.
 // Provably back-facing from fast window positions p0, p1, p2 (in the strip's vertex order, `even`
-// when that order has the triangle's own winding): each fast position is within m = kFastMargin of
+// when that order has the triangle's own winding): each fast position is within the draw's margin m of
 // its snapped position, so the snapped signed area differs from the one of the fast positions by at
 // most 2m(|a.x| + |a.y| + |b.x| + |b.y|) + 8m^2 (a = p1 - p0, b = p2 - p0); the binary32 evaluation
 // adds at most 5u(|a.x b.y| + |a.y b.x|), bounded here by 2^-20 times that sum, and the bound's own
 // roundings are covered by the factor 1 + 2^-16.  A negative snapped area is culled in every stage,
 // so the triangle covers nothing.  NaN positions (outside the fast range) never pass.
-__device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2, bool even)
+__device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2, bool even, float m)
 {
     const float ax = p1.x - p0.x, ay = p1.y - p0.y, bx = p2.x - p0.x, by = p2.y - p0.y;
     const float P = ax * by, Q = ay * bx;
     const float A = even ? P - Q : Q - P;
-    const float m = kFastMargin;
     const float B = (2.0f * m) * ((__builtin_fabsf(ax) + __builtin_fabsf(ay)) + (__builtin_fabsf(bx) + __builtin_fabsf(by))) +
                     8.0f * m * m + (1.0f / 1048576.0f) * (__builtin_fabsf(P) + __builtin_fabsf(Q));
     return A < -(B * (1.0f + 1.0f / 65536.0f));
@@ -728,7 +735,7 @@ __device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2
 // What the sphere test reads of a draw and its view (one record, so one batch of loads per draw).
 struct SphereDraw {
     float Rx[4], Ry[4], Aw[4];
-    float wnorm, slack, wmax, hmax;
+    float wnorm, slack, wmax, hmax, reach;
     uint32_t view;
 };
 
@@ -747,6 +754,7 @@ __device__ __forceinline__ SphereDraw sphere_draw(const DrawDesc* __restrict__ d
     s.view = D.view;
     s.wmax = D.wmax;
     s.hmax = D.hmax;
+    s.reach = D.reach;
     return s;
 }
 
@@ -769,11 +777,12 @@ __device__ __forceinline__ bool sphere_reject(const SphereDraw& D, const float (
     const float t = r * __builtin_amdgcn_rcpf(den);
     const float rx = __builtin_fmaf(nx, t, D.slack), ry = __builtin_fmaf(ny, t, D.slack);
     // the extent test of fast_reject_extent on the box xc +- rx, yc +- ry, without branches
-    const float lx = (xc - rx) - (kFastMargin + 0.5f);
-    const float fx = __builtin_floorf((xc + rx) + (kFastMargin - 0.5f));
-    const float ly = (yc - ry) - (kFastMargin + 0.5f);
-    const float fy = __builtin_floorf((yc + ry) + (kFastMargin - 0.5f));
-    const bool outside = (fx < 0.0f) | (lx > D.wmax) | (fy < 0.0f) | (ly > D.hmax);
+    const float back = 1.0f - D.reach;
+    const float lx = (xc - rx) + back;
+    const float fx = __builtin_floorf((xc + rx) + D.reach);
+    const float ly = (yc - ry) + back;
+    const float fy = __builtin_floorf((yc + ry) + D.reach);
+    const bool outside = (fx < 1.0f) | (lx > D.wmax + 1.0f) | (fy < 1.0f) | (ly > D.hmax + 1.0f);
     const bool empty = (fx < lx) | (fy < ly);
     return (den >= 0.5f * w) & (outside | (tiny_cull & empty));
 }
@@ -886,7 +895,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
 #pragma unroll 1
             for (uint32_t d = d0; d < d1; ++d) {
                 const DrawDesc& D = d_draws[d];
-                const ViewDesc V = d_views[D.view & kDrawViewMask];
+                const ViewDesc V = draw_view(D);
                 auto body = [&](auto tag) {
                     constexpr bool INTERIOR = decltype(tag)::value;
 #pragma unroll
@@ -1156,7 +1165,8 @@ stage1_strips_kernel(RasterArgs a, CURAST_DESC_PARAMS)
                 const bool rej = fast_reject(w[k], w[k + 1], w[k + 2], V, tiny_cull);
                 // even permutations of the strip's order: first and second vertex (0, 1), (1, 2) or (2, 0)
                 const uint32_t o = (ord >> (4 * k)) & 15;
-                const bool back = fast_back_facing(w[k], w[k + 1], w[k + 2], o == 4u || o == 9u || o == 2u);
+                const bool back = fast_back_facing(w[k], w[k + 1], w[k + 2], o == 4u || o == 9u || o == 2u,
+                                                   V.reach - 0.5f);
                 if (have && !all_out) {
                     if (rej) st.add(kStCulledTiny);
                     else if (back) st.add(kStCulledBack);
@@ -1392,7 +1402,7 @@ __global__ void __launch_bounds__(64) stage1_share_kernel(RasterArgs a, CURAST_D
 #pragma unroll 1
         for (uint32_t d = d0; d < d1; ++d) {
             const DrawDesc D = d_draws[d];
-            const ViewDesc V = d_views[D.view & kDrawViewMask];
+            const ViewDesc V = draw_view(D);
             const bool interior = (D.view & kDrawInterior) != 0;
 #pragma unroll
             for (int r = 0; r < RS; ++r) {

@@ -406,13 +406,27 @@ bool sphere_interior(const float A[12], const float bs[4], float near_plane)
     return lo > 0.0;
 }
 
+// DrawDesc::reach from a bound m on the distance between fast and snapped window positions: m + 1/2,
+// rounded up (1 - reach, the other side's constant in the kernels, is then exact in binary32).
+float reach_of(double m) { return std::nextafter((float)(0.5 + m), 1.0f); }
+
+// The same for draws that take the general fast path: the reciprocal and the two roundings after it
+// differ from the exact path by at most 1.625 h 2^-20 px (|x|, |y| <= 2w, h half the larger side);
+// snapping adds 2^-9 px and the box arithmetic (3h + 1) 2^-24 per operation.
+float general_reach(int32_t width, int32_t height)
+{
+    const double h = 0.5 * std::max(width, height);
+    return reach_of(1.01 * (1.625 * std::ldexp(h, -20) + std::ldexp(3.0 * h + 1.0, -23)) + std::ldexp(1.0, -9));
+}
+
 // Prescaled window rows of an interior draw, R = (hW (row x + row w), hH (row y + row w)), rounded
 // once from binary64.  Returns false when the error bound of the fast positions they give (see the
 // stage-1 kernels: hW u ((7 S_x + 19 S_w) / w + 16) against the exact path, plus 2^-9 px of
-// snapping and (3 hW + 1) u of box arithmetic, 1% slack) may exceed the fast margin of 1/32 px
+// snapping and (3 hW + 1) u of box arithmetic, 1% slack) may exceed 1/32 px
 // anywhere in the bounding sphere; S_r bounds sum_j |row_rj| |v_j| + |row_r3| over the sphere and
 // w is bounded below by its smallest depth.
-bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, float R[8], float* wnorm, float* slack)
+bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, float R[8], float* wnorm, float* slack,
+                    float* reach)
 {
     const double u = std::ldexp(1.0, -24);
     const double c[3] = {bs[0], bs[1], bs[2]}, r = bs[3];
@@ -435,6 +449,7 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
         return 1.01 * (h * u * ((7.0 * s_row + 19.0 * sw) / w_lo + 16.0) + (3.0 * h + 1.0) * u) + std::ldexp(1.0, -9);
     };
     if (!(bound(hW, sx) <= 1.0 / 32.0) || !(bound(hH, sy) <= 1.0 / 32.0)) return false;
+    *reach = reach_of(std::max(bound(hW, sx), bound(hH, sy)));
     for (int k = 0; k < 4; ++k) {
         R[k] = (float)((double)hW * ((double)A[k] + (double)A[8 + k]));
         R[4 + k] = (float)((double)hH * ((double)A[4 + k] + (double)A[8 + k]));
@@ -630,7 +645,8 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
         d.near_plane = views[v].near_plane;
         d.wmax = (float)(views[v].width - 1);
         d.hmax = (float)(views[v].height - 1);
-        d.pad[0] = d.pad[1] = 0;
+        d.reach = 0.0f;
+        d.pad = 0;
         d.tile_base = P.hdr.n_tiles;
         P.hdr.n_tiles += (uint32_t)(((d.W + kTileSize - 1) / kTileSize) * ((d.H + kTileSize - 1) / kTileSize));
         P.total_pixels += (uint64_t)d.W * (uint64_t)d.H;
@@ -670,11 +686,11 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
                 D.hmax = (float)(views[v].height - 1);
                 D.vis = reinterpret_cast<unsigned long long*>(views[v].visbuffer);
                 D.near_plane = views[v].near_plane;
-                D.pad = 0;
                 const bool inner = !out && !(o.flags & kFlagNoFastInterior) &&
                                    sphere_interior(D.A, me.bsphere, views[v].near_plane) &&
                                    prescaled_rows(D.A, me.bsphere, 0.5f * (float)views[v].width,
-                                                  0.5f * (float)views[v].height, D.R, &D.wnorm, &D.slack);
+                                                  0.5f * (float)views[v].height, D.R, &D.wnorm, &D.slack, &D.reach);
+                if (!inner) D.reach = general_reach(views[v].width, views[v].height);
                 if (visible) visible[(P.pair_count + i) * (uint64_t)n_views + v] = out ? 0 : inner ? 2 : 1;
                 if (out) {
                     P.draws_culled++;
