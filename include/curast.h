@@ -115,7 +115,8 @@ typedef struct {
     uint32_t s1_tris_per_thread;/* triangles per thread per stage-1 work item of a mesh drawn once:
                                    1, 2, 4 or 8 (default 4; with 0 a launch of fewer
                                    than 7M triangles takes 2, of fewer than 0.7M 1) */
-    uint32_t s1_draws_per_item; /* (instance x view) draws per stage-1 work item (default 64, Sec. 4.5) */
+    uint32_t s1_draws_per_item; /* (instance x view) draws per stage-1 work item (Sec. 4.5); with 0, 8 to
+                                   128 by the size of the launch (reported as 64) */
     uint32_t s2_waves;          /* persistent stage-2 wavefronts (default 16 per CU) */
     uint32_t s3_blocks;         /* persistent stage-3 workgroups (default 2 per CU) */
     uint32_t q2_capacity;       /* stage-1 -> stage-2 queue entries (default 16M, 128 MB); overflow
@@ -123,7 +124,8 @@ typedef struct {
     uint32_t q3_capacity;       /* stage-2 -> stage-3 tile parts (default 1M); overflow as above */
     uint32_t large_capacity;    /* large (sub-)triangle records for stage 3 (default 256K) */
     uint32_t flags;             /* CURAST_FLAG_* */
-    uint32_t s1_mode;           /* stage-1 kernel: 0 = auto (currently 2), 1 = one lane per
+    uint32_t s1_mode;           /* stage-1 kernel: 0 = auto (2; with s1_multi_tris_per_thread 0, 2 or 4 by
+                                   the draws' triangle sizes), 1 = one lane per
                                    triangle with exact arithmetic only, 2 = conservative fast reject
                                    with approximate reciprocals and wave-compacted exact work, where
                                    a strip of the multi-draw launch is first tested through the
@@ -134,7 +136,8 @@ typedef struct {
                                    s1_mode 3), for meshes with two or more surviving draws, which
                                    stage 1 takes in a launch of its own; with 2 or more, a lane's
                                    consecutive triangles are tested as one strip when they form
-                                   one (default 4) */
+                                   one (default 4; with 0, 8 for tiny triangles and 2 for small
+                                   launches) */
     uint32_t s1_blocks_per_cu;  /* stage-1 grid: at most this many workgroups per compute unit per
                                    launch, each looping over work items (default 2048, 1..65536) */
 } curast_options;

@@ -576,6 +576,8 @@ struct PlanT {
     bool compressed = false;         // some mesh is compressed
     uint32_t compressed_parts = 0;   // RasterArgs::compressed_parts of this frame's stage-1 parts
     uint32_t tpt_single = 0;         // triangles per lane of the single-draw stage-1 launch
+    uint32_t tpt_multi = 0;          // and of the multi-draw one
+    bool spheres = false;            // strip spheres in the multi-draw launch
     bool read_first = false;         // that launch reads the stored key before each atomic
     size_t max_draws = 0;            // without any culling
     size_t off_views = 0, off_meshes = 0, off_segs = 0, off_draws = 0, bytes = 0, max_bytes = 0;
@@ -611,11 +613,37 @@ uint32_t default_single_tpt(uint64_t tris) { return tris < 700000 ? 1u : tris < 
 // costs a round trip per fragment (16 per pixel: 192 and 161 us, 2.3: 137 and 67 us, 0.5: 81 and 29).
 constexpr uint64_t kReadFirstDensity = 32;
 
-// auto_tpt: the caller left s1_tris_per_thread at its default.
-template <template <class> class Vec>
-int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const curast_mesh* meshes, uint32_t M,
-               const curast_view* views, uint32_t n_views, PlanT<Vec>& P, uint8_t* visible = nullptr)
+// Typical triangle edge in pixels of a draw, from the projected radius of its bounding sphere and the
+// triangle count, as if they tiled the sphere (4 pi R^2 = T sqrt(3) / 4 e^2); large without a sphere or
+// with its centre behind the camera.
+double edge_pixels(const DrawDesc& D, const curast_mesh& m)
 {
+    const float* c = m.bsphere;
+    if (!(c[3] > 0.0f)) return 1e3;
+    const double w = (double)D.A[8] * c[0] + (double)D.A[9] * c[1] + (double)D.A[10] * c[2] + D.A[11];
+    if (!(w > 0.0)) return 1e3;
+    const double y = std::sqrt((double)D.A[4] * D.A[4] + (double)D.A[5] * D.A[5] + (double)D.A[6] * D.A[6]);
+    return std::min(1e3, 0.5 * ((double)D.hmax + 1.0) * y * c[3] / w * 5.4 / std::sqrt((double)m.num_triangles));
+}
+
+// Shape of the multi-draw launch where the options leave it open, from the mean edge length over its
+// triangle x draw items.  Strip spheres with strips of 8 pay while a strip stays well under a pixel (4 to 5
+// edges long); boxes around strips of 4 otherwise.  Measured (spheres of 8 / spheres of 4 / boxes of 4 /
+// boxes of 2): edges of 0.03 px 3.08 / 3.91 / 5.82 / 8.07 ms, of about 0.1 px 21.5 / 17.6 / 16.6 / 19.0 ms, of
+// 0.28 px 352 / 281 / 195 / 203 us.
+constexpr double kSphereEdge = 0.06;
+// Draws per work item: as many as leave this many items, at least 8 and at most 128 (a lane's set-up is
+// shared by all of them; fewer items than a few per resident wavefront leave the chip idle at the end):
+// 600 draws of 131K triangles 245 us with 64 (5120 items), 225 with 16; 150 draws of 92K 154 and 66; 4088 draws of
+// 2.1M triangles 3.95 ms with 64, 3.80 with 128, 3.99 with 256.
+constexpr uint64_t kMinItems = 16384;
+
+// `user`: the options as the caller set them, zeros where the choice is open; `o`: with defaults.
+template <template <class> class Vec>
+int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options& o, const curast_mesh* meshes,
+               uint32_t M, const curast_view* views, uint32_t n_views, PlanT<Vec>& P, uint8_t* visible = nullptr)
+{
+    const bool auto_tpt = !user.s1_tris_per_thread;
     if (M && !meshes) return fail(ctx, CURAST_E_INVALID, "meshes is NULL");
     if (!views || n_views == 0) return fail(ctx, CURAST_E_INVALID, "no view");
     for (uint32_t v = 0; v < n_views; ++v) {
@@ -633,7 +661,6 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
         if (total_ids > kMaxIds) return fail(ctx, CURAST_E_ID_RANGE, "more than 2^36 triangle instances");
     }
     const bool cull = !(o.flags & kFlagNoMeshCull);
-    const uint32_t dpi = o.s1_draws_per_item;
     P.views.resize(n_views);
     for (uint32_t v = 0; v < n_views; ++v) {
         ViewDesc& d = P.views[v];
@@ -653,12 +680,6 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
     }
     P.meshes.resize(M);
     uint64_t base = 0;
-    // triangles per work item of the first stage-1 launch (the strip and vertex-sharing kernels run
-    // 64-lane workgroups)
-    const uint32_t bt_multi =
-        (o.s1_mode == 3 || uses_strips(o, 1, o.s1_multi_tris_per_thread) ? 64u : o.s1_block) * o.s1_multi_tris_per_thread;
-    // smallest batch of either launch (the default single-draw batch depends on the surviving draws)
-    const uint32_t bt_min = std::min(bt_multi, auto_tpt ? 64u : 64u * o.s1_tris_per_thread);
     P.mesh_draw_begin.resize(M);
     P.mesh_draw_count.resize(M);
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "too many meshes or views for the allocation-free form");
@@ -706,23 +727,58 @@ int build_plan(curast_ctx* ctx, const curast_options& o, bool auto_tpt, const cu
         mesh_draw_begin[m] = draw_begin;
         mesh_draw_count[m] = (uint32_t)P.draws.size() - draw_begin;
         if (me.num_triangles) {
-            const uint64_t all = (uint64_t)ni * n_views;
-            const uint64_t groups = (all + dpi - 1) / dpi;
-            P.max_draws += all;
-            P.max_batches += ((me.num_triangles + bt_min - 1) / bt_min) * groups;
+            P.max_draws += (uint64_t)ni * n_views;
         }
     }
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes at most 32 instances");
     // stage-1 segments: meshes drawn more than once first (their own launch, whose lanes reuse each
     // loaded triangle over many draws), then the rest; mode 3 sends every mesh to the first
     auto shared_mesh = [&](uint32_t m) { return o.s1_mode == 3 || mesh_draw_count[m] >= 2; };
-    uint64_t single_tris = 0;
-    for (uint32_t m = 0; m < M; ++m)
-        if (mesh_draw_count[m] && !shared_mesh(m)) single_tris += meshes[m].num_triangles;
+    uint64_t single_tris = 0, multi_items = 0;
+    double edges = 0.0;
+    const bool open_shape = !user.s1_multi_tris_per_thread;
+    for (uint32_t m = 0; m < M; ++m) {
+        if (!mesh_draw_count[m]) continue;
+        if (!shared_mesh(m)) {
+            single_tris += meshes[m].num_triangles;
+            continue;
+        }
+        multi_items += meshes[m].num_triangles * (uint64_t)mesh_draw_count[m];
+        if (open_shape)
+            for (uint32_t d = 0; d < mesh_draw_count[m]; ++d)
+                edges += (double)meshes[m].num_triangles * edge_pixels(P.draws[mesh_draw_begin[m] + d], meshes[m]);
+    }
     P.tpt_single = auto_tpt ? default_single_tpt(single_tris) : o.s1_tris_per_thread;
     P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
-    // triangles per work item of the single-draw launch
+    const bool tiny = edges <= kSphereEdge * (double)multi_items;
+    // mode 0 with a given strip length stands for mode 2
+    P.spheres = user.s1_mode || user.s1_multi_tris_per_thread ? o.s1_mode == 0 || o.s1_mode == 2 : tiny;
+    P.tpt_multi = user.s1_multi_tris_per_thread ? o.s1_multi_tris_per_thread : P.spheres && tiny ? 8u : 4u;
+    // triangles per work item of the two launches (the strip and vertex-sharing kernels run 64-lane
+    // workgroups), and draws per work item
+    auto multi_batch = [&] {
+        return (o.s1_mode == 3 || uses_strips(o, 1, P.tpt_multi) ? 64u : o.s1_block) * P.tpt_multi;
+    };
+    auto items = [&](uint32_t per_item) {
+        uint64_t n = 0;
+        for (uint32_t m = 0; m < M; ++m)
+            if (mesh_draw_count[m] && shared_mesh(m))
+                n += (meshes[m].num_triangles + multi_batch() - 1) / multi_batch() *
+                     ((mesh_draw_count[m] + per_item - 1) / per_item);
+        return n;
+    };
+    uint32_t dpi = o.s1_draws_per_item;
+    if (!user.s1_draws_per_item && multi_items)
+        for (dpi = 128; dpi > 8 && items(dpi) < kMinItems; dpi /= 2) {}
+    if (!user.s1_multi_tris_per_thread && P.tpt_multi == 4 && items(dpi) < kMinItems / 2) P.tpt_multi = 2;
+    const uint32_t bt_multi = multi_batch();
     const uint32_t bt = (uses_strips(o, 2, P.tpt_single) ? 64u : o.s1_block) * P.tpt_single;
+    for (uint32_t m = 0; m < M; ++m)
+        if (meshes[m].num_triangles) {
+            const uint64_t all = (uint64_t)n_inst(meshes[m]) * n_views;
+            P.max_batches += (meshes[m].num_triangles + std::min(bt, bt_multi) - 1) / std::min(bt, bt_multi) *
+                             ((all + dpi - 1) / dpi);
+        }
     for (int pass = 0; pass < 2; ++pass) {
         bool any_cmp = false, all_cmp = true;
         for (uint32_t m = 0; m < M; ++m) {
@@ -881,8 +937,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
             if (part == 1 && mode == 3) return launch_stage1_share(a1, tpt, stats, grid, st);
             if (mode == 1) return launch_stage1(a1, blk, tpt, stats, grid, st);
             if (!uses_strips(ctx->opt, part, tpt)) return launch_stage1_fast(a1, blk, tpt, stats, grid, st);
-            // strip spheres in the multi-draw launch, s1_mode 0 and 2 (s1_mode 4: union boxes only)
-            return launch_stage1_strips(a1, tpt, part == 1 && mode != 4, stats, grid, st);
+            return launch_stage1_strips(a1, tpt, part == 1 && P.spheres, stats, grid, st);
         };
         if (grid_share && (a.flags & kFlagS1Overlap)) {
             // the single-draw launch (bound by memory) on the side stream next to the multi-draw one
@@ -894,14 +949,14 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
             e = launch_part(2, P.tpt_single, std::max<uint32_t>(grid1, 1), ctx->side_stream);
             if (e == hipSuccess) e = hipEventRecord(ctx->join_ev, ctx->side_stream);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch");
-            e = launch_part(1, ctx->opt.s1_multi_tris_per_thread, grid_share, s);
+            e = launch_part(1, P.tpt_multi, grid_share, s);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch (multi-draw meshes)");
             if (tf) hipEventRecord(tf->ev[2], s);
             e = hipStreamWaitEvent(s, ctx->join_ev, 0);
             if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 stream join");
         } else {
             if (grid_share) {
-                e = launch_part(1, ctx->opt.s1_multi_tris_per_thread, grid_share, s);
+                e = launch_part(1, P.tpt_multi, grid_share, s);
                 if (e != hipSuccess) return hip_fail(ctx, e, "stage-1 kernel launch (multi-draw meshes)");
             }
             if (tf) hipEventRecord(tf->ev[2], s);
@@ -940,7 +995,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     if (!ctx) return CURAST_E_INVALID;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     Plan P;
-    int rc = build_plan(ctx, ctx->opt, !ctx->user.s1_tris_per_thread, meshes, M, views, n_views, P);
+    int rc = build_plan(ctx, ctx->user, ctx->opt, meshes, M, views, n_views, P);
     if (rc) return rc;
     rc = ensure_queues(ctx);
     if (rc) return rc;
@@ -977,8 +1032,8 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     const uint32_t grid1 = grid_for(P.max_batches);
     // the queue capacities are kernel arguments of the captured launches, so they are part of the key
     uint64_t key[11] = {(uint64_t)M, (uint64_t)n_views, (uint64_t)P.max_bytes, (uint64_t)grid1,
-                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.read_first << 16) | (P.tpt_single << 8) |
-                           (ctx->opt.s1_multi_tris_per_thread << 4) | ctx->opt.s1_mode,
+                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.spheres << 17) | ((uint64_t)P.read_first << 16) |
+                           (P.tpt_single << 8) | (P.tpt_multi << 4) | ctx->opt.s1_mode,
                        ((uint64_t)ctx->opt.s2_waves << 32) | ctx->opt.s3_blocks,
                        ((uint64_t)ctx->opt.flags << 32) | ctx->opt.small_px,
                        ((uint64_t)ctx->opt.medium_px << 32) | ctx->opt.s1_draws_per_item,
@@ -1100,7 +1155,7 @@ int rasterize_noalloc(curast_ctx* ctx, const curast_mesh& mesh, const curast_vie
     if (mesh.instances && mesh.num_instances > kFixedDraws)
         return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes at most 32 instances");
     PlanT<FixVec> P;
-    int rc = build_plan(ctx, ctx->opt, !ctx->user.s1_tris_per_thread, &mesh, 1, &view, 1, P);
+    int rc = build_plan(ctx, ctx->user, ctx->opt, &mesh, 1, &view, 1, P);
     if (rc) return rc;
     NaDesc d;
     std::memset(&d, 0, sizeof d);
@@ -1847,7 +1902,7 @@ int curast_plan(const curast_mesh* meshes, uint32_t M, const curast_view* views,
     if (validate_options(u, msg)) return CURAST_E_INVALID;
     const curast_options o = resolve_defaults(u, 256);
     Plan P;
-    int rc = build_plan(nullptr, o, !u.s1_tris_per_thread, meshes, M, views, n_views, P, visible);
+    int rc = build_plan(nullptr, u, o, meshes, M, views, n_views, P, visible);
     if (rc) return rc;
     log_plan("plan", P, M, n_views);
     if (bases) {

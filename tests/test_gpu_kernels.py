@@ -148,3 +148,27 @@ def test_compression_ranges(ctx, vertices, triangles):
     assert np.array_equal(small.packed.cpu().numpy().view(np.uint32), words)
     q = small.qpos.cpu().numpy().view(np.uint16)
     assert q[-1] == 0 and np.array_equal(q[:-1].reshape(-1, 3), O.quantize_positions(m.pos, lo, step))
+
+
+@pytest.mark.parametrize("order", ["strips", "shuffled", "mixed"])
+@pytest.mark.parametrize("lat,scale,instances", [(4, 0.5, 2), (24, 0.3, 9), (96, 0.05, 40), (128, 0.01, 300)])
+def test_multi_draw_launch_shapes(ctx, order, lat, scale, instances):
+    """The multi-draw launch as the library shapes it by itself: strips of 8 with spheres for tiny
+    triangles, boxes otherwise, few and many draws per work item, odd triangle counts, meshes without a
+    bounding sphere, work items that are not strips throughout."""
+    rng = np.random.default_rng(lat)
+    pos, idx = W.uv_sphere(lat, 2 * lat + 1, 1.0)
+    idx = idx[:-1]
+    if order == "shuffled":
+        idx = idx[rng.permutation(len(idx))]
+    elif order == "mixed":
+        swap = rng.choice(len(idx), len(idx) // 50 + 2, replace=False)
+        idx[np.sort(swap)] = idx[swap]
+    t = np.stack([rng.uniform(-1.8, 1.8, instances), rng.uniform(-1.2, 1.2, instances),
+                  rng.uniform(-3, 3.2, instances)], axis=1)
+    inst = W.instance_matrices(W.random_rotations(rng, instances), rng.uniform(0.5, 2, instances) * scale, t)
+    view = _view(233, 170)
+    for sphere in (True, False):
+        m = W.Mesh(pos, idx, inst=inst, bsphere=W.bounding_sphere(pos) if sphere else None)
+        vis = ctx.rasterize_meshes([api.GpuMesh.from_host(m)], view)
+        assert_vis_equal(api.as_uint64(vis), O.rasterize([m], view), f"{order} {lat} {instances} sphere {sphere}")
