@@ -161,7 +161,8 @@ struct RasterArgs {
                                   // mesh of part p is compressed (host-side kernel choice)
 };
 
-// A frame's descriptor block as a kernel argument (at most 4 KB in all), with what the clear needs.
+// A frame's descriptor block as a kernel argument (at most 4 KB in all), with what the clear needs.  Of a
+// block that is too large, the argument holds the first WORDS and `tail` the rest in pinned host memory.
 constexpr int kBlockWordsSmall = 240, kBlockWords = 960;
 template <int WORDS>
 struct FrameBlock {
@@ -170,7 +171,9 @@ struct FrameBlock {
     uint32_t* tile_head;
     uint32_t words, views_word;   // words of the block in use; the first word of its views
     uint32_t n_views, n_tiles;
-    uint32_t pad[2];
+    const uint32_t* tail;         // pinned host memory: words WORDS, WORDS + 1, ... of the block
+    uint32_t tail_words;
+    uint32_t pad[3];
     alignas(16) uint32_t w[WORDS];
 };
 static_assert(sizeof(FrameBlock<kBlockWords>) <= 4096 - 128, "fits a kernel argument");

@@ -234,10 +234,12 @@ __global__ void __launch_bounds__(256) clear_kernel(RasterArgs a)
 
 // The same with the frame's descriptor block as part of the kernel argument: workgroup 0 writes the
 // block to device memory for the kernels that follow, and every workgroup reads the views it clears
-// from the argument.  Small frames are bound by launches: the copy that uploads larger blocks costs
+// from the argument.  Small frames are bound by launches: a copy that uploads the block costs
 // 3-4 us on the stream and a gap before the next kernel.  With the stage-3 lists and the overflow pass
 // inside stage 2, a 320x240 low-poly frame and its resolve went from 81 to 61 us, a 512x512 frame of
-// 262K triangles from 90 to 71 us.
+// 262K triangles from 90 to 71 us.  The rest of a larger block (more than 25
+// draws) is read from pinned host memory, 16 bytes per lane and spread over the grid, while the
+// other workgroups clear: frames of 150 and 601 draws 103 -> 87 us and 246 -> 230 us against a copy first.
 template <int WORDS>
 __global__ void __launch_bounds__(256) frame_begin_kernel(FrameBlock<WORDS> b)
 {
@@ -250,6 +252,14 @@ __global__ void __launch_bounds__(256) frame_begin_kernel(FrameBlock<WORDS> b)
         if (threadIdx.x < kNumCounters) gl(k->counters)[threadIdx.x] = 0;
         const uint32_t n = k->words;
         for (uint32_t i = threadIdx.x; i < n; i += 256) gl(k->dst)[i] = k->w[i];
+    }
+    const uint32_t tail = k->tail_words;
+    if (tail) {
+        // both sides are 16-byte aligned: the buffers are, and WORDS is a multiple of 4
+        const CURAST_GLOBAL uint4* src = (const CURAST_GLOBAL uint4*)gl(k->tail);
+        CURAST_GLOBAL uint4* dst = (CURAST_GLOBAL uint4*)gl(k->dst + WORDS);
+        for (uint64_t i = tid; i < tail / 4; i += stride) dst[i] = src[i];
+        if (tid < (tail & 3)) gl(k->dst + WORDS)[(tail & ~3u) + tid] = gl(k->tail)[(tail & ~3u) + tid];
     }
     const uint32_t nt = k->n_tiles, nv = k->n_views;
     for (uint64_t i = tid; i < nt; i += stride) gl(k->tile_head)[i] = kNoPart;

@@ -885,8 +885,9 @@ uint32_t clear_grid(const curast_ctx* ctx, uint64_t total_pixels)
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((pairs + 255) / 256, ctx->cus * 16ull));
 }
 
-// The frame's first launch when its descriptor block fits a kernel argument: writes the block to the
-// device and clears (see frame_begin_kernel).
+// The frame's first launch: writes the descriptor block to the device and clears (see
+// frame_begin_kernel).  The launch reads what lies past the first WORDS words of a larger block where it is:
+// such a block is in pinned memory until the launch has ended, with its views in the first WORDS.
 template <int WORDS>
 hipError_t frame_begin(const curast_ctx* ctx, const RasterArgs& a, const void* block, size_t bytes, size_t off_views,
                        const FrameHeader& hdr, uint64_t total_pixels, hipStream_t s)
@@ -895,12 +896,17 @@ hipError_t frame_begin(const curast_ctx* ctx, const RasterArgs& a, const void* b
     b.dst = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(a.hdr));
     b.counters = a.counters;
     b.tile_head = a.tile_head;
-    b.words = (uint32_t)((bytes + 3) / 4);
+    const uint32_t words = (uint32_t)((bytes + 3) / 4);
+    b.words = std::min<uint32_t>(words, WORDS);
+    b.tail_words = words - b.words;
+    b.tail = b.tail_words ? static_cast<const uint32_t*>(block) + WORDS : nullptr;
     b.views_word = (uint32_t)(off_views / 4);
     b.n_views = hdr.n_views;
     b.n_tiles = hdr.n_tiles;
-    std::memcpy(b.w, block, bytes);
-    return launch_frame_begin(b, clear_grid(ctx, total_pixels), s);
+    std::memcpy(b.w, block, std::min(bytes, sizeof b.w));
+    // 16 bytes of the tail per lane, as far as four workgroups per compute unit go
+    const uint32_t tail_grid = std::min<uint32_t>((b.tail_words + 1023) / 1024, (uint32_t)ctx->cus * 4);
+    return launch_frame_begin(b, std::max(clear_grid(ctx, total_pixels), tail_grid), s);
 }
 
 // Launch the device part of a frame over the buffers in `a` (descriptors, queues, counters):
@@ -1002,8 +1008,10 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     rc = ensure_tiles(ctx, P.hdr.n_tiles);
     if (rc) return rc;
     const size_t bytes = use_graph ? P.max_bytes : P.bytes;
-    // a small descriptor block travels as a kernel argument; larger ones through pinned memory
+    // a small descriptor block travels as a kernel argument; larger ones through pinned memory, which the
+    // first launch reads when the views are in the argument
     const bool inline_block = !use_graph && bytes <= sizeof(uint32_t) * kBlockWords;
+    const bool inline_views = !use_graph && P.off_views + sizeof(ViewDesc) * n_views <= sizeof(uint32_t) * kBlockWordsSmall;
     alignas(16) char block[sizeof(uint32_t) * kBlockWords];
     rc = ensure_staging(ctx, ctx->raster_stage, bytes,
                         inline_block ? HostSide::kNone : use_graph ? HostSide::kFixed : HostSide::kNext);
@@ -1014,13 +1022,18 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     TimedFrame* tf = begin_timing(ctx);
     if (!use_graph) {
         const RasterArgs a = make_args(ctx, P);
-        if (!inline_block) {
+        const void* pinned = ctx->raster_stage.host->p;
+        if (!inline_block && !inline_views) {
             rc = upload_staging(ctx, ctx->raster_stage, P.bytes, s);
             if (rc) return rc;
         }
         const uint64_t shared = P.hdr.shared_batches;
         auto clear = [&] {
-            if (!inline_block) return launch_clear(a, clear_grid(ctx, P.total_pixels), s);
+            if (!inline_block) {
+                if (!inline_views) return launch_clear(a, clear_grid(ctx, P.total_pixels), s);
+                hipError_t e = frame_begin<kBlockWordsSmall>(ctx, a, pinned, bytes, P.off_views, P.hdr, P.total_pixels, s);
+                return e == hipSuccess && staging_used(ctx, ctx->raster_stage, s) ? hipErrorUnknown : e;
+            }
             return bytes <= sizeof(uint32_t) * kBlockWordsSmall
                        ? frame_begin<kBlockWordsSmall>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s)
                        : frame_begin<kBlockWords>(ctx, a, block, bytes, P.off_views, P.hdr, P.total_pixels, s);

@@ -172,3 +172,25 @@ def test_multi_draw_launch_shapes(ctx, order, lat, scale, instances):
         m = W.Mesh(pos, idx, inst=inst, bsphere=W.bounding_sphere(pos) if sphere else None)
         vis = ctx.rasterize_meshes([api.GpuMesh.from_host(m)], view)
         assert_vis_equal(api.as_uint64(vis), O.rasterize([m], view), f"{order} {lat} {instances} sphere {sphere}")
+
+
+@pytest.mark.parametrize("n_views", [1, 16, 24])
+@pytest.mark.parametrize("instances", [26, 27, 301, 2500])
+def test_descriptors_from_pinned_memory(instances, n_views):
+    """Frames in flight whose descriptors lie past the kernel argument: the first launch reads them from
+    pinned memory (views in the argument) or a copy uploads them (too many views)."""
+    pos, idx = W.uv_sphere(4, 8, 1.0)
+    views = [_view(16 + i, 20) for i in range(n_views)]
+    rng = np.random.default_rng(instances)
+    with api.Context(flags=api.FLAG_NO_GRAPH) as c:
+        frames = []
+        for _ in range(5):
+            t = np.stack([rng.uniform(-2, 2, instances), rng.uniform(-1.5, 1.5, instances),
+                          rng.uniform(-3, 3, instances)], axis=1)
+            inst = W.instance_matrices(W.random_rotations(rng, instances), rng.uniform(0.02, 0.2, instances), t)
+            m = W.Mesh(pos, idx, inst=inst)
+            g = api.GpuMesh.from_host(m)
+            frames.append((m, g, c.rasterize_batched([g], views) if n_views > 1 else [c.rasterize_meshes([g], views[0])]))
+        for k, (m, _, vis) in enumerate(frames):
+            for i in range(0, n_views, 7):
+                assert_vis_equal(api.as_uint64(vis[i]), O.rasterize([m], views[i]), f"frame {k} view {i}")
