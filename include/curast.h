@@ -124,8 +124,8 @@ typedef struct {
     uint32_t q3_capacity;       /* stage-2 -> stage-3 tile parts (default 1M); overflow as above */
     uint32_t large_capacity;    /* large (sub-)triangle records for stage 3 (default 256K) */
     uint32_t flags;             /* CURAST_FLAG_* */
-    uint32_t s1_mode;           /* stage-1 kernel: 0 = auto (2; with s1_multi_tris_per_thread 0, 2 or 4 by
-                                   the draws' triangle sizes), 1 = one lane per
+    uint32_t s1_mode;           /* stage-1 kernel: 0 = auto (2; with s1_multi_tris_per_thread 0, 2 or 4
+                                   draw by draw, by the triangles' size), 1 = one lane per
                                    triangle with exact arithmetic only, 2 = conservative fast reject
                                    with approximate reciprocals and wave-compacted exact work, where
                                    a strip of the multi-draw launch is first tested through the
@@ -136,8 +136,7 @@ typedef struct {
                                    s1_mode 3), for meshes with two or more surviving draws, which
                                    stage 1 takes in a launch of its own; with 2 or more, a lane's
                                    consecutive triangles are tested as one strip when they form
-                                   one (default 4; with 0, 8 for tiny triangles and 2 for small
-                                   launches) */
+                                   one (default 4; with 0, 2 for small launches) */
     uint32_t s1_blocks_per_cu;  /* stage-1 grid: at most this many workgroups per compute unit per
                                    launch, each looping over work items (default 2048, 1..65536) */
 } curast_options;

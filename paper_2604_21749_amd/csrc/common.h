@@ -81,8 +81,9 @@ struct DrawDesc {                 // 128 B: one cache line holds all that a frag
     uint64_t id_base;
     uint32_t view;                // view index | kDrawInterior
     uint32_t mesh;
-    float wnorm;                  // interior draws: |(A[8], A[9], A[10])| rounded up (strip spheres)
-    float slack;                  // interior draws: pixels added to a strip sphere's projected radius
+    float scale;                  // interior draws: pixels per unit of length at most; 0: bound too loose;
+                                  // < 0: triangles too large for strip spheres
+    float grow;                   // interior draws: pixels added to a strip sphere's projected radius
     float wmax, hmax;             // W - 1, H - 1 of the view (exact)
     unsigned long long* vis;      // visibility buffer of the view
     float near_plane;             // of the view

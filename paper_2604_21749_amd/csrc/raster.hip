@@ -719,12 +719,18 @@ __device__ __forceinline__ bool fast_reject_strip(const float2 (&w)[N], bool any
 // through a bounding sphere (c, r) of its vertices, computed once per work item in object space.
 // For a vertex v = c + d, |d| <= r, with a = (row x'')[0..2] and b = (row w)[0..2] of the draw,
 //   x(v) - x(c) = ((a - x(c) b) . d) / (w(c) + b . d),  so  |x(v) - x(c)| <= |a - x(c) b| r / (w(c) - |b| r)
-// (and likewise y), provided w(c) - |b| r > 0; the test requires at least w(c) / 2.  The box
-// x(c) +- that bound, widened by the per-draw slack the host derived for the binary32 error of the
-// projected centre and of the box arithmetic (DrawDesc::slack), holds every exact window position of
-// the strip's vertices up to the draw's margin, so the extent test of the union box applies to it.  The
-// radius itself is inflated by 2^-10 in relative terms, which covers the few roundings in r, the
-// norms, the reciprocal and the products below.  A rejected strip covers no pixel centre.
+// (and likewise y), provided w(c) - |b| r > 0; the test requires at least w(c) / 2.  By the mean value
+// theorem it is also at most L r, where L bounds the gradient |a - x b| / w over the mesh's bounding sphere
+// (radius p, centre at x0, w0, smallest depth w1): |a - x b| <= |a - x0 b| + |x - x0| |b| and |x - x0| <=
+// |a - x0 b| p / w1, so L = |a - x0 b| (1 + p |b| / w1) / w1, which the host computes once per draw
+// (DrawDesc::scale, the larger axis).  A mesh much nearer than it is large makes L loose; the host then
+// leaves scale 0 and the lane evaluates the first bound.  The box x(c) +- the bound, widened by the per-draw
+// slack the host derived for the binary32 error of the projected centre and of the box arithmetic and by the
+// draw's reach (DrawDesc::grow), holds every exact window position of the strip's vertices up to the draw's
+// margin, so the extent test of the union box applies to it.  The radius itself is inflated by 2^-10 in
+// relative terms, which covers the few roundings in r, the norms, the reciprocal and the products below.
+// A rejected strip covers no pixel centre.  With the first bound alone,
+// 4096 instances of a 2.1M-triangle mesh took 2.95 ms with strips of 8 and 3.75 with 4; with L 2.70 and 2.95.
 // Provably back-facing from fast window positions p0, p1, p2 (in the strip's vertex order, `even`
 // when that order has the triangle's own winding): each fast position is within the draw's margin m of
 // its snapped position, so the snapped signed area differs from the one of the fast positions by at
@@ -745,7 +751,7 @@ __device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2
 // What the sphere test reads of a draw and its view (one record, so one batch of loads per draw).
 struct SphereDraw {
     float Rx[4], Ry[4], Aw[4];
-    float wnorm, slack, wmax, hmax, reach;
+    float scale, grow, wmax, hmax;
     uint32_t view;
 };
 
@@ -759,12 +765,11 @@ __device__ __forceinline__ SphereDraw sphere_draw(const DrawDesc* __restrict__ d
         s.Ry[k] = D.R[4 + k];
         s.Aw[k] = D.A[8 + k];
     }
-    s.wnorm = D.wnorm;
-    s.slack = D.slack;
+    s.scale = D.scale;
+    s.grow = D.grow;
     s.view = D.view;
     s.wmax = D.wmax;
     s.hmax = D.hmax;
-    s.reach = D.reach;
     return s;
 }
 
@@ -777,24 +782,47 @@ __device__ __forceinline__ bool sphere_reject(const SphereDraw& D, const float (
     const float rw = __builtin_amdgcn_rcpf(w);
     const float xc = row_dot(Rx, c[0], c[1], c[2]) * rw;
     const float yc = row_dot(Ry, c[0], c[1], c[2]) * rw;
-    const float ex0 = __builtin_fmaf(-xc, Aw[0], Rx[0]), ex1 = __builtin_fmaf(-xc, Aw[1], Rx[1]),
-                ex2 = __builtin_fmaf(-xc, Aw[2], Rx[2]);
-    const float ey0 = __builtin_fmaf(-yc, Aw[0], Ry[0]), ey1 = __builtin_fmaf(-yc, Aw[1], Ry[1]),
-                ey2 = __builtin_fmaf(-yc, Aw[2], Ry[2]);
-    const float nx = __builtin_amdgcn_sqrtf(__builtin_fmaf(ex2, ex2, __builtin_fmaf(ex1, ex1, ex0 * ex0)));
-    const float ny = __builtin_amdgcn_sqrtf(__builtin_fmaf(ey2, ey2, __builtin_fmaf(ey1, ey1, ey0 * ey0)));
-    const float den = __builtin_fmaf(-D.wnorm, r, w);
-    const float t = r * __builtin_amdgcn_rcpf(den);
-    const float rx = __builtin_fmaf(nx, t, D.slack), ry = __builtin_fmaf(ny, t, D.slack);
+    float rx, ry;
+    bool bounded = true;
+    if (D.scale > 0.0f) {                // uniform
+        rx = ry = __builtin_fmaf(D.scale, r, D.grow);
+    } else {
+        const float ex0 = __builtin_fmaf(-xc, Aw[0], Rx[0]), ex1 = __builtin_fmaf(-xc, Aw[1], Rx[1]),
+                    ex2 = __builtin_fmaf(-xc, Aw[2], Rx[2]);
+        const float ey0 = __builtin_fmaf(-yc, Aw[0], Ry[0]), ey1 = __builtin_fmaf(-yc, Aw[1], Ry[1]),
+                    ey2 = __builtin_fmaf(-yc, Aw[2], Ry[2]);
+        const float nx = __builtin_amdgcn_sqrtf(__builtin_fmaf(ex2, ex2, __builtin_fmaf(ex1, ex1, ex0 * ex0)));
+        const float ny = __builtin_amdgcn_sqrtf(__builtin_fmaf(ey2, ey2, __builtin_fmaf(ey1, ey1, ey0 * ey0)));
+        const float nw = __builtin_amdgcn_sqrtf(__builtin_fmaf(Aw[2], Aw[2], __builtin_fmaf(Aw[1], Aw[1], Aw[0] * Aw[0])));
+        const float den = __builtin_fmaf(-nw * (1.0f + 1.0f / 1048576.0f), r, w);
+        const float t = r * __builtin_amdgcn_rcpf(den);
+        rx = __builtin_fmaf(nx, t, D.grow);
+        ry = __builtin_fmaf(ny, t, D.grow);
+        bounded = den >= 0.5f * w;
+    }
     // the extent test of fast_reject_extent on the box xc +- rx, yc +- ry, without branches
-    const float back = 1.0f - D.reach;
-    const float lx = (xc - rx) + back;
-    const float fx = __builtin_floorf((xc + rx) + D.reach);
-    const float ly = (yc - ry) + back;
-    const float fy = __builtin_floorf((yc + ry) + D.reach);
+    const float lx = (xc - rx) + 1.0f;
+    const float fx = __builtin_floorf(xc + rx);
+    const float ly = (yc - ry) + 1.0f;
+    const float fy = __builtin_floorf(yc + ry);
     const bool outside = (fx < 1.0f) | (lx > D.wmax + 1.0f) | (fy < 1.0f) | (ly > D.hmax + 1.0f);
     const bool empty = (fx < lx) | (fy < ly);
-    return (den >= 0.5f * w) & (outside | (tiny_cull & empty));
+    return bounded & (outside | (tiny_cull & empty));
+}
+
+// The same for a draw with a scale, with tiny culling, as the lane's bit `bit` when the strip passes: no
+// branch, so that two draws' instructions fill each other's latencies (with one draw at a time through
+// sphere_reject its branches and waits cost as much as its arithmetic: 2.70 -> 2.45 ms
+// with strips of 8, 2.95 -> 2.42 with 4).
+__device__ __forceinline__ uint32_t sphere_pass(const SphereDraw& D, const float (&c)[3], float r, uint32_t bit)
+{
+    const float rw = __builtin_amdgcn_rcpf(row_dot(D.Aw, c[0], c[1], c[2]));
+    const float xc = row_dot(D.Rx, c[0], c[1], c[2]) * rw;
+    const float yc = row_dot(D.Ry, c[0], c[1], c[2]) * rw;
+    const float R = __builtin_fmaf(D.scale, r, D.grow);
+    const float lx = fmaxf((xc - R) + 1.0f, 1.0f), ly = fmaxf((yc - R) + 1.0f, 1.0f);
+    const float fx = fminf(__builtin_floorf(xc + R), D.wmax + 1.0f), fy = fminf(__builtin_floorf(yc + R), D.hmax + 1.0f);
+    return (fx >= lx) & (fy >= ly) ? bit : 0u;
 }
 
 // Object-space bounding sphere of N points: their mean (a convex combination, so it lies inside
@@ -1190,27 +1218,58 @@ stage1_strips_kernel(RasterArgs a, CURAST_DESC_PARAMS)
             const bool last = dc >= d1;
             const uint32_t dn = last ? 0u : min(32u, d1 - dc);
             uint32_t bits = 0;
+            uint32_t rest = dn == 32 ? ~0u : (1u << dn) - 1;   // draws that take the general form below
+            if constexpr (SPH) {
+                const float scale = d_draws[lane < dn ? dc + lane : d0].scale;
+                uint32_t quick = tiny_cull ? (uint32_t)__ballot(lane < dn && scale > 0.0f) : 0u;
+                rest &= ~quick;
 #pragma unroll 1
-            for (uint32_t j = 0; j < dn; ++j) {
+                while (quick) {
+                    const uint32_t j0 = (uint32_t)__builtin_ctz(quick);
+                    quick &= quick - 1;
+                    const uint32_t j1 = quick ? (uint32_t)__builtin_ctz(quick) : j0;
+                    quick &= quick - 1;
+                    const SphereDraw s0 = sphere_draw(d_draws, dc + j0), s1 = sphere_draw(d_draws, dc + j1);
+                    bits |= sphere_pass(s0, sc, sr, 1u << j0) | sphere_pass(s1, sc, sr, 1u << j1);
+                }
+                bits = any_valid ? bits : 0u;
+                if (STATS && any_valid) {
+                    const uint32_t n = (uint32_t)__popc(~rest & (dn == 32 ? ~0u : (1u << dn) - 1)), p = (uint32_t)__popc(bits);
+                    st.add(kStTriDraws, TPT * n);
+                    st.add(kStStripDraws, n);
+                    st.add(kStSpherePass, p);
+                    st.add(kStCulledTiny, TPT * (n - p));
+                }
+            }
+#pragma unroll 1
+            while (rest) {
+                const uint32_t j = (uint32_t)__builtin_ctz(rest);
+                rest &= rest - 1;
                 const DrawDesc& D = d_draws[dc + j];
                 bool pass;
                 if constexpr (SPH) {
                     // the view word with the sphere test's fields: one batch of scalar loads per draw
                     const SphereDraw sd = sphere_draw(d_draws, dc + j);
-                    if (sd.view & kDrawInterior) {
+                    if ((sd.view & kDrawInterior) && sd.scale >= 0.0f) {
                         pass = any_valid && !sphere_reject(sd, sc, sr, tiny_cull);
                         if (pass) st.add(kStSpherePass);
                     } else {
                         const ViewDesc V = draw_view(D);
-                        float2 w[NV];
-                        bool any_nan = false;
+                        auto body = [&](auto tag) {
+                            constexpr bool INTERIOR = decltype(tag)::value;
+                            float2 w[NV];
+                            bool any_nan = false;
 #pragma unroll
-                        for (int i = 0; i < NV; ++i) {
-                            const float* qq = s_q[lane] + 3 * i;
-                            w[i] = fast_window<true>(transform(D.A, qq[0], qq[1], qq[2]), V);
-                            any_nan |= __builtin_isnan(w[i].x);
-                        }
-                        pass = any_valid && !fast_reject_strip<NV, true>(w, any_nan, V, tiny_cull);
+                            for (int i = 0; i < NV; ++i) {
+                                const float* qq = s_q[lane] + 3 * i;
+                                w[i] = INTERIOR ? fast_window_prescaled(D.R, D.A + 8, qq[0], qq[1], qq[2])
+                                                : fast_window<true>(transform(D.A, qq[0], qq[1], qq[2]), V);
+                                if constexpr (!INTERIOR) any_nan |= __builtin_isnan(w[i].x);
+                            }
+                            pass = any_valid && !fast_reject_strip<NV, true>(w, any_nan, V, tiny_cull);
+                        };
+                        if (sd.view & kDrawInterior) body(std::true_type{});
+                        else body(std::false_type{});
                     }
                 } else {
                     const ViewDesc V = draw_view(D);

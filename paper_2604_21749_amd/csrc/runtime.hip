@@ -419,13 +419,17 @@ float general_reach(int32_t width, int32_t height)
     return reach_of(1.01 * (1.625 * std::ldexp(h, -20) + std::ldexp(3.0 * h + 1.0, -23)) + std::ldexp(1.0, -9));
 }
 
+// Largest and mean scale over a mesh's bounding sphere may differ by this factor for the strip spheres to use
+// one scale per draw.
+constexpr double kLooseScale = 1.5;
+
 // Prescaled window rows of an interior draw, R = (hW (row x + row w), hH (row y + row w)), rounded
 // once from binary64.  Returns false when the error bound of the fast positions they give (see the
 // stage-1 kernels: hW u ((7 S_x + 19 S_w) / w + 16) against the exact path, plus 2^-9 px of
 // snapping and (3 hW + 1) u of box arithmetic, 1% slack) may exceed 1/32 px
 // anywhere in the bounding sphere; S_r bounds sum_j |row_rj| |v_j| + |row_r3| over the sphere and
 // w is bounded below by its smallest depth.
-bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, float R[8], float* wnorm, float* slack,
+bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, float R[8], float* scale, float* grow,
                     float* reach)
 {
     const double u = std::ldexp(1.0, -24);
@@ -435,14 +439,14 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
         for (int j = 0; j < 3; ++j) s += std::fabs((double)A[4 * row + j]) * (std::fabs(c[j]) + r);
         return s;
     };
-    double w_lo = A[11], g = 0.0, mag = std::fabs((double)A[11]);
+    double w_c = A[11], g = 0.0, mag = std::fabs((double)A[11]);
     for (int j = 0; j < 3; ++j) {
-        w_lo += (double)A[8 + j] * c[j];
+        w_c += (double)A[8 + j] * c[j];
         mag += std::fabs((double)A[8 + j] * c[j]);
         g += (double)A[8 + j] * A[8 + j];
     }
     g = std::sqrt(g);
-    w_lo -= r * g + 1e-4 * (mag + r * g);
+    const double w_lo = w_c - (r * g + 1e-4 * (mag + r * g));
     if (!(w_lo > 0.0)) return false;
     const double sx = S(0), sy = S(1), sw = S(2);
     auto bound = [&](double h, double s_row) {
@@ -454,16 +458,31 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
         R[k] = (float)((double)hW * ((double)A[k] + (double)A[8 + k]));
         R[4 + k] = (float)((double)hH * ((double)A[4 + k] + (double)A[8 + k]));
     }
-    // strip spheres (stage 1, multi-draw launch): |(w row)| rounded up, and the pixels a sphere's
-    // projected radius gets on top, which cover the binary32 error of the projected centre
+    // strip spheres (stage 1, multi-draw launch): the pixels a sphere's projected radius gets on top, which
+    // cover the binary32 error of the projected centre
     // (3.01u S_R / w + |x| (3.01u S_w / w + 3u) with S_R <= hW (S_x + S_w) and |x| <= 3 hW), the same
-    // error carried into the radius, and two roundings of box arithmetic at |x| <= 3 hW
-    *wnorm = std::nextafter((float)std::sqrt((double)A[8] * A[8] + (double)A[9] * A[9] + (double)A[10] * A[10]),
-                            INFINITY);
+    // error carried into the radius, and two roundings of box arithmetic at |x| <= 3 hW, and the reach of
+    // the draw (the third rounding is in its box arithmetic)
     auto slack_of = [&](double h, double s_row) {
         return 2.0 * h * u * (3.01 * s_row / w_lo + 12.04 * sw / w_lo + 9.0) + 6.0 * h * u;
     };
-    *slack = std::nextafter((float)(1.01 * std::max(slack_of(hW, sx), slack_of(hH, sy))), INFINITY);
+    *grow = std::nextafter((float)(1.01 * std::max(slack_of(hW, sx), slack_of(hH, sy)) + *reach), INFINITY);
+    // and the most pixels a unit of length projects to anywhere in the bounding sphere (see the kernels);
+    // for a mesh as near as a few of its radii that is far more than at its far end
+    const double near_by = w_c / w_lo * (1.0 + r * g / w_lo);
+    double most = 0.0;
+    for (int row = 0; row < 2; ++row) {
+        const double h = row == 0 ? hW : hH;
+        double a[3], x0 = h * ((double)A[4 * row + 3] + A[11]), n = 0.0;
+        for (int j = 0; j < 3; ++j) {
+            a[j] = h * ((double)A[4 * row + j] + A[8 + j]);
+            x0 += a[j] * c[j];
+        }
+        x0 /= w_c;
+        for (int j = 0; j < 3; ++j) n += (a[j] - x0 * A[8 + j]) * (a[j] - x0 * A[8 + j]);
+        most = std::max(most, std::sqrt(n) / w_lo * (1.0 + r * g / w_lo));
+    }
+    *scale = near_by <= kLooseScale && most < 1e30 ? std::nextafter((float)(1.001 * most), INFINITY) : 0.0f;
     return true;
 }
 
@@ -626,12 +645,12 @@ double edge_pixels(const DrawDesc& D, const curast_mesh& m)
     return std::min(1e3, 0.5 * ((double)D.hmax + 1.0) * y * c[3] / w * 5.4 / std::sqrt((double)m.num_triangles));
 }
 
-// Shape of the multi-draw launch where the options leave it open, from the mean edge length over its
-// triangle x draw items.  Strip spheres with strips of 8 pay while a strip stays well under a pixel (4 to 5
-// edges long); boxes around strips of 4 otherwise.  Measured (spheres of 8 / spheres of 4 / boxes of 4 /
-// boxes of 2): edges of 0.03 px 3.08 / 3.91 / 5.82 / 8.07 ms, of about 0.1 px 21.5 / 17.6 / 16.6 / 19.0 ms, of
-// 0.28 px 352 / 281 / 195 / 203 us.
-constexpr double kSphereEdge = 0.06;
+// Typical edge in pixels up to which a draw's strips (of 4 triangles) are first tested through their
+// bounding spheres, where the options leave the form open: a sphere costs a third of a box around the strip's
+// vertices, but its extent passes more often.  Spheres / boxes, 4096 instances of a 2.1M-triangle mesh:
+// 0.02 to 0.03 px 0.43 / 0.91 ms, 0.06 to 0.09 px 0.93 / 1.85; 64 views of 512 meshes: 0.06 to 0.09 px
+// 2.06 / 2.40 ms, 0.09 to 0.13 px 2.46 / 2.69, 0.13 to 0.16 px 1.80 / 1.80, 0.2 to 0.25 px 2.13 / 1.85.
+constexpr double kSphereEdge = 0.13;
 // Draws per work item: as many as leave this many items, at least 8 and at most 128 (a lane's set-up is
 // shared by all of them; fewer items than a few per resident wavefront leave the chip idle at the end):
 // 600 draws of 131K triangles 245 us with 64 (5120 items), 225 with 16; 150 draws of 92K 154 and 66; 4088 draws of
@@ -702,7 +721,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
                 draw_matrix(views[v].view_proj, me.instances ? me.instances + 12ull * i : nullptr, D.A);
                 const bool out = cull && sphere_outside(D.A, me.bsphere, views[v].near_plane);
                 for (int k = 0; k < 8; ++k) D.R[k] = 0.0f;
-                D.wnorm = D.slack = 0.0f;
+                D.scale = D.grow = 0.0f;
                 D.wmax = (float)(views[v].width - 1);
                 D.hmax = (float)(views[v].height - 1);
                 D.vis = reinterpret_cast<unsigned long long*>(views[v].visbuffer);
@@ -710,7 +729,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
                 const bool inner = !out && !(o.flags & kFlagNoFastInterior) &&
                                    sphere_interior(D.A, me.bsphere, views[v].near_plane) &&
                                    prescaled_rows(D.A, me.bsphere, 0.5f * (float)views[v].width,
-                                                  0.5f * (float)views[v].height, D.R, &D.wnorm, &D.slack, &D.reach);
+                                                  0.5f * (float)views[v].height, D.R, &D.scale, &D.grow, &D.reach);
                 if (!inner) D.reach = general_reach(views[v].width, views[v].height);
                 if (visible) visible[(P.pair_count + i) * (uint64_t)n_views + v] = out ? 0 : inner ? 2 : 1;
                 if (out) {
@@ -735,8 +754,9 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     // loaded triangle over many draws), then the rest; mode 3 sends every mesh to the first
     auto shared_mesh = [&](uint32_t m) { return o.s1_mode == 3 || mesh_draw_count[m] >= 2; };
     uint64_t single_tris = 0, multi_items = 0;
-    double edges = 0.0;
-    const bool open_shape = !user.s1_multi_tris_per_thread;
+    // spheres as the mode says (mode 0 with a given strip length stands for mode 2), or draw by draw
+    const bool open_shape = !user.s1_mode && !user.s1_multi_tris_per_thread;
+    P.spheres = !open_shape && (o.s1_mode == 0 || o.s1_mode == 2);
     for (uint32_t m = 0; m < M; ++m) {
         if (!mesh_draw_count[m]) continue;
         if (!shared_mesh(m)) {
@@ -745,15 +765,15 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
         }
         multi_items += meshes[m].num_triangles * (uint64_t)mesh_draw_count[m];
         if (open_shape)
-            for (uint32_t d = 0; d < mesh_draw_count[m]; ++d)
-                edges += (double)meshes[m].num_triangles * edge_pixels(P.draws[mesh_draw_begin[m] + d], meshes[m]);
+            for (uint32_t d = 0; d < mesh_draw_count[m]; ++d) {
+                DrawDesc& D = P.draws[mesh_draw_begin[m] + d];
+                if (edge_pixels(D, meshes[m]) > kSphereEdge) D.scale = -1.0f;
+                else P.spheres = true;
+            }
     }
     P.tpt_single = auto_tpt ? default_single_tpt(single_tris) : o.s1_tris_per_thread;
     P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
-    const bool tiny = edges <= kSphereEdge * (double)multi_items;
-    // mode 0 with a given strip length stands for mode 2
-    P.spheres = user.s1_mode || user.s1_multi_tris_per_thread ? o.s1_mode == 0 || o.s1_mode == 2 : tiny;
-    P.tpt_multi = user.s1_multi_tris_per_thread ? o.s1_multi_tris_per_thread : P.spheres && tiny ? 8u : 4u;
+    P.tpt_multi = user.s1_multi_tris_per_thread ? o.s1_multi_tris_per_thread : 4u;
     // triangles per work item of the two launches (the strip and vertex-sharing kernels run 64-lane
     // workgroups), and draws per work item
     auto multi_batch = [&] {
