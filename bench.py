@@ -50,16 +50,15 @@ VALU_ISSUE_PEAK = CUS * CLOCK_HZ            # wave64 VALU instructions per secon
 #   reciprocal and two multiplies = 12;
 #   the box test of n window positions: 4 (n - 1) min/max, then 2 margin subtracts, 2 margin adds,
 #   2 floors and 6 compares = 4 (n - 1) + 12;
-#   the sphere test of a strip (s1_mode 0 and 2): the centre's projection (12), the two vectors
-#   a - x b (6 FMA), their squared norms (6) and square roots (2), the denominator (1 FMA, 1 multiply,
-#   1 compare), its reciprocal and the radius scale (2), the two radii (2 FMA), the box +- radius (4)
-#   and the extent test (12) = 49;
+#   the sphere test of a strip (s1_mode 0 and 2): the centre's projection (12), the radius (1 FMA),
+#   the clamped lower (3) and upper (4) end of its box on each axis, 2 compares, a select and an or
+#   = 31;
 #   one (strip of S triangles, draw): the sphere test, then for a strip the sphere cannot reject
 #   S + 2 projections and the union-box test of its S + 2 vertices (s1_mode 4: always the latter);
 #   a strip whose union box may hold a pixel centre: S more box tests of 3 positions (20 each);
 #   a triangle outside a strip (poles, row ends): 3 projections and its box test.
 PROJ_OPS = 12
-SPHERE_OPS = 49
+SPHERE_OPS = 31
 
 
 def box_ops(n: int) -> int:
@@ -399,9 +398,9 @@ def stage1_rooflines(h):
     o = h["options"]
     strip = o["s1_multi_tris_per_thread"] in (2, 4, 8) and not (o["flags"] & 0x100)
     sph = "true" if strip and o["s1_mode"] in (0, 2) else "false"
-    k_single = f"stage1_fast_kernel<{o['s1_block']}, {o['s1_tris_per_thread']}, false, false, 0, false>"
-    k_multi = f"stage1_fast_kernel<{o['s1_block']}, {o['s1_multi_tris_per_thread']}, {'true' if strip else 'false'}, " \
-              f"false, 0, {sph}>"
+    k_single = f"stage1_fast_kernel<{o['s1_block']}, {o['s1_tris_per_thread']}, false, 0>"
+    k_multi = f"stage1_strips_kernel<{o['s1_multi_tris_per_thread']}, {sph}, false, 0>" if strip else \
+        f"stage1_fast_kernel<{o['s1_block']}, {o['s1_multi_tris_per_thread']}, false, 0>"
     single_bytes = stage1_algorithmic_bytes(h["single"])
     t_single = max(sm["stage1_single"] * 1e-3, 1e-12)
     t_multi = max(sm["stage1_multi"] * 1e-3, 1e-12)

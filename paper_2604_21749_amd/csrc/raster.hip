@@ -1,7 +1,7 @@
-// Rasterization kernels for gfx950: clear, stage 1 (one lane per small triangle), the stage-1
-// overflow pass, stage 2 (a wavefront sets up 64 medium triangles in parallel, clipping them, then
-// rasterizes them one by one) and stage 3 (one workgroup per 64x64 tile part of a large
-// triangle).  Sec. 4.1-4.3 describe the three stages; the wave64
+// Rasterization kernels for gfx950: the frame's first launch (descriptors and clear), stage 1 (one lane
+// per small triangle, or per strip of a mesh drawn several times), stage 2 (the stage-1 overflow pass;
+// then a wavefront sets up to 64 medium triangles up in parallel, clipping them, and rasterizes them one
+// by one) and stage 3 (workgroups over quarters of the 64x64 tiles that large triangles touch).  Sec. 4.1-4.3 describe the three stages; the wave64
 // mapping, ballot-compacted queues and in-place overflow handling are this implementation's.
 #include <hip/hip_runtime.h>
 
@@ -423,7 +423,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_kernel(RasterArgs a, CURAST_DESC
 //  (3) interior draws (bounding sphere inside |x|, |y| <= 1.99 w, w >= 1.001 near, checked on the
 //      host) skip the per-vertex range tests and take their window position from two prescaled
 //      rows, x'' = hW (row x + row w) . (v, 1) and likewise y'', so that x''/w is the window x;
-//  (4) with STRIPS a lane owns TPT consecutive triangles; when every lane's triangles form a
+//  (4) in the strip kernel a lane owns TPT consecutive triangles; when every lane's triangles form a
 //      strip (each shares an edge with the next, as along the rows of a grid or the bands of a
 //      sphere) they need TPT + 2 window positions per draw instead of 3 TPT, and one test of the
 //      box around all of them rejects the whole strip (it contains each triangle's box).
@@ -519,8 +519,8 @@ __device__ __forceinline__ bool fast_reject(float2 a, float2 b, float2 c, const 
 
 // Undecided (triangle, draw) pairs wait in a per-wavefront ring in LDS; the wavefront drains 64 of
 // them at a time with every lane busy.  Entries carry the exact clip coordinates where the lane
-// has them at hand (ClipEntry: the drain then loads only the draw and its view); the strip
-// kernels store ids (IdEntry) and the drain reloads the triangle, which is rare there.  Head and
+// has them at hand (ClipEntry: the drain then loads only the draw and its view); the vertex-sharing
+// kernel stores ids (IdEntry) and the drain reloads the triangle, which is rare there.  Head and
 // tail are wave-uniform (scalar), so no workgroup barrier is needed.
 struct ClipEntry {
     float c[9];
