@@ -487,19 +487,16 @@ class Context:
         """curast_resolve: interpolated attributes float32 [H, W, C] of a visibility buffer.  With
         samples_per_axis = s > 1 (curast_resolve_supersampled) `view` and `vis` are at s times the
         output size and the result is [H / s, W / s, C], the mean of each pixel's s x s samples."""
+        # the library reads one pointer per mesh: a list that ends early may leave out only meshes without triangles
+        if any(m.num_triangles for m in meshes[len(attrs):]):
+            raise ValueError("one attrs entry per mesh with triangles")
         keep = []
         ss = int(samples_per_axis)
         arr = _mesh_array(meshes, keep)
         Cn = int(attrs[0].shape[1])
-        if len(attrs) == len(meshes):
-            ptrs = _row_pointers(attrs, meshes, Cn, "attrs")
-        else:
-            for a in attrs:
-                _check_cuda(a, torch.float32, "attrs", Cn)
-            for m, a in zip(meshes, attrs):
-                if a.shape[0] != m.num_vertices:
-                    raise ValueError("attrs[m] must have one row per vertex of mesh m")
-            ptrs = (C.c_void_p * max(1, len(attrs)))(*[a.data_ptr() for a in attrs])
+        ptrs = _row_pointers(attrs, meshes, Cn, "attrs")
+        for a in attrs[len(meshes):]:
+            _check_cuda(a, torch.float32, "attrs", Cn)
         if ss < 1 or view.width % ss or view.height % ss:
             raise ValueError("view size must be a multiple of samples_per_axis")
         shape = (view.height // ss, view.width // ss, Cn)
