@@ -116,7 +116,7 @@ typedef struct {
                                    1, 2, 4 or 8 (default 4; with 0 a launch of fewer
                                    than 7M triangles takes 2, of fewer than 0.7M 1) */
     uint32_t s1_draws_per_item; /* (instance x view) draws per stage-1 work item (Sec. 4.5); with 0, 8 to
-                                   128 by the size of the launch (reported as 64) */
+                                   128 by the size of the launch */
     uint32_t s2_waves;          /* persistent stage-2 wavefronts (default 16 per CU) */
     uint32_t s3_blocks;         /* persistent stage-3 workgroups (default 2 per CU) */
     uint32_t q2_capacity;       /* stage-1 -> stage-2 queue entries (default 16M, 128 MB); overflow
@@ -220,7 +220,9 @@ int curast_create(const curast_options* opt, curast_ctx** out);
 /* Destroy a context after its enqueued work has completed.  NULL is accepted. */
 int curast_destroy(curast_ctx* ctx);
 
-/* Replace / read the context options (same validation as curast_create). */
+/* Replace / read the context options (same validation as curast_create).  Reading gives every option its
+   effective value, except that s1_tris_per_thread, s1_multi_tris_per_thread and s1_draws_per_item read 0
+   when they were left at 0, since every launch chooses them by itself: setting what was read changes nothing. */
 int curast_set_options(curast_ctx* ctx, const curast_options* opt);
 int curast_get_options(const curast_ctx* ctx, curast_options* opt);
 
@@ -433,7 +435,8 @@ int curast_resolve_backward_meshes(curast_ctx* ctx, const curast_mesh* meshes, u
  * cache_path is not NULL, stored in a JSON file keyed by device and scene class; an existing
  * entry for the same key is loaded instead of measuring.  views' visbuffers are overwritten.
  * Candidates are timed with the context's stage timers (GPU time of the frame's kernels), which
- * are reset.  Queue capacities are raised to twice the measured fill when that exceeds the
+ * are reset.  The search starts from the context's options, and 0 (every launch chooses by itself)
+ * is a candidate of the three options that allow it.  Queue capacities are raised to twice the measured fill when that exceeds the
  * library defaults and are never set below the defaults, so a cached choice does not push a
  * busier scene of the same class into the in-place overflow path (q2_overflow / q3_overflow in
  * curast_stats count triangles that took it).

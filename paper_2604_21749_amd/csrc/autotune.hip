@@ -186,10 +186,11 @@ extern "C" int curast_autotune(curast_ctx* ctx, const curast_mesh* meshes, uint3
         uint32_t curast_options::*ptr;
         std::vector<uint32_t> values;
     };
+    // 0 leaves a choice to every launch; it is where the search starts unless the caller has set the option
     std::vector<Axis> axes = {
         {&curast_options::s1_mode, {0, 1, 2, 3, 4}},
         {&curast_options::s1_block, {64, 128, 256, 512}},
-        {&curast_options::s1_tris_per_thread, {1, 2, 4, 8}},
+        {&curast_options::s1_tris_per_thread, {0, 1, 2, 4, 8}},
         {&curast_options::s1_blocks_per_cu, {256, 1024, 2048, 4096}},
         {&curast_options::small_px, {32, 64, 128, 256, 512}},
         {&curast_options::medium_px, {1024, 4096, 16384}},
@@ -197,8 +198,8 @@ extern "C" int curast_autotune(curast_ctx* ctx, const curast_mesh* meshes, uint3
         {&curast_options::s3_blocks, {cus, cus * 2, cus * 4}},
     };
     if (max_draws > 1) {
-        axes.push_back({&curast_options::s1_multi_tris_per_thread, {1, 2, 4, 8}});
-        axes.push_back({&curast_options::s1_draws_per_item, {8, 16, 32, 64, 128, 256}});
+        axes.push_back({&curast_options::s1_multi_tris_per_thread, {0, 1, 2, 4, 8}});
+        axes.push_back({&curast_options::s1_draws_per_item, {0, 8, 16, 32, 64, 128, 256}});
     }
     for (int pass = 0; pass < 2; ++pass) {
         bool improved = false;

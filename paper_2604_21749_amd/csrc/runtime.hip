@@ -1486,6 +1486,10 @@ int curast_get_options(const curast_ctx* ctx, curast_options* opt)
 {
     if (!ctx || !opt) return CURAST_E_INVALID;
     *opt = ctx->opt;
+    // fields whose value every launch chooses by itself stay 0, so that setting what was read changes nothing
+    opt->s1_tris_per_thread = ctx->user.s1_tris_per_thread;
+    opt->s1_multi_tris_per_thread = ctx->user.s1_multi_tris_per_thread;
+    opt->s1_draws_per_item = ctx->user.s1_draws_per_item;
     return CURAST_OK;
 }
 
