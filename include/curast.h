@@ -114,7 +114,8 @@ typedef struct {
     uint32_t s1_block;          /* stage-1 workgroup size: 64, 128, 256 or 512 (default 64, Sec. 4.1) */
     uint32_t s1_tris_per_thread;/* triangles per thread per stage-1 work item of a mesh drawn once:
                                    1, 2, 4 or 8 (default 4; with 0 a launch of fewer
-                                   than 7M triangles takes 2, of fewer than 0.7M 1) */
+                                   than 7M triangles takes 2, of fewer than 0.7M 1, except under
+                                   CURAST_FLAG_SINGLE_STRIPS, which takes strips of 4) */
     uint32_t s1_draws_per_item; /* (instance x view) draws per stage-1 work item (Sec. 4.5); with 0, 8 to
                                    128 by the size of the launch */
     uint32_t s2_waves;          /* persistent stage-2 wavefronts (default 16 per CU) */

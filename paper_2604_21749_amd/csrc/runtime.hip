@@ -623,8 +623,11 @@ bool uses_strips(const curast_options& o, uint32_t part, uint32_t tpt)
 // loads in flight per wavefront, but a launch too small to fill the chip gains more from more
 // wavefronts (256 compute units hold about 5000 of them).  Measured with 1 / 2 / 4: 0.26 M triangles
 // 10.6 / 11.6 / 18.7 us, 1.0 M 23.5 / 23.4 / 28.8, 3.4 M 42 / 34 / 44, 8.4 M 87 / 67.5 / 66.8,
-// 10 M 99 / 64 / 56.
-uint32_t default_single_tpt(uint64_t tris) { return tris < 700000 ? 1u : tris < 7000000 ? 2u : 4u; }
+// 10 M 99 / 64 / 56.  A launch that is asked to look for strips (CURAST_FLAG_SINGLE_STRIPS) takes strips of 4.
+uint32_t default_single_tpt(const curast_options& o, uint64_t tris)
+{
+    return uses_strips(o, 2, 4) ? 4u : tris < 700000 ? 1u : tris < 7000000 ? 2u : 4u;
+}
 
 // Triangles per pixel from which the single-draw launch reads the stored key before each atomic.  The
 // read saves atomics at the memory side, which counts only where the launch streams far more
@@ -771,7 +774,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
                 else P.spheres = true;
             }
     }
-    P.tpt_single = auto_tpt ? default_single_tpt(single_tris) : o.s1_tris_per_thread;
+    P.tpt_single = auto_tpt ? default_single_tpt(o, single_tris) : o.s1_tris_per_thread;
     P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
     P.tpt_multi = user.s1_multi_tris_per_thread ? o.s1_multi_tris_per_thread : 4u;
     // triangles per work item of the two launches (the strip and vertex-sharing kernels run 64-lane
