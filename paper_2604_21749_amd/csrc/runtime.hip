@@ -85,10 +85,12 @@ struct Staging {
 
 enum class HostSide { kNone, kNext, kFixed };
 
+// The captured launches of a batched frame, without and with strip spheres: which of the two a frame
+// replays follows its cameras, everything else in the key the sizes and options.
 struct GraphEntry {
     uint64_t key[11];
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    hipGraph_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t exec[2] = {nullptr, nullptr};
 };
 
 constexpr size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -207,10 +209,11 @@ curast_options resolve_defaults(const curast_options& u, int cus)
 
 void drop_graphs(curast_ctx* ctx)
 {
-    for (auto& g : ctx->graphs) {
-        if (g.exec) hipGraphExecDestroy(g.exec);
-        if (g.graph) hipGraphDestroy(g.graph);
-    }
+    for (auto& g : ctx->graphs)
+        for (int k = 0; k < 2; ++k) {
+            if (g.exec[k]) hipGraphExecDestroy(g.exec[k]);
+            if (g.graph[k]) hipGraphDestroy(g.graph[k]);
+        }
     ctx->graphs.clear();
 }
 
@@ -590,7 +593,7 @@ struct PlanT {
     uint64_t tri_draws = 0;
     uint64_t draws_culled = 0;
     uint64_t total_pixels = 0;
-    uint64_t max_batches = 0;        // without any culling (graph grid bound)
+    uint64_t max_batches = 0;        // without any culling (graph grid)
     uint64_t pair_count = 0;
     bool compressed = false;         // some mesh is compressed
     uint32_t compressed_parts = 0;   // RasterArgs::compressed_parts of this frame's stage-1 parts
@@ -660,10 +663,13 @@ constexpr double kSphereEdge = 0.13;
 // 2.1M triangles 3.95 ms with 64, 3.80 with 128, 3.99 with 256.
 constexpr uint64_t kMinItems = 16384;
 
-// `user`: the options as the caller set them, zeros where the choice is open; `o`: with defaults.
+// `user`: the options as the caller set them, zeros where the choice is open; `o`: with defaults.  `graph`: for a
+// captured graph, whose kernels and grids are chosen from sizes and options alone (as if nothing were culled), so
+// that a camera path replays what its first frame captured.
 template <template <class> class Vec>
 int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options& o, const curast_mesh* meshes,
-               uint32_t M, const curast_view* views, uint32_t n_views, PlanT<Vec>& P, uint8_t* visible = nullptr)
+               uint32_t M, const curast_view* views, uint32_t n_views, PlanT<Vec>& P, uint8_t* visible = nullptr,
+               bool graph = false)
 {
     const bool auto_tpt = !user.s1_tris_per_thread;
     if (M && !meshes) return fail(ctx, CURAST_E_INVALID, "meshes is NULL");
@@ -756,17 +762,15 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     // stage-1 segments: meshes drawn more than once first (their own launch, whose lanes reuse each
     // loaded triangle over many draws), then the rest; mode 3 sends every mesh to the first
     auto shared_mesh = [&](uint32_t m) { return o.s1_mode == 3 || mesh_draw_count[m] >= 2; };
-    uint64_t single_tris = 0, multi_items = 0;
+    uint64_t single_tris = 0;
+    bool multi = false;
     // spheres as the mode says (mode 0 with a given strip length stands for mode 2), or draw by draw
     const bool open_shape = !user.s1_mode && !user.s1_multi_tris_per_thread;
     P.spheres = !open_shape && (o.s1_mode == 0 || o.s1_mode == 2);
     for (uint32_t m = 0; m < M; ++m) {
-        if (!mesh_draw_count[m]) continue;
-        if (!shared_mesh(m)) {
-            single_tris += meshes[m].num_triangles;
-            continue;
-        }
-        multi_items += meshes[m].num_triangles * (uint64_t)mesh_draw_count[m];
+        if (graph || (mesh_draw_count[m] && !shared_mesh(m))) single_tris += meshes[m].num_triangles;
+        if (!mesh_draw_count[m] || !shared_mesh(m)) continue;
+        multi = true;
         if (open_shape)
             for (uint32_t d = 0; d < mesh_draw_count[m]; ++d) {
                 DrawDesc& D = P.draws[mesh_draw_begin[m] + d];
@@ -782,25 +786,33 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     auto multi_batch = [&] {
         return (o.s1_mode == 3 || uses_strips(o, 1, P.tpt_multi) ? 64u : o.s1_block) * P.tpt_multi;
     };
-    auto items = [&](uint32_t per_item) {
+    // work items of the multi-draw launch, of the surviving draws or of `all`
+    auto items = [&](uint32_t per_item, bool all) {
         uint64_t n = 0;
-        for (uint32_t m = 0; m < M; ++m)
-            if (mesh_draw_count[m] && shared_mesh(m))
-                n += (meshes[m].num_triangles + multi_batch() - 1) / multi_batch() *
-                     ((mesh_draw_count[m] + per_item - 1) / per_item);
+        for (uint32_t m = 0; m < M; ++m) {
+            const uint64_t draws = all ? (uint64_t)n_inst(meshes[m]) * n_views : mesh_draw_count[m];
+            if (draws >= (o.s1_mode == 3 ? 1u : 2u))
+                n += (meshes[m].num_triangles + multi_batch() - 1) / multi_batch() * ((draws + per_item - 1) / per_item);
+        }
         return n;
     };
-    uint32_t dpi = o.s1_draws_per_item;
-    if (!user.s1_draws_per_item && multi_items)
-        for (dpi = 128; dpi > 8 && items(dpi) < kMinItems; dpi /= 2) {}
-    if (!user.s1_multi_tris_per_thread && P.tpt_multi == 4 && items(dpi) < kMinItems / 2) P.tpt_multi = 2;
+    auto draws_per_item = [&](bool all) {
+        uint32_t d = o.s1_draws_per_item;
+        if (!user.s1_draws_per_item && (all || multi))
+            for (d = 128; d > 8 && items(d, all) < kMinItems; d /= 2) {}
+        return d;
+    };
+    uint32_t dpi = draws_per_item(graph);
+    const uint32_t dpi_most = dpi;
+    if (!user.s1_multi_tris_per_thread && P.tpt_multi == 4 && items(dpi, graph) < kMinItems / 2) P.tpt_multi = 2;
+    if (graph) dpi = draws_per_item(false);   // read from the frame's header, not part of the graph
     const uint32_t bt_multi = multi_batch();
     const uint32_t bt = (uses_strips(o, 2, P.tpt_single) ? 64u : o.s1_block) * P.tpt_single;
     for (uint32_t m = 0; m < M; ++m)
         if (meshes[m].num_triangles) {
             const uint64_t all = (uint64_t)n_inst(meshes[m]) * n_views;
             P.max_batches += (meshes[m].num_triangles + std::min(bt, bt_multi) - 1) / std::min(bt, bt_multi) *
-                             ((all + dpi - 1) / dpi);
+                             ((all + dpi_most - 1) / dpi_most);
         }
     for (int pass = 0; pass < 2; ++pass) {
         bool any_cmp = false, all_cmp = true;
@@ -902,6 +914,12 @@ TimedFrame* begin_timing(curast_ctx* ctx)
     return &ctx->timed.back();
 }
 
+// Most workgroups of a stage-1 launch.
+uint32_t stage1_grid_cap(const curast_ctx* ctx)
+{
+    return (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * ctx->opt.s1_blocks_per_cu, 1ull << 24);
+}
+
 uint32_t clear_grid(const curast_ctx* ctx, uint64_t total_pixels)
 {
     const uint64_t pairs = (total_pixels + 1) / 2;
@@ -955,7 +973,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
         // items: a workgroup's set-up is then shared by several items, and the dispatcher
         // launches fewer workgroups (one per item measured slower on the HBM-bound launch)
         const uint32_t mode = ctx->opt.s1_mode, blk = ctx->opt.s1_block;
-        const uint32_t grid_cap = (uint32_t)std::min<uint64_t>((uint64_t)cus * ctx->opt.s1_blocks_per_cu, 1ull << 24);
+        const uint32_t grid_cap = stage1_grid_cap(ctx);
         // a fragment is written by the atomic alone, without reading the stored key first (a memory
         // round trip per fragment), except in dense single-draw launches (kReadFirstDensity)
         auto launch_part = [&](uint32_t part, uint32_t tpt, uint32_t grid, hipStream_t st) {
@@ -1024,7 +1042,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     if (!ctx) return CURAST_E_INVALID;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     Plan P;
-    int rc = build_plan(ctx, ctx->user, ctx->opt, meshes, M, views, n_views, P);
+    int rc = build_plan(ctx, ctx->user, ctx->opt, meshes, M, views, n_views, P, nullptr, use_graph);
     if (rc) return rc;
     rc = ensure_queues(ctx);
     if (rc) return rc;
@@ -1063,12 +1081,12 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
         };
         return launch_frame(ctx, a, P, clear, grid_for(P.hdr.total_batches - shared), shared ? grid_for(shared) : 0, s, tf);
     }
-    // graph path: one captured sequence per structure (sizes of the descriptor block, grid bound,
+    // graph path: one captured sequence per structure (sizes of the descriptor block, grid,
     // options); replays copy the new descriptor contents from the same pinned buffer
-    const uint32_t grid1 = grid_for(P.max_batches);
+    const uint32_t grid1 = std::min(grid_for(P.max_batches), stage1_grid_cap(ctx));
     // the queue capacities are kernel arguments of the captured launches, so they are part of the key
     uint64_t key[11] = {(uint64_t)M, (uint64_t)n_views, (uint64_t)P.max_bytes, (uint64_t)grid1,
-                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.spheres << 17) | ((uint64_t)P.read_first << 16) |
+                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.read_first << 16) |
                            (P.tpt_single << 8) | (P.tpt_multi << 4) | ctx->opt.s1_mode,
                        ((uint64_t)ctx->opt.s2_waves << 32) | ctx->opt.s3_blocks,
                        ((uint64_t)ctx->opt.flags << 32) | ctx->opt.small_px,
@@ -1082,11 +1100,16 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     if (!ge) {
         GraphEntry g;
         std::memcpy(g.key, key, sizeof key);
+        ctx->graphs.push_back(g);
+        ge = &ctx->graphs.back();
+    }
+    auto capture = [&](int k) -> int {
         HIP_TRY(ctx, hipStreamBeginCapture(ctx->capture_stream, hipStreamCaptureModeThreadLocal));
         hipError_t e = hipMemcpyAsync(ctx->raster_stage.dev, ctx->raster_stage.host->p, P.max_bytes, hipMemcpyHostToDevice,
                                       ctx->capture_stream);
         const RasterArgs a = make_args(ctx, P);
         auto clear = [&] { return launch_clear(a, clear_grid(ctx, P.total_pixels), ctx->capture_stream); };
+        P.spheres = k != 0;
         int lrc = e == hipSuccess ? launch_frame(ctx, a, P, clear, grid1, grid1, ctx->capture_stream, nullptr)
                                   : hip_fail(ctx, e, "capture memcpy");
         hipGraph_t graph = nullptr;
@@ -1096,24 +1119,32 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
             return lrc;
         }
         if (e2 != hipSuccess) return hip_fail(ctx, e2, "hipStreamEndCapture");
-        g.graph = graph;
-        e = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0);
+        e = hipGraphInstantiate(&ge->exec[k], graph, nullptr, nullptr, 0);
         if (e != hipSuccess) {
+            ge->exec[k] = nullptr;
             hipGraphDestroy(graph);
             return hip_fail(ctx, e, "hipGraphInstantiate");
         }
-        ctx->graphs.push_back(g);
+        ge->graph[k] = graph;
         log_line("captured a frame graph (%zu held by the context)", ctx->graphs.size());
-        ge = &ctx->graphs.back();
+        return CURAST_OK;
+    };
+    const int variant = P.spheres ? 1 : 0;
+    if (!ge->exec[variant]) {
+        rc = capture(variant);
+        if (rc) return rc;
     }
     if (tf) HIP_TRY(ctx, hipEventRecord(tf->ev[0], s));
-    HIP_TRY(ctx, hipGraphLaunch(ge->exec, s));
+    HIP_TRY(ctx, hipGraphLaunch(ge->exec[variant], s));
     rc = staging_used(ctx, ctx->raster_stage, s);
     if (rc) return rc;
     if (tf) {
         HIP_TRY(ctx, hipEventRecord(tf->ev[kNumSlots], s));
         tf->used[kTFrame] = 1;
     }
+    // the other variant while the device runs this one, so that no later frame of the path captures
+    const bool open_shape = !ctx->user.s1_mode && !ctx->user.s1_multi_tris_per_thread;
+    if (open_shape && !ge->exec[1 - variant]) (void)capture(1 - variant);
     return CURAST_OK;
 }
 
