@@ -1786,77 +1786,129 @@ __global__ void __launch_bounds__(256) stage3_kernel(RasterArgs a)
 
 // ----------------------------------------------------------------------------------------------
 // Stage 3 binned by screen tile.  Stage 2 linked the parts of every 64x64 tile (a list head per
-// tile) and listed the tiles that have any, so one launch is enough: a workgroup takes a quarter of
-// a listed tile (16 rows) and walks all parts of its list.  Lane l owns the 4 pixels (l % 64,
-// l / 64 + 4k) of the quarter and keeps their running minimum keys in registers, so the parts of one
+// tile) and listed the tiles that have any, so one launch is enough: a workgroup takes a tile, or a
+// quarter of it (16 rows), and walks all parts of its list.  Lane l owns the pixels (l % 64, l / 64 + 4k) of
+// its share and keeps their running minimum keys in registers, so the parts of one
 // tile need no atomics among themselves and the tile costs one global 64-bit atomic minimum per
-// covered pixel however many large triangles overlap it.  The next part's record is loaded while
-// the current one is rasterized.  Latency bounds it on small views (a 512x512 ground plane has 64
-// tiles, fewer than compute units): whole tiles of 16 pixels per lane took 15.4 us there,
-// quarters take 7.6, and the scan and scatter launches that grouped the parts before cost 7-9 us in
-// every frame.
+// covered pixel however many large triangles overlap it.  The list is followed two parts ahead: the record
+// of the next part and the link of the one after it load while the current one is rasterized.
+//
+// Vector instructions bound it where lists are long (a part costs a lane about 165 and 68 per pixel), latency
+// where they are short.  Few tiles are taken in quarters, or most compute units would idle (a 512x512 view of
+// 64 tiles and one ground quad 15.4 us in whole tiles, 7.6 in quarters; 192 tiles with 1900 triangles that cover
+// them 5.6 and 3.8 ms); quarters that would need a fourth round of the grid lose to whole tiles, which set each
+// part up once instead of four times (375 tiles 7.5 ms either way, 400 tiles 7.7 and 9.0, 510 tiles 6.9 and 11.1).
+// Whole tiles are taken in screen order, not in that of the list (510 tiles 7.1 and 7.9 ms; 2040 tiles with 3000
+// triangles of 350 tiles each 5.6 and 9.0).
 // ----------------------------------------------------------------------------------------------
-constexpr uint32_t kTileParts = 4;                    // workgroups' shares of a tile
-constexpr int kShareRows = kTileSize / (int)kTileParts;
-constexpr int kSharePixels = kShareRows / 4;          // per lane of a 256-lane workgroup
+template <bool STATS, int SHARES>
+__device__ __forceinline__ void stage3_share(const RasterArgs& a, const ViewDesc* __restrict__ d_views, uint32_t t,
+                                             uint32_t head, uint32_t share, StatAcc<STATS>& st)
+{
+    constexpr int kShareRows = kTileSize / SHARES;
+    constexpr int kSharePixels = kShareRows / 4;      // per lane of a 256-lane workgroup
+    const bool early_out = !(a.flags & kFlagNoEarlyOut);
+    const int32_t col = threadIdx.x & 63;
+    const int32_t row0 = threadIdx.x >> 6;
+    // a record as one word per lane: read where it is used, not as soon as it is loaded
+    static_assert(sizeof(LargeTri) == 48, "12 words");
+    auto load_record = [&](uint32_t rec) {
+        return gl(reinterpret_cast<const uint32_t*>(a.large + rec))[lane_id() < 12 ? lane_id() : 0];
+    };
+    auto record = [](uint32_t words) {
+        auto word = [&](int k) { return __builtin_amdgcn_readlane(words, k); };
+        LargeTri r;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            r.X[k] = (int32_t)word(k);
+            r.Y[k] = (int32_t)word(3 + k);
+            r.zI[k] = __uint_as_float(word(6 + k));
+        }
+        r.view = word(9);
+        r.id = (uint64_t)word(11) << 32 | word(10);
+        return r;
+    };
+    uint32_t next = a.q3_next[head];
+    uint32_t words = load_record(a.q3[head].rec);
+    // the part after the current one: its record's index, and the part after it (of the head once the
+    // list has ended, so that every load is in range)
+    uint32_t at = next == kNoPart ? head : next;
+    uint32_t rec = a.q3[at].rec, after = a.q3_next[at];
+    const ViewDesc V = d_views[record(words).view];
+    const uint32_t ntx = (uint32_t)(V.W + kTileSize - 1) / kTileSize;
+    const uint32_t local = t - V.tile_base;
+    const int32_t px = (int32_t)(local % ntx) * kTileSize + col;
+    const int32_t y_first = (int32_t)(local / ntx) * kTileSize + (int32_t)share * kShareRows;
+    const int32_t py0 = y_first + row0;
+    unsigned long long best[kSharePixels];
+#pragma unroll
+    for (int k = 0; k < kSharePixels; ++k) best[k] = kEmptyKey;
+    while (true) {
+        const LargeTri cur = record(words);
+        const bool last = next == kNoPart;
+        words = load_record(rec);
+        next = after;
+        at = next == kNoPart ? head : next;
+        rec = a.q3[at].rec;
+        after = a.q3_next[at];
+        Tri64 tri;
+        if (setup_tri64(cur.X, cur.Y, cur.zI, V.W, V.H, tri) && tri.py0 < y_first + kShareRows &&
+            tri.py1 >= y_first && px >= tri.px0 && px <= tri.px1) {
+            // edge values at (px, py0), stepped by four rows
+            int64_t e[3];
+            const int64_t step[3] = {(int64_t)tri.dx[0] * 1024, (int64_t)tri.dx[1] * 1024,
+                                     (int64_t)tri.dx[2] * 1024};
+#pragma unroll
+            for (int k = 0; k < 3; ++k) e[k] = edge64(tri, k, px, py0);
+            const float area_f = (float)tri.area;
+#pragma unroll
+            for (int k = 0; k < kSharePixels; ++k) {
+                const int32_t py = py0 + 4 * k;
+                if (py >= tri.py0 && py <= tri.py1 &&
+                    ((e[0] + tri.bias[0]) | (e[1] + tri.bias[1]) | (e[2] + tri.bias[2])) >= 0) {
+                    const float depth = frag_depth((float)e[0], (float)e[1], (float)e[2], tri.zI, area_f);
+                    const unsigned long long key = make_key(depth, cur.id);
+                    best[k] = key < best[k] ? key : best[k];
+                    st.add(kStFragments);
+                }
+                e[0] += step[0];
+                e[1] += step[1];
+                e[2] += step[2];
+            }
+        }
+        if (last) break;
+    }
+#pragma unroll
+    for (int k = 0; k < kSharePixels; ++k) {
+        const int32_t py = py0 + 4 * k;
+        if (best[k] != kEmptyKey && px < V.W && py < V.H)
+            write_fragment(V.vis + (size_t)py * (size_t)V.W + (size_t)px, best[k], early_out);
+    }
+}
 
 template <bool STATS>
 __global__ void __launch_bounds__(256) stage3_tile_kernel(RasterArgs a, const ViewDesc* __restrict__ d_views)
 {
-    const uint32_t n = (uint32_t)a.counters[kCntTiles] * kTileParts;
-    const bool early_out = !(a.flags & kFlagNoEarlyOut);
-    const int32_t col = threadIdx.x & 63;
-    const int32_t row0 = threadIdx.x >> 6;
+    const uint32_t n = (uint32_t)a.counters[kCntTiles];
     StatAcc<STATS> st;
-    for (uint32_t item = blockIdx.x; item < n; item += gridDim.x) {
-        const uint32_t t = a.tile_list[item / kTileParts];
-        uint32_t part = a.tile_head[t];
-        LargeTri r = a.large[a.q3[part].rec];
-        const ViewDesc V = d_views[r.view];
-        const uint32_t ntx = (uint32_t)(V.W + kTileSize - 1) / kTileSize;
-        const uint32_t local = t - V.tile_base;
-        const int32_t px = (int32_t)(local % ntx) * kTileSize + col;
-        const int32_t y_first = (int32_t)(local / ntx) * kTileSize + (int32_t)(item % kTileParts) * kShareRows;
-        const int32_t py0 = y_first + row0;
-        unsigned long long best[kSharePixels];
-#pragma unroll
-        for (int k = 0; k < kSharePixels; ++k) best[k] = kEmptyKey;
-        while (true) {
-            const LargeTri cur = r;
-            part = a.q3_next[part];
-            if (part != kNoPart) r = a.large[a.q3[part].rec];
-            Tri64 tri;
-            if (setup_tri64(cur.X, cur.Y, cur.zI, V.W, V.H, tri) && tri.py0 < y_first + kShareRows &&
-                tri.py1 >= y_first && px >= tri.px0 && px <= tri.px1) {
-                // edge values at (px, py0), stepped by four rows
-                int64_t e[3];
-                const int64_t step[3] = {(int64_t)tri.dx[0] * 1024, (int64_t)tri.dx[1] * 1024,
-                                         (int64_t)tri.dx[2] * 1024};
-#pragma unroll
-                for (int k = 0; k < 3; ++k) e[k] = edge64(tri, k, px, py0);
-                const float area_f = (float)tri.area;
-#pragma unroll
-                for (int k = 0; k < kSharePixels; ++k) {
-                    const int32_t py = py0 + 4 * k;
-                    if (py >= tri.py0 && py <= tri.py1 &&
-                        ((e[0] + tri.bias[0]) | (e[1] + tri.bias[1]) | (e[2] + tri.bias[2])) >= 0) {
-                        const float depth = frag_depth((float)e[0], (float)e[1], (float)e[2], tri.zI, area_f);
-                        const unsigned long long key = make_key(depth, cur.id);
-                        best[k] = key < best[k] ? key : best[k];
-                        st.add(kStFragments);
-                    }
-                    e[0] += step[0];
-                    e[1] += step[1];
-                    e[2] += step[2];
-                }
-            }
-            if (part == kNoPart) break;
+    if (n * 4 <= gridDim.x * 3) {
+        for (uint32_t item = blockIdx.x; item < n * 4; item += gridDim.x) {
+            const uint32_t t = a.tile_list[item / 4];
+            stage3_share<STATS, 4>(a, d_views, t, a.tile_head[t], item % 4, st);
         }
-#pragma unroll
-        for (int k = 0; k < kSharePixels; ++k) {
-            const int32_t py = py0 + 4 * k;
-            if (best[k] != kEmptyKey && px < V.W && py < V.H)
-                write_fragment(V.vis + (size_t)py * (size_t)V.W + (size_t)px, best[k], early_out);
+    } else {
+        // tiles blockIdx, blockIdx + gridDim, ...: the heads of 64 of them at a time, one per lane
+        const uint32_t n_tiles = a.hdr->n_tiles;
+        for (uint64_t base = blockIdx.x; base < n_tiles; base += 64ull * gridDim.x) {
+            const uint64_t mine = base + (uint64_t)lane_id() * gridDim.x;
+            const uint32_t heads = mine < n_tiles ? a.tile_head[mine] : kNoPart;
+            unsigned long long some = __ballot(heads != kNoPart);
+            while (some) {
+                const uint32_t j = (uint32_t)__builtin_ctzll(some);
+                some &= some - 1;
+                stage3_share<STATS, 1>(a, d_views, (uint32_t)(base + (uint64_t)j * gridDim.x),
+                                       __builtin_amdgcn_readlane(heads, j), 0, st);
+            }
         }
     }
     st.flush(a.stats);
