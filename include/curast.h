@@ -93,7 +93,8 @@ typedef enum {
 #define CURAST_FLAG_EARLY_OUT_ALL 0x800u /* read the stored key before each atomic minimum and skip the
                                             atomic when the key is not smaller, in every stage; by
                                             default only the stage-1 launch over single-draw meshes
-                                            does, and only with 32 or more triangles per pixel, while
+                                            does, and only with 32 or more triangles per pixel or for
+                                            triangles that one stored depth shows to be covered, while
                                             everything else issues the atomic directly as the paper
                                             does (Sec. 4.1), which measured faster there;
                                             CURAST_FLAG_NO_EARLY_OUT, when also set, wins (no stage

@@ -22,6 +22,8 @@ constexpr uint32_t kNoPart = 0xFFFFFFFFu;         // end of a tile's list of sta
 // x and y: every edge-function value at a pixel centre of the box (and one step past it) then
 // fits in int32 (|E| <= 2 * ext * (ext + 384) < 2^31).
 constexpr int32_t kSmallExtent = 32768 - 512;
+// Twice-areas in 1/256 px squared of the rule that raster_small explains: 1.5 and 6 px.
+constexpr int32_t kSampleArea = 3 << 16, kReadArea = 12 << 16, kNeverSample = 0x7FFFFFFF;
 
 struct FrameHeader {              // 48 B
     uint64_t total_batches;       // stage-1 work items over all segments
@@ -154,6 +156,8 @@ struct RasterArgs {
     uint32_t flags;
     uint32_t s1_mode;             // 0 auto (= 2), 1 exact only, 2 fast reject (strip spheres in the
                                   // multi-draw launch), 3 vertex sharing for every mesh, 4 as 2 without spheres
+    int32_t sample_area;          // stage 1: a triangle's twice-area, in 1/256 px squared, from which its lane samples
+                                  // the stored depth to decide whether to read before its atomics
     uint32_t part;                // stage-1 work items: 0 all, 1 the shared prefix, 2 the rest
     uint32_t* tile_head;          // [n_tiles] last part linked to each tile (kNoPart: none; clear kernel)
     uint32_t* tile_list;          // [n_tiles] the tiles that have parts, kCntTiles of them

@@ -134,10 +134,25 @@ __device__ __forceinline__ ViewDesc draw_view(const DrawDesc& D)
 
 // One lane rasterizes a small triangle over its bounding box (Sec. 4.1): y outer, x inner,
 // incremental int32 edge values (see kSmallExtent for the range argument).
+//
+// Atomics alone are the faster way to write a fragment until many layers lie over one another: then most
+// of them change nothing, and reading first saves them.  So the lane of a triangle of some size reads one stored
+// depth, in the middle of the box: if that is nearer than all of the triangle (for one of 6 px and more: if the
+// pixel holds anything) it reads before each atomic.  Smaller triangles have too few fragments to gain.
+// Stage 1 with grids of 3 px triangles, alone / always reading / sampled: one layer 24.9 / 29.1 / 25.3 us, 40 layers
+// front to back 600 / 229 / 239, back to front 594 / 440 / 341; of 0.8 px, 40 layers, 496 / 506 and 498 / 714.
+// Of 12 px: one layer 31.0 / 37.9 / 31.4, 40 layers 923 / 286 / 289 and 905 / 491 / 530.
 template <bool STATS>
 __device__ __forceinline__ void raster_small(const SmallTri& s, uint64_t id, const ViewDesc& V, bool early_out,
-                                             StatAcc<STATS>& st)
+                                             int32_t sample_area, StatAcc<STATS>& st)
 {
+    if (!early_out && s.area >= sample_area) {
+        // the depth stored in the middle of the box (NaN of an empty pixel) against the nearest vertex
+        const unsigned long long key =
+            gl(V.vis)[(size_t)((s.py0 + s.py1) >> 1) * (size_t)V.W + (size_t)((s.px0 + s.px1) >> 1)];
+        const float behind = __uint_as_float((uint32_t)(key >> 36) << 3) * fmaxf(s.zI[0], fmaxf(s.zI[1], s.zI[2]));
+        early_out = s.area >= kReadArea ? !__builtin_isnan(behind) : behind < 1.0f;
+    }
     int32_t sdx[3], sdy[3], row[3], bias[3];
     const int32_t Px0 = 256 * s.px0 + 128, Py0 = 256 * s.py0 + 128;
 #pragma unroll
@@ -402,7 +417,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_kernel(RasterArgs a, CURAST_DESC
                 }
                 if (route == kRouteSmall) {
                     st.add(kStS1Raster);
-                    raster_small<STATS>(s, D.id_base + t, V, early_out, st);
+                    raster_small<STATS>(s, D.id_base + t, V, early_out, a.sample_area, st);
                 }
             }
         }
@@ -565,7 +580,7 @@ __device__ __forceinline__ void exact_route(const RasterArgs& a, bool have, cons
     }
     if (route == kRouteSmall) {
         st.add(kStS1Raster);
-        raster_small<STATS>(s, idb + tt, V, early_out, st);
+        raster_small<STATS>(s, idb + tt, V, early_out, a.sample_area, st);
     }
 }
 

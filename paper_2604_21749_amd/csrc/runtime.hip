@@ -975,12 +975,14 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
         const uint32_t mode = ctx->opt.s1_mode, blk = ctx->opt.s1_block;
         const uint32_t grid_cap = stage1_grid_cap(ctx);
         // a fragment is written by the atomic alone, without reading the stored key first (a memory
-        // round trip per fragment), except in dense single-draw launches (kReadFirstDensity)
+        // round trip per fragment), except in dense single-draw launches (kReadFirstDensity) and where a lane
+        // of the single-draw launch finds its triangle covered (kSampleArea)
         auto launch_part = [&](uint32_t part, uint32_t tpt, uint32_t grid, hipStream_t st) {
             grid = std::min(grid, grid_cap);
             RasterArgs a1 = a;
             a1.part = part;
             if (part == 1 || !P.read_first) a1.flags |= atomic_alone;
+            a1.sample_area = part == 2 && !(a.flags & kFlagNoEarlyOut) ? kSampleArea : kNeverSample;
             if (part == 1 && mode == 3) return launch_stage1_share(a1, tpt, stats, grid, st);
             if (mode == 1) return launch_stage1(a1, blk, tpt, stats, grid, st);
             if (!uses_strips(ctx->opt, part, tpt)) return launch_stage1_fast(a1, blk, tpt, stats, grid, st);
