@@ -568,9 +568,9 @@ __global__ void __launch_bounds__(256) resolve_screen_kernel(ScreenArgs a)
 // side, one request per 64-byte sector and instruction, about 16 G requests/s: that rate bounds the
 // kernels, not the bytes.  So a workgroup adds the contributions of its 16 x 16 pixel tile in LDS first,
 // one table row (C attribute and 3 position components) per vertex, and then issues one atomic per
-// touched row and component, neighbouring lanes on neighbouring components and rows.  Vertices hash to
-// their low bits, so that the rows of neighbouring vertices, which share sectors, stay neighbours in
-// the table.  1.85 M requests (2.25 M with one staged row per pixel and vertex) for 0.46 M pixels of a
+// touched row and component, neighbouring lanes on neighbouring components and rows.  A vertex's row is
+// its low bits where it can be, so that the rows of neighbouring vertices, which share sectors, stay neighbours
+// in the table.  1.85 M requests (2.25 M with one staged row per pixel and vertex) for 0.46 M pixels of a
 // 10M-triangle mesh take 105 us, 143 before; 0.2 M pixels of coarser meshes, 4 channels and positions,
 // 269 us with an atomic per value and 57 here.
 constexpr uint32_t kBwdSlots = 1024;           // at most 3 x 256 vertices per tile: never full
@@ -627,19 +627,43 @@ __device__ __forceinline__ void bwd_pos(const BwdTerms& t, const double (&G)[3],
     }
 }
 
-// Table row of a vertex, inserted when it is new (`first`).  Colliding vertices step by an odd distance
-// taken from their high bits.
+// Table rows of a pixel's three vertices, inserted where they are new (`first`).  A vertex's row is the low bits
+// of its index; if that is taken, a row among those of its group of 16 vertices, which the group's hash places; from
+// there on odd steps, which reach every row.  Low bits alone, with the steps right after them, made the rows of a
+// lat-long sphere's tile share an eighth of the table wherever a row of the mesh has 2^k + 1 vertices (4.2 M triangles,
+// 130 K pixels, 3 channels and positions 46 us, 28 with the groups; 16.8 M triangles 94 and 48); hashed groups
+// alone cost a mesh of rows that do not collide their neighbourhood (train step of a 10M-triangle scan 290 us, 279
+// with the low bits first).  The three are probed together, a placed one again at its own row, so that a round
+// costs one LDS round trip instead of three.
 template <class Key>
-__device__ __forceinline__ uint32_t bwd_slot(Key* keys, Key key, uint32_t v, bool& first)
+__device__ __forceinline__ void bwd_slots(Key* keys, const Key (&key)[3], const uint32_t (&v)[3], uint32_t (&slot)[3],
+                                          bool (&first)[3])
 {
-    uint32_t h = v & (kBwdSlots - 1);
-    const uint32_t step = ((v / kBwdSlots) * 2654435761u >> 20) | 1u;
-    while (true) {
-        const Key prev = atomicCAS(keys + h, (Key)~(Key)0, key);
-        first = prev == (Key)~(Key)0;
-        if (first || prev == key) return h;
-        h = (h + step) & (kBwdSlots - 1);
+    constexpr Key kFree = (Key)~(Key)0;
+    uint32_t move[3], step[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t h = (v[k] >> 4) * 2654435761u;
+        slot[k] = v[k] & (kBwdSlots - 1);
+        move[k] = ((h >> 26) << 4 | (v[k] & 15)) - slot[k];
+        step[k] = (h >> 13) | 1u;
+        first[k] = false;
     }
+    bool more;
+    do {
+        Key prev[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) prev[k] = atomicCAS(keys + slot[k], kFree, key[k]);
+        more = false;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const bool other = prev[k] != kFree && prev[k] != key[k];
+            first[k] |= prev[k] == kFree;
+            slot[k] = other ? (slot[k] + move[k]) & (kBwdSlots - 1) : slot[k];
+            move[k] = other ? step[k] : move[k];
+            more |= other;
+        }
+    } while (more);
 }
 
 // A pixel's upstream gradient and the attribute rows of its three vertices, G channels from c0 on,
@@ -752,8 +776,7 @@ __global__ void __launch_bounds__(256) resolve_backward_kernel(ScreenArgs a)
         BwdChannels<CC, POS> ch;
         ch.load(rows, grad, 0, C);
         px.pos = true;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) px.slot[k] = bwd_slot(keys, vi[k], vi[k], px.first[k]);
+        bwd_slots(keys, vi, vi, px.slot, px.first);
         BwdTerms t;
         bwd_terms(sx, sy, w, x, y, t);
         px.store(t, rows, grad, C, ch, val);
@@ -805,9 +828,14 @@ __global__ void __launch_bounds__(256) resolve_backward_meshes_kernel(ResolveBlo
         BwdChannels<CC, POS> ch;
         ch.load(rows, grad, 0, C);
         px.pos = POS && a.grad_pos[m] != nullptr;
+        unsigned long long key[3];
+        uint32_t hash[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            px.slot[k] = bwd_slot(keys, (unsigned long long)m << 32 | vi[k], vi[k] + m * 0x9E3779B9u, px.first[k]);
+        for (int k = 0; k < 3; ++k) {
+            key[k] = (unsigned long long)m << 32 | vi[k];
+            hash[k] = vi[k] + m * 0x9E3779B9u;
+        }
+        bwd_slots(keys, key, hash, px.slot, px.first);
         BwdTerms t;
         bwd_terms(sx, sy, w, x, y, t);
         px.store(t, rows, grad, C, ch, val);
