@@ -153,6 +153,7 @@ struct RasterArgs {
     unsigned long long* stats;
     uint32_t q2_cap, large_cap, q3_cap;
     uint32_t small_px, medium_px;
+    uint32_t s2_blocks;           // workgroups that walk the stage-2 queue
     uint32_t flags;
     uint32_t s1_mode;             // 0 auto (= 2), 1 exact only, 2 fast reject (strip spheres in the
                                   // multi-draw launch), 3 vertex sharing for every mesh, 4 as 2 without spheres

@@ -1641,7 +1641,10 @@ template <bool STATS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))   // what its LDS allows
 stage2_kernel(RasterArgs a, CURAST_DESC_PARAMS)
 {
+    // the grid is that of the overflow pass where that is the larger one; the queue is walked by
+    // the first s2_blocks workgroups, as many as the option says
     if (a.counters[kCntQ2] > a.q2_cap) stage1_overflow(a, d_hdr, d_views, d_meshes, d_segs, d_draws);
+    if (blockIdx.x >= a.s2_blocks) return;
     // Each wavefront takes up to 64 queue entries at a time.  Every lane sets up one of them
     // (descriptor, index and vertex loads, transform, clip, snap: 64 dependent load chains in flight
     // at once) and leaves the snapped polygon in LDS; then the whole wavefront rasterizes the
@@ -1651,7 +1654,7 @@ stage2_kernel(RasterArgs a, CURAST_DESC_PARAMS)
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wslot = threadIdx.x >> 6;
     const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t nwaves = min(gridDim.x, a.s2_blocks) * (blockDim.x >> 6);
     const unsigned long long n = min(a.counters[kCntQ2], (unsigned long long)a.q2_cap);
     const bool early_out = !(a.flags & kFlagNoEarlyOut);
     StatAcc<STATS> st;
