@@ -44,7 +44,7 @@ struct ViewDesc {                 // 48 B
     float near_plane;
     uint32_t tile_base;           // first stage-3 tile of this view; its tiles are row-major
     float wmax, hmax;             // W - 1, H - 1 (exact)
-    float reach;                  // on the device only: DrawDesc::reach of the current draw
+    float reach;                  // DrawDesc::reach of the view's general draws (on the device: of the current draw)
     uint32_t pad;
 };
 

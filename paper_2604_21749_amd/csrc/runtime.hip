@@ -351,6 +351,7 @@ bool sphere_outside(const float A[12], const float bs[4], float near_plane)
     const double cx = bs[0], cy = bs[1], cz = bs[2], r = bs[3];
     auto test = [&](const double* pl) {
         const double v = pl[0] * cx + pl[1] * cy + pl[2] * cz + pl[3];
+        if (v >= 0.0) return false;   // the centre is inside: no root needed
         const double g = std::sqrt(pl[0] * pl[0] + pl[1] * pl[1] + pl[2] * pl[2]);
         const double mag = std::fabs(pl[0] * cx) + std::fabs(pl[1] * cy) + std::fabs(pl[2] * cz) + std::fabs(pl[3]) + r * g;
         return v + r * g + 1e-4 * mag < 0.0;
@@ -387,6 +388,16 @@ bool sphere_interior(const float A[12], const float bs[4], float near_plane)
         lo = v - r * g - slack;
         hi = v + r * g + slack;
     };
+    // whether the lower end of the same range is positive, without its root
+    auto positive = [&](const double* pl) {
+        double v = 0.0, mag = 0.0;
+        for (int k = 0; k < 4; ++k) {
+            v += pl[k] * c[k];
+            mag += std::fabs(pl[k] * c[k]);
+        }
+        const double rest = v - 1e-4 * mag, rg = r * 1.0001;
+        return rest > 0.0 && rest * rest > rg * rg * (pl[0] * pl[0] + pl[1] * pl[1] + pl[2] * pl[2]);
+    };
     double x[4], y[4], w[4], pl[4], lo, hi;
     for (int k = 0; k < 4; ++k) {
         x[k] = A[k];
@@ -396,22 +407,29 @@ bool sphere_interior(const float A[12], const float bs[4], float near_plane)
     range(w, lo, hi);
     if (!(lo >= 1.001 * (double)near_plane) || !(hi < 1e29)) return false;
     for (int k = 0; k < 4; ++k) pl[k] = 1.99 * w[k] - x[k];
-    range(pl, lo, hi);
-    if (!(lo > 0.0)) return false;
+    if (!positive(pl)) return false;
     for (int k = 0; k < 4; ++k) pl[k] = 1.99 * w[k] + x[k];
-    range(pl, lo, hi);
-    if (!(lo > 0.0)) return false;
+    if (!positive(pl)) return false;
     for (int k = 0; k < 4; ++k) pl[k] = 1.99 * w[k] - y[k];
-    range(pl, lo, hi);
-    if (!(lo > 0.0)) return false;
+    if (!positive(pl)) return false;
     for (int k = 0; k < 4; ++k) pl[k] = 1.99 * w[k] + y[k];
-    range(pl, lo, hi);
-    return lo > 0.0;
+    return positive(pl);
+}
+
+// The next binary32 above a positive finite one.  (A library call each for this
+// and for the powers of two below took a tenth of a draw's time on the host.)
+float next_up(float x)
+{
+    uint32_t u;
+    std::memcpy(&u, &x, sizeof u);
+    ++u;
+    std::memcpy(&x, &u, sizeof x);
+    return x;
 }
 
 // DrawDesc::reach from a bound m on the distance between fast and snapped window positions: m + 1/2,
 // rounded up (1 - reach, the other side's constant in the kernels, is then exact in binary32).
-float reach_of(double m) { return std::nextafter((float)(0.5 + m), 1.0f); }
+float reach_of(double m) { return next_up((float)(0.5 + m)); }
 
 // The same for draws that take the general fast path: the reciprocal and the two roundings after it
 // differ from the exact path by at most 1.625 h 2^-20 px (|x|, |y| <= 2w, h half the larger side);
@@ -419,7 +437,7 @@ float reach_of(double m) { return std::nextafter((float)(0.5 + m), 1.0f); }
 float general_reach(int32_t width, int32_t height)
 {
     const double h = 0.5 * std::max(width, height);
-    return reach_of(1.01 * (1.625 * std::ldexp(h, -20) + std::ldexp(3.0 * h + 1.0, -23)) + std::ldexp(1.0, -9));
+    return reach_of(1.01 * (1.625 * (h * 0x1p-20) + (3.0 * h + 1.0) * 0x1p-23) + 0x1p-9);
 }
 
 // Largest and mean scale over a mesh's bounding sphere may differ by this factor for the strip spheres to use
@@ -435,7 +453,7 @@ constexpr double kLooseScale = 1.5;
 bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, float R[8], float* scale, float* grow,
                     float* reach)
 {
-    const double u = std::ldexp(1.0, -24);
+    constexpr double u = 0x1p-24;
     const double c[3] = {bs[0], bs[1], bs[2]}, r = bs[3];
     auto S = [&](int row) {
         double s = std::fabs((double)A[4 * row + 3]);
@@ -451,12 +469,13 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
     g = std::sqrt(g);
     const double w_lo = w_c - (r * g + 1e-4 * (mag + r * g));
     if (!(w_lo > 0.0)) return false;
-    const double sx = S(0), sy = S(1), sw = S(2);
+    const double sx = S(0), sy = S(1), sw = S(2), per_w = 1.0 / w_lo;
     auto bound = [&](double h, double s_row) {
-        return 1.01 * (h * u * ((7.0 * s_row + 19.0 * sw) / w_lo + 16.0) + (3.0 * h + 1.0) * u) + std::ldexp(1.0, -9);
+        return 1.01 * (h * u * ((7.0 * s_row + 19.0 * sw) * per_w + 16.0) + (3.0 * h + 1.0) * u) + 0x1p-9;
     };
-    if (!(bound(hW, sx) <= 1.0 / 32.0) || !(bound(hH, sy) <= 1.0 / 32.0)) return false;
-    *reach = reach_of(std::max(bound(hW, sx), bound(hH, sy)));
+    const double off_x = bound(hW, sx), off_y = bound(hH, sy);
+    if (!(off_x <= 1.0 / 32.0) || !(off_y <= 1.0 / 32.0)) return false;
+    *reach = reach_of(std::max(off_x, off_y));
     for (int k = 0; k < 4; ++k) {
         R[k] = (float)((double)hW * ((double)A[k] + (double)A[8 + k]));
         R[4 + k] = (float)((double)hH * ((double)A[4 + k] + (double)A[8 + k]));
@@ -467,13 +486,16 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
     // error carried into the radius, and two roundings of box arithmetic at |x| <= 3 hW, and the reach of
     // the draw (the third rounding is in its box arithmetic)
     auto slack_of = [&](double h, double s_row) {
-        return 2.0 * h * u * (3.01 * s_row / w_lo + 12.04 * sw / w_lo + 9.0) + 6.0 * h * u;
+        return 2.0 * h * u * ((3.01 * s_row + 12.04 * sw) * per_w + 9.0) + 6.0 * h * u;
     };
-    *grow = std::nextafter((float)(1.01 * std::max(slack_of(hW, sx), slack_of(hH, sy)) + *reach), INFINITY);
+    *grow = next_up((float)(1.01 * std::max(slack_of(hW, sx), slack_of(hH, sy)) + *reach));
     // and the most pixels a unit of length projects to anywhere in the bounding sphere (see the kernels);
     // for a mesh as near as a few of its radii that is far more than at its far end
-    const double near_by = w_c / w_lo * (1.0 + r * g / w_lo);
-    double most = 0.0;
+    const double spread = 1.0 + r * g * per_w;
+    *scale = 0.0f;
+    if (!(w_c * per_w * spread <= kLooseScale)) return true;
+    const double per_c = 1.0 / w_c;
+    double most2 = 0.0;
     for (int row = 0; row < 2; ++row) {
         const double h = row == 0 ? hW : hH;
         double a[3], x0 = h * ((double)A[4 * row + 3] + A[11]), n = 0.0;
@@ -481,11 +503,12 @@ bool prescaled_rows(const float A[12], const float bs[4], float hW, float hH, fl
             a[j] = h * ((double)A[4 * row + j] + A[8 + j]);
             x0 += a[j] * c[j];
         }
-        x0 /= w_c;
+        x0 *= per_c;
         for (int j = 0; j < 3; ++j) n += (a[j] - x0 * A[8 + j]) * (a[j] - x0 * A[8 + j]);
-        most = std::max(most, std::sqrt(n) / w_lo * (1.0 + r * g / w_lo));
+        most2 = std::max(most2, n);
     }
-    *scale = near_by <= kLooseScale && most < 1e30 ? std::nextafter((float)(1.001 * most), INFINITY) : 0.0f;
+    const double most = std::sqrt(most2) * per_w * spread;
+    if (most < 1e30) *scale = next_up((float)(1.001 * most));
     return true;
 }
 
@@ -564,6 +587,7 @@ struct FixedVec {
         if (n < N) buf[n++] = v;
         else overflow = true;
     }
+    void reserve(size_t) {}
     void resize(size_t k)
     {
         overflow |= k > N;
@@ -638,17 +662,18 @@ uint32_t default_single_tpt(const curast_options& o, uint64_t tris)
 // costs a round trip per fragment (16 per pixel: 192 and 161 us, 2.3: 137 and 67 us, 0.5: 81 and 29).
 constexpr uint64_t kReadFirstDensity = 32;
 
-// Typical triangle edge in pixels of a draw, from the projected radius of its bounding sphere and the
-// triangle count, as if they tiled the sphere (4 pi R^2 = T sqrt(3) / 4 e^2); large without a sphere or
-// with its centre behind the camera.
-double edge_pixels(const DrawDesc& D, const curast_mesh& m)
+// Whether a draw's typical triangle edge is at most `px` pixels: from the projected radius of its bounding sphere
+// and the triangle count, as if they tiled the sphere (4 pi R^2 = T sqrt(3) / 4 e^2); not without a
+// sphere or with its centre behind the camera.  Compared in squares.
+bool edge_at_most(const DrawDesc& D, const curast_mesh& m, double px)
 {
     const float* c = m.bsphere;
-    if (!(c[3] > 0.0f)) return 1e3;
+    if (!(c[3] > 0.0f)) return false;
     const double w = (double)D.A[8] * c[0] + (double)D.A[9] * c[1] + (double)D.A[10] * c[2] + D.A[11];
-    if (!(w > 0.0)) return 1e3;
-    const double y = std::sqrt((double)D.A[4] * D.A[4] + (double)D.A[5] * D.A[5] + (double)D.A[6] * D.A[6]);
-    return std::min(1e3, 0.5 * ((double)D.hmax + 1.0) * y * c[3] / w * 5.4 / std::sqrt((double)m.num_triangles));
+    if (!(w > 0.0)) return false;
+    const double y2 = (double)D.A[4] * D.A[4] + (double)D.A[5] * D.A[5] + (double)D.A[6] * D.A[6];
+    const double k = 0.5 * ((double)D.hmax + 1.0) * c[3] * 5.4, e = px * w;
+    return k * k * y2 <= e * e * (double)m.num_triangles;
 }
 
 // Typical edge in pixels up to which a draw's strips (of 4 triangles) are first tested through their
@@ -700,7 +725,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
         d.near_plane = views[v].near_plane;
         d.wmax = (float)(views[v].width - 1);
         d.hmax = (float)(views[v].height - 1);
-        d.reach = 0.0f;
+        d.reach = general_reach(d.W, d.H);
         d.pad = 0;
         d.tile_base = P.hdr.n_tiles;
         P.hdr.n_tiles += (uint32_t)(((d.W + kTileSize - 1) / kTileSize) * ((d.H + kTileSize - 1) / kTileSize));
@@ -708,6 +733,9 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     }
     P.meshes.resize(M);
     uint64_t base = 0;
+    for (uint32_t m = 0; m < M; ++m)
+        if (meshes[m].num_triangles) P.max_draws += (uint64_t)n_inst(meshes[m]) * n_views;
+    P.draws.reserve(std::min<size_t>(P.max_draws, 1u << 16));   // more grow as they come: most may be culled
     P.mesh_draw_begin.resize(M);
     P.mesh_draw_count.resize(M);
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "too many meshes or views for the allocation-free form");
@@ -739,7 +767,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
                                    sphere_interior(D.A, me.bsphere, views[v].near_plane) &&
                                    prescaled_rows(D.A, me.bsphere, 0.5f * (float)views[v].width,
                                                   0.5f * (float)views[v].height, D.R, &D.scale, &D.grow, &D.reach);
-                if (!inner) D.reach = general_reach(views[v].width, views[v].height);
+                if (!inner) D.reach = P.views[v].reach;
                 if (visible) visible[(P.pair_count + i) * (uint64_t)n_views + v] = out ? 0 : inner ? 2 : 1;
                 if (out) {
                     P.draws_culled++;
@@ -754,9 +782,6 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
         P.pair_count += ni;
         mesh_draw_begin[m] = draw_begin;
         mesh_draw_count[m] = (uint32_t)P.draws.size() - draw_begin;
-        if (me.num_triangles) {
-            P.max_draws += (uint64_t)ni * n_views;
-        }
     }
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes at most 32 instances");
     // stage-1 segments: meshes drawn more than once first (their own launch, whose lanes reuse each
@@ -774,8 +799,8 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
         if (open_shape)
             for (uint32_t d = 0; d < mesh_draw_count[m]; ++d) {
                 DrawDesc& D = P.draws[mesh_draw_begin[m] + d];
-                if (edge_pixels(D, meshes[m]) > kSphereEdge) D.scale = -1.0f;
-                else P.spheres = true;
+                if (edge_at_most(D, meshes[m], kSphereEdge)) P.spheres = true;
+                else D.scale = -1.0f;
             }
     }
     P.tpt_single = auto_tpt ? default_single_tpt(o, single_tris) : o.s1_tris_per_thread;
