@@ -2020,6 +2020,27 @@ int curast_plan(const curast_mesh* meshes, uint32_t M, const curast_view* views,
     return CURAST_OK;
 }
 
+// The draws of a plan as the kernels read them, and the shape of its stage-1 launches (internal, used by the
+// tests): at most `room` records to `draws` (32 words each, see DrawDesc); shape[0..6] = draws, triangles per lane of
+// the single-draw and of the multi-draw launch, draws per work item, strip spheres, read before each atomic of
+// the single-draw launch, work items without any culling.  `graph`: as planned for a captured graph.
+int curast_internal_plan_draws(const curast_mesh* meshes, uint32_t M, const curast_view* views, uint32_t n_views,
+                               const curast_options* opt, int graph, void* draws, uint64_t room, uint64_t shape[7])
+{
+    curast_options u{};
+    if (opt) u = *opt;
+    std::string msg;
+    if (validate_options(u, msg) || !shape) return CURAST_E_INVALID;
+    Plan P;
+    const int rc = build_plan(nullptr, u, resolve_defaults(u, 256), meshes, M, views, n_views, P, nullptr, graph != 0);
+    if (rc) return rc;
+    if (draws && !P.draws.empty())
+        std::memcpy(draws, P.draws.data(), sizeof(DrawDesc) * (size_t)std::min<uint64_t>(room, P.draws.size()));
+    const uint64_t s[7] = {P.draws.size(), P.tpt_single, P.tpt_multi, P.hdr.draws_per_item, P.spheres, P.read_first, P.max_batches};
+    std::memcpy(shape, s, sizeof s);
+    return CURAST_OK;
+}
+
 // Queue fill of the last frame (internal, used by the autotuner): Q2, large records, Q3.
 int curast_internal_queue_counts(curast_ctx* ctx, uint64_t out[3])
 {
