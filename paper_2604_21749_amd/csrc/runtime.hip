@@ -624,7 +624,8 @@ struct PlanT {
     uint32_t tpt_single = 0;         // triangles per lane of the single-draw stage-1 launch
     uint32_t tpt_multi = 0;          // and of the multi-draw one
     bool spheres = false;            // strip spheres in the multi-draw launch
-    bool read_first = false;         // that launch reads the stored key before each atomic
+    bool read_first = false;         // the single-draw launch reads the stored key before each atomic
+    bool sample = false;             // or samples the stored depth of larger triangles to decide it
     size_t max_draws = 0;            // without any culling
     size_t off_views = 0, off_meshes = 0, off_segs = 0, off_draws = 0, bytes = 0, max_bytes = 0;
     bool full() const;
@@ -661,6 +662,11 @@ uint32_t default_single_tpt(const curast_options& o, uint64_t tris)
 // triangles than it writes fragments (65 per pixel: 2291 us with the read, 2363 without); elsewhere it
 // costs a round trip per fragment (16 per pixel: 192 and 161 us, 2.3: 137 and 67 us, 0.5: 81 and 29).
 constexpr uint64_t kReadFirstDensity = 32;
+// Pixels per triangle up to which its lanes sample the stored depth of larger triangles at all (kSampleArea): a launch
+// of fewer cannot lay many layers over one another, and pays for the sample in latency (131K triangles of a few px over
+// 1280 x 721, other meshes drawn before: 16.8 us with, 13.7 without; 12 layers of 12 px triangles at 2.6
+// pixels per triangle: 145 and 272 us).
+constexpr uint64_t kSamplePixels = 4;
 
 // Whether a draw's typical triangle edge is at most `px` pixels: from the projected radius of its bounding sphere
 // and the triangle count, as if they tiled the sphere (4 pi R^2 = T sqrt(3) / 4 e^2); not without a
@@ -805,6 +811,7 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     }
     P.tpt_single = auto_tpt ? default_single_tpt(o, single_tris) : o.s1_tris_per_thread;
     P.read_first = single_tris >= kReadFirstDensity * P.total_pixels;
+    P.sample = single_tris * kSamplePixels >= P.total_pixels;
     P.tpt_multi = user.s1_multi_tris_per_thread ? o.s1_multi_tris_per_thread : 4u;
     // triangles per work item of the two launches (the strip and vertex-sharing kernels run 64-lane
     // workgroups), and draws per work item
@@ -1007,7 +1014,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
             RasterArgs a1 = a;
             a1.part = part;
             if (part == 1 || !P.read_first) a1.flags |= atomic_alone;
-            a1.sample_area = part == 2 && !(a.flags & kFlagNoEarlyOut) ? kSampleArea : kNeverSample;
+            a1.sample_area = part == 2 && P.sample && !(a.flags & kFlagNoEarlyOut) ? kSampleArea : kNeverSample;
             if (part == 1 && mode == 3) return launch_stage1_share(a1, tpt, stats, grid, st);
             if (mode == 1) return launch_stage1(a1, blk, tpt, stats, grid, st);
             if (!uses_strips(ctx->opt, part, tpt)) return launch_stage1_fast(a1, blk, tpt, stats, grid, st);
@@ -1117,7 +1124,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     const uint32_t grid1 = std::min(grid_for(P.max_batches), stage1_grid_cap(ctx));
     // the queue capacities are kernel arguments of the captured launches, so they are part of the key
     uint64_t key[11] = {(uint64_t)M, (uint64_t)n_views, (uint64_t)P.max_bytes, (uint64_t)grid1,
-                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.read_first << 16) |
+                       ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.sample << 17) | ((uint64_t)P.read_first << 16) |
                            (P.tpt_single << 8) | (P.tpt_multi << 4) | ctx->opt.s1_mode,
                        ((uint64_t)ctx->opt.s2_waves << 32) | ctx->opt.s3_blocks,
                        ((uint64_t)ctx->opt.flags << 32) | ctx->opt.small_px,
@@ -2022,8 +2029,8 @@ int curast_plan(const curast_mesh* meshes, uint32_t M, const curast_view* views,
 
 // The draws of a plan as the kernels read them, and the shape of its stage-1 launches (internal, used by the
 // tests): at most `room` records to `draws` (32 words each, see DrawDesc); shape[0..6] = draws, triangles per lane of
-// the single-draw and of the multi-draw launch, draws per work item, strip spheres, read before each atomic of
-// the single-draw launch, work items without any culling.  `graph`: as planned for a captured graph.
+// the single-draw and of the multi-draw launch, draws per work item, strip spheres, what the single-draw launch
+// reads first (1: the stored key before each atomic, 2: samples), work items without any culling.  `graph`: as planned for a captured graph.
 int curast_internal_plan_draws(const curast_mesh* meshes, uint32_t M, const curast_view* views, uint32_t n_views,
                                const curast_options* opt, int graph, void* draws, uint64_t room, uint64_t shape[7])
 {
@@ -2036,7 +2043,8 @@ int curast_internal_plan_draws(const curast_mesh* meshes, uint32_t M, const cura
     if (rc) return rc;
     if (draws && !P.draws.empty())
         std::memcpy(draws, P.draws.data(), sizeof(DrawDesc) * (size_t)std::min<uint64_t>(room, P.draws.size()));
-    const uint64_t s[7] = {P.draws.size(), P.tpt_single, P.tpt_multi, P.hdr.draws_per_item, P.spheres, P.read_first, P.max_batches};
+    const uint64_t s[7] = {P.draws.size(), P.tpt_single, P.tpt_multi, P.hdr.draws_per_item, P.spheres,
+                           (uint64_t)P.read_first | (uint64_t)P.sample << 1, P.max_batches};
     std::memcpy(shape, s, sizeof s);
     return CURAST_OK;
 }

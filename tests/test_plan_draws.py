@@ -152,3 +152,13 @@ def test_graph_shapes_follow_sizes_alone(opts):
         fixed.add((s["tpt_single"], s["tpt_multi"], s["read_first"], s["max_items"]))
         counts.add(s["draws"])
     assert len(counts) > 2 and len(fixed) == 1, (counts, fixed)
+
+
+def test_single_draw_launch_reads_by_density():
+    """What the single-draw launch reads before its atomics follows the triangles per pixel: nothing below a
+    quarter, samples from there on, every key from 32."""
+    pos, _ = W.uv_sphere(6, 12, 1.0)
+    view = W.View(W.camera((0.0, 0.0, 3.0), (0.0, 0.0, 0.0)), W.NEAR, 200, 100)
+    for triangles, reads in ((4999, 0), (5000, 2), (639999, 2), (640000, 3)):
+        for graph in (False, True):
+            assert plan_draws([_mesh(pos, None, triangles)], [view], graph)[1]["read_first"] == reads, triangles
