@@ -29,12 +29,10 @@ struct FrameHeader {              // 48 B
     uint64_t total_batches;       // stage-1 work items over all segments
     uint32_t n_segs;
     uint32_t n_views;
-    uint32_t batch_tris;          // triangles per work item of the plain stage-1 kernels
     uint32_t draws_per_item;      // draws per work item
-    uint64_t shared_batches;      // work items [0, shared_batches) belong to meshes drawn more than once
     uint32_t n_tiles;             // 64x64 screen tiles over all views (stage-3 bins)
-    uint32_t pad0;
-    uint64_t pad1;
+    uint64_t shared_batches;      // work items [0, shared_batches) belong to meshes drawn more than once
+    uint64_t pad[2];
 };
 
 struct ViewDesc {                 // 48 B
@@ -77,7 +75,7 @@ struct Segment {                  // 32 B
 // Bit 31 of `view` (kDrawInterior) marks draws whose bounding sphere the host proved to lie in
 // front of the near plane and inside |x|, |y| <= 1.99 w: no vertex of such a draw needs the
 // per-vertex near/guard tests of the fast stage-1 path.
-struct DrawDesc {                 // 128 B: one cache line holds all that a fragment of the draw needs
+struct DrawDesc {                 // 128 B, aligned to them: one cache line holds all that a fragment of the draw needs
     float A[12];                  // rows x, y, w of VP * X (the exact transform)
     float R[8];                   // interior draws: hW (row x + row w), hH (row y + row w)
     uint64_t id_base;

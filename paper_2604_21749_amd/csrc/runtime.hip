@@ -872,12 +872,11 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     if (P.full()) return fail(ctx, CURAST_E_INVALID, "the allocation-free form takes one mesh and one view");
     P.hdr.n_segs = (uint32_t)P.segs.size();
     P.hdr.n_views = n_views;
-    P.hdr.batch_tris = bt;
     P.hdr.draws_per_item = dpi;
     P.off_views = align_up(sizeof(FrameHeader), 64);
     P.off_meshes = align_up(P.off_views + sizeof(ViewDesc) * n_views, 64);
     P.off_segs = align_up(P.off_meshes + sizeof(MeshDesc) * std::max<uint32_t>(M, 1), 64);
-    P.off_draws = align_up(P.off_segs + sizeof(Segment) * std::max<uint32_t>(M, 1), 64);
+    P.off_draws = align_up(P.off_segs + sizeof(Segment) * std::max<uint32_t>(M, 1), sizeof(DrawDesc));
     P.bytes = align_up(P.off_draws + sizeof(DrawDesc) * std::max<size_t>(P.draws.size(), 1), 64);
     P.max_bytes = align_up(P.off_draws + sizeof(DrawDesc) * std::max<size_t>(P.max_draws, 1), 256);
     return CURAST_OK;
@@ -1210,10 +1209,12 @@ struct NaDesc {
     ViewDesc view;
     MeshDesc mesh;
     Segment segs[2];
-    DrawDesc draws[kFixedDraws];
+    alignas(sizeof(DrawDesc)) DrawDesc draws[kFixedDraws];
 };
 static_assert(sizeof(NaDesc) % 4 == 0 && sizeof(NaDesc) <= 2 * sizeof(uint32_t) * kBlockWords,
               "descriptor block fits two kernel arguments");
+
+static_assert(offsetof(NaDesc, draws) % sizeof(DrawDesc) == 0, "one cache line per draw");
 
 constexpr size_t kNaOffCounters = align_up(sizeof(NaDesc), 256);
 constexpr size_t kNaOffStats = kNaOffCounters + 256;
@@ -2028,11 +2029,12 @@ int curast_plan(const curast_mesh* meshes, uint32_t M, const curast_view* views,
 }
 
 // The draws of a plan as the kernels read them, and the shape of its stage-1 launches (internal, used by the
-// tests): at most `room` records to `draws` (32 words each, see DrawDesc); shape[0..6] = draws, triangles per lane of
+// tests): at most `room` records to `draws` (32 words each, see DrawDesc); shape[0..7] = draws, triangles per lane of
 // the single-draw and of the multi-draw launch, draws per work item, strip spheres, what the single-draw launch
-// reads first (1: the stored key before each atomic, 2: samples), work items without any culling.  `graph`: as planned for a captured graph.
+// reads first (1: the stored key before each atomic, 2: samples), work items without any culling, byte offset of the draws in the
+// descriptor block.  `graph`: as planned for a captured graph.
 int curast_internal_plan_draws(const curast_mesh* meshes, uint32_t M, const curast_view* views, uint32_t n_views,
-                               const curast_options* opt, int graph, void* draws, uint64_t room, uint64_t shape[7])
+                               const curast_options* opt, int graph, void* draws, uint64_t room, uint64_t shape[8])
 {
     curast_options u{};
     if (opt) u = *opt;
@@ -2043,8 +2045,8 @@ int curast_internal_plan_draws(const curast_mesh* meshes, uint32_t M, const cura
     if (rc) return rc;
     if (draws && !P.draws.empty())
         std::memcpy(draws, P.draws.data(), sizeof(DrawDesc) * (size_t)std::min<uint64_t>(room, P.draws.size()));
-    const uint64_t s[7] = {P.draws.size(), P.tpt_single, P.tpt_multi, P.hdr.draws_per_item, P.spheres,
-                           (uint64_t)P.read_first | (uint64_t)P.sample << 1, P.max_batches};
+    const uint64_t s[8] = {P.draws.size(), P.tpt_single, P.tpt_multi, P.hdr.draws_per_item, P.spheres,
+                           (uint64_t)P.read_first | (uint64_t)P.sample << 1, P.max_batches, P.off_draws};
     std::memcpy(shape, s, sizeof s);
     return CURAST_OK;
 }

@@ -22,12 +22,13 @@ def plan_draws(meshes, views, graph=False, **options):
         vs[i].visbuffer = C.addressof(vis) + 8 * i
     room = sum(m.num_instances for m in meshes) * len(views)
     draws = np.zeros(room, DRAW)
-    shape = (C.c_uint64 * 7)()
+    shape = (C.c_uint64 * 8)()
     opt = api.Context._options(options)
     f = api.lib().curast_internal_plan_draws
     f.argtypes = [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint32, C.c_void_p, C.c_int, C.c_void_p, C.c_uint64, C.c_void_p]
     rc = f(arr, len(meshes), vs, len(views), C.byref(opt), int(graph), draws.ctypes.data, room, shape)
     assert rc == api.OK, rc
-    names = ("draws", "tpt_single", "tpt_multi", "draws_per_item", "spheres", "read_first", "max_items")
+    names = ("draws", "tpt_single", "tpt_multi", "draws_per_item", "spheres", "read_first", "max_items",
+             "offset")
     shape = dict(zip(names, map(int, shape)))
     return draws[:shape["draws"]], shape

@@ -162,3 +162,12 @@ def test_single_draw_launch_reads_by_density():
     for triangles, reads in ((4999, 0), (5000, 2), (639999, 2), (640000, 3)):
         for graph in (False, True):
             assert plan_draws([_mesh(pos, None, triangles)], [view], graph)[1]["read_first"] == reads, triangles
+
+
+@pytest.mark.parametrize("n_meshes", [1, 2, 25, 40])
+@pytest.mark.parametrize("n_views", [1, 2, 7])
+def test_draw_records_are_cache_lines(n_meshes, n_views):
+    """The records start at a multiple of their 128 bytes in the descriptor block, whatever comes before them."""
+    pos, _ = W.uv_sphere(6, 12, 1.0)
+    views = [W.View(W.camera((0.0, 0.0, 3.0 + i), (0.0, 0.0, 0.0)), W.NEAR, 64, 64) for i in range(n_views)]
+    assert plan_draws([_mesh(pos)] * n_meshes, views)[1]["offset"] % 128 == 0
