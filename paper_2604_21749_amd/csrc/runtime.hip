@@ -945,10 +945,13 @@ TimedFrame* begin_timing(curast_ctx* ctx)
     return &ctx->timed.back();
 }
 
-// Most workgroups of a stage-1 launch.
-uint32_t stage1_grid_cap(const curast_ctx* ctx)
+// Most workgroups of a stage-1 launch.  Those of a launch that counts (CURAST_FLAG_STATS) each add to the same few
+// counters when they end, so it has no more than eight per compute unit (600 instances of a 131K-triangle mesh
+// 1035 us with one per work item, 290 so).
+uint32_t stage1_grid_cap(const curast_ctx* ctx, bool stats)
 {
-    return (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * ctx->opt.s1_blocks_per_cu, 1ull << 24);
+    const uint64_t per_cu = stats ? std::min(ctx->opt.s1_blocks_per_cu, 8u) : ctx->opt.s1_blocks_per_cu;
+    return (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * per_cu, 1ull << 24);
 }
 
 uint32_t clear_grid(const curast_ctx* ctx, uint64_t total_pixels)
@@ -1004,7 +1007,7 @@ int launch_frame(curast_ctx* ctx, const RasterArgs& a, const PlanType& P, Clear 
         // items: a workgroup's set-up is then shared by several items, and the dispatcher
         // launches fewer workgroups (one per item measured slower on the HBM-bound launch)
         const uint32_t mode = ctx->opt.s1_mode, blk = ctx->opt.s1_block;
-        const uint32_t grid_cap = stage1_grid_cap(ctx);
+        const uint32_t grid_cap = stage1_grid_cap(ctx, stats);
         // a fragment is written by the atomic alone, without reading the stored key first (a memory
         // round trip per fragment), except in dense single-draw launches (kReadFirstDensity) and where a lane
         // of the single-draw launch finds its triangle covered (kSampleArea)
@@ -1120,7 +1123,7 @@ int rasterize_impl(curast_ctx* ctx, const curast_mesh* meshes, uint32_t M, const
     }
     // graph path: one captured sequence per structure (sizes of the descriptor block, grid,
     // options); replays copy the new descriptor contents from the same pinned buffer
-    const uint32_t grid1 = std::min(grid_for(P.max_batches), stage1_grid_cap(ctx));
+    const uint32_t grid1 = std::min(grid_for(P.max_batches), stage1_grid_cap(ctx, ctx->opt.flags & kFlagStats));
     // the queue capacities are kernel arguments of the captured launches, so they are part of the key
     uint64_t key[11] = {(uint64_t)M, (uint64_t)n_views, (uint64_t)P.max_bytes, (uint64_t)grid1,
                        ((uint64_t)ctx->opt.s1_block << 32) | ((uint64_t)P.sample << 17) | ((uint64_t)P.read_first << 16) |
