@@ -693,6 +693,9 @@ constexpr double kSphereEdge = 0.13;
 // 600 draws of 131K triangles 245 us with 64 (5120 items), 225 with 16; 150 draws of 92K 154 and 66; 4088 draws of
 // 2.1M triangles 3.95 ms with 64, 3.80 with 128, 3.99 with 256.
 constexpr uint64_t kMinItems = 16384;
+// Fewer in mode 3, whose set-up (the deduplication of an item's vertices) is the larger part of an item: 600 draws
+// of 131K shuffled triangles 589 us with 16, 302 with 64; 100 draws 224 and 319.
+constexpr uint64_t kMinShareItems = 4096;
 
 // `user`: the options as the caller set them, zeros where the choice is open; `o`: with defaults.  `graph`: for a
 // captured graph, whose kernels and grids are chosen from sizes and options alone (as if nothing were culled), so
@@ -830,8 +833,9 @@ int build_plan(curast_ctx* ctx, const curast_options& user, const curast_options
     };
     auto draws_per_item = [&](bool all) {
         uint32_t d = o.s1_draws_per_item;
+        const uint64_t enough = o.s1_mode == 3 ? kMinShareItems : kMinItems;
         if (!user.s1_draws_per_item && (all || multi))
-            for (d = 128; d > 8 && items(d, all) < kMinItems; d /= 2) {}
+            for (d = 128; d > 8 && items(d, all) < enough; d /= 2) {}
         return d;
     };
     uint32_t dpi = draws_per_item(graph);

@@ -171,3 +171,15 @@ def test_draw_records_are_cache_lines(n_meshes, n_views):
     pos, _ = W.uv_sphere(6, 12, 1.0)
     views = [W.View(W.camera((0.0, 0.0, 3.0 + i), (0.0, 0.0, 0.0)), W.NEAR, 64, 64) for i in range(n_views)]
     assert plan_draws([_mesh(pos)] * n_meshes, views)[1]["offset"] % 128 == 0
+
+
+@pytest.mark.parametrize("instances,per_item", [(600, 64), (100, 8), (3000, 128)])
+def test_vertex_sharing_items_keep_more_draws(instances, per_item):
+    """Mode 3 deduplicates an item's vertices first, so its items keep more draws than the strip kernel's."""
+    rng = np.random.default_rng(instances)
+    pos, _ = W.uv_sphere(6, 12, 1.0)
+    inst = W.instance_matrices(W.random_rotations(rng, instances), np.full(instances, 0.01), rng.uniform(-0.5, 0.5, (instances, 3)))
+    view = W.View(W.camera((0.0, 0.0, 3.0), (0.0, 0.0, 0.0)), W.NEAR, 1000, 1000)
+    mesh = _mesh(pos, inst, triangles=131072)
+    assert plan_draws([mesh], [view], s1_mode=3)[1]["draws_per_item"] == per_item
+    assert plan_draws([mesh], [view])[1]["draws_per_item"] <= per_item
