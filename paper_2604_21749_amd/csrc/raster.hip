@@ -146,7 +146,8 @@ template <bool STATS>
 __device__ __forceinline__ void raster_small(const SmallTri& s, uint64_t id, const ViewDesc& V, bool early_out,
                                              int32_t sample_area, StatAcc<STATS>& st)
 {
-    if (!early_out && s.area >= sample_area) {
+    // (without tiny culling the box may be empty and lie past the view)
+    if (!early_out && s.area >= sample_area && s.px0 <= s.px1 && s.py0 <= s.py1) {
         // the depth stored in the middle of the box (NaN of an empty pixel) against the nearest vertex
         const unsigned long long key =
             gl(V.vis)[(size_t)((s.py0 + s.py1) >> 1) * (size_t)V.W + (size_t)((s.px0 + s.px1) >> 1)];

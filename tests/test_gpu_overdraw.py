@@ -46,3 +46,26 @@ def test_layers(cell, layers, order, jitter):
             vis = torch.empty((view.height, view.width), dtype=torch.int64, device="cuda")
             c.rasterize_noalloc(gm.pos, gm.idx, view.vp, view.near, view.width, view.height, vis)
             assert_vis_equal(api.as_uint64(vis), ref, f"{cell} {layers} {order} {opts}, allocation-free")
+
+
+@pytest.mark.parametrize("size", [(64, 64), (61, 33), (200, 5)])
+def test_boxes_past_the_view_without_tiny_culling(size):
+    """Triangles that miss the view past its corners, where no single side culls them: without tiny culling they
+    reach the small rasterizer with an empty box, which holds no pixel to sample."""
+    rng = np.random.default_rng(size[0])
+    view = W.View(W.camera((0.0, 0.0, 3.0), (0.0, 0.0, 0.0), aspect=size[0] / size[1]), W.NEAR, *size)
+    half = 3.0 / np.reshape(view.vp, (4, 4))[1, 1]
+    c = rng.choice([-1.0, 1.0], (6000, 1, 2)) * np.array([half * size[0] / size[1], half])
+    d = rng.uniform(-0.06, 0.06, (6000, 3, 2)) + 0.03 * np.sign(c)
+    pos = np.concatenate([c + d, rng.uniform(-0.1, 0.1, (6000, 3, 1))], 2).reshape(-1, 3).astype(np.float32)
+    mesh = W.Mesh(pos, np.arange(18000, dtype=np.uint32).reshape(-1, 3))
+    ref = O.rasterize([mesh], view)
+    gm = api.GpuMesh.from_host(mesh)
+    guard = torch.full((3 * size[1], size[0]), -1, dtype=torch.int64, device="cuda")
+    for flags in (0, api.FLAG_NO_TINY_CULL, api.FLAG_NO_TINY_CULL | api.FLAG_STATS):
+        for mode in (0, 1):
+            guard.fill_(-1)
+            with api.Context(flags=flags, s1_mode=mode) as ctx:
+                ctx.rasterize_meshes([gm], view, out=guard[size[1]:2 * size[1]])
+            assert_vis_equal(api.as_uint64(guard[size[1]:2 * size[1]]), ref, f"{size} {flags} {mode}")
+            assert (guard[:size[1]] == -1).all() and (guard[2 * size[1]:] == -1).all()
