@@ -38,11 +38,12 @@ if ROOT not in sys.path:
 
 METRIC = "Gtris/s & ms/frame at 3840x2160 (plain vs batched); resolve bwd ms"
 HBM_PEAK_GBS = 8000.0
-# vector ALU of MI355X without packed fp32 (which the build turns off): 256 CUs x 4 SIMDs x 16 lanes
-# at 2.4 GHz, i.e. 64 lane-operations per CU per clock, or one wave64 instruction per CU per clock
+# A yardstick for vector instructions: one wave64 instruction per CU and clock, i.e. 64 lane-operations, at 2.4
+# GHz.  It is no bound: the multi-draw launch issues up to 1.17 per CU and busy clock, and the card's headline
+# fp32 rate without matrix cores counts 128 lanes per CU and clock.
 CUS, CLOCK_HZ = 256, 2.4e9
 ALU_PEAK_TOPS = CUS * 64 * CLOCK_HZ / 1e12
-VALU_ISSUE_PEAK = CUS * CLOCK_HZ            # wave64 VALU instructions per second
+VALU_ISSUE_PEAK = CUS * CLOCK_HZ            # wave64 VALU instructions per second of that yardstick
 
 # Algorithmic lane-operations of the multi-draw stage-1 launch (the strip algorithm; every draw
 # counted as an interior one, whose vertices need no range tests):
@@ -54,7 +55,8 @@ VALU_ISSUE_PEAK = CUS * CLOCK_HZ            # wave64 VALU instructions per secon
 #   the clamped lower (3) and upper (4) end of its box on each axis, 2 compares, a select and an or
 #   = 31;
 #   one (strip of S triangles, draw): the sphere test, then for a strip the sphere cannot reject
-#   S + 2 projections and the union-box test of its S + 2 vertices (s1_mode 4: always the latter);
+#   S + 2 projections and the union-box test of its S + 2 vertices (s1_mode 4, and draws of larger
+#   triangles with the defaults: always the latter);
 #   a strip whose union box may hold a pixel centre: S more box tests of 3 positions (20 each);
 #   a triangle outside a strip (poles, row ends): 3 projections and its box test.
 PROJ_OPS = 12
@@ -99,6 +101,34 @@ def split_meshes(api, scene, gm):
             single.append(m)
             single_items += m.num_triangles * draws
     return multi, single, multi_items, single_items
+
+
+def launch_shape(api, gm, views, options) -> dict:
+    """The stage-1 launches' shape at `options` (a context's), with what it leaves to every launch as this
+    one chooses it: triangles per lane, draws per work item, strips, strip spheres, and the triangle x draw items
+    of the multi-draw launch whose strips are tested through boxes all the same."""
+    import ctypes as C
+    keep = []
+    arr = api._mesh_array(gm, keep, check=False)
+    vis = (C.c_uint64 * len(views))()               # distinct non-NULL buffers, never touched
+    vs = (api.ViewStruct * len(views))()
+    for i, v in enumerate(views):
+        vs[i] = api._view_struct(v.vp, v.near, v.width, v.height, None)
+        vs[i].visbuffer = C.addressof(vis) + 8 * i
+    draws = np.zeros((sum(m.num_instances for m in gm) * len(views), 32), np.uint32)   # curast::DrawDesc
+    shape = (C.c_uint64 * 8)()
+    opt = api.Context._options(options)
+    rc = api.lib().curast_internal_plan_draws(arr, C.c_uint32(len(gm)), vs, C.c_uint32(len(views)), C.byref(opt), 0,
+                                              C.c_void_p(draws.ctypes.data), C.c_uint64(len(draws)), shape)
+    if rc != api.OK:
+        raise RuntimeError(f"launch shape: status {rc}")
+    n, single, multi, per_item, spheres = (int(x) for x in shape[:5])
+    view, mesh, scale = draws[:n, 22], draws[:n, 23], draws[:n, 24].view(np.float32)
+    boxes = (np.bincount(mesh, minlength=len(gm))[mesh] >= 2) & ((scale < 0) | (view < 1 << 31))
+    strips = multi >= 2 and options["s1_mode"] not in (1, 3) and not (options["flags"] & api.FLAG_NO_STRIPS)
+    return {"single": single, "multi": multi, "draws_per_item": per_item, "strips": strips,
+            "spheres": bool(strips and spheres),
+            "box_items": int(np.array([m.num_triangles for m in gm], np.int64)[mesh[boxes]].sum())}
 
 
 def autotuned_options(args, ctx, gm, views, outs) -> dict:
@@ -191,6 +221,7 @@ def run_frame_config(args, api, torch, W, name, secondary=False):
          "stage_ms": stage_ms, "frame_events": frame_ev, "frame_events_no_events": frame_ev_plain,
          "visible": visible, "stats": st, "multi": multi, "single": single, "multi_items": multi_items,
          "single_items": single_items, "options": ctx.options(), "autotuned": bool(tuned)}
+    h["shape"] = launch_shape(api, gm, [view], h["options"])
     h["supersampling"] = run_supersampling(args, api, torch, ctx, gm, attrs, view, ms_plain) if secondary else {}
     h["compressed"] = run_compressed(args, api, torch, ctx, gm, attrs, view, visible) if secondary else {}
     h["textured"] = run_textured(args, api, torch, W, ctx, gm, attrs, view, vis) if secondary else {}
@@ -371,15 +402,16 @@ def multi_launch_ops(h) -> int:
     """Algorithmic lane-operations of one multi-draw stage-1 launch (see the counts at the top):
     from the frame's statistics at the timed options, the (strip, draw) pairs, those whose union
     box may hold a pixel centre, and the triangle x draw items outside strips."""
-    o, st = h["options"], h["stats"]
-    strips = o["s1_multi_tris_per_thread"] in (2, 4, 8) and not (o["flags"] & 0x100) and o["s1_mode"] != 3
+    sh, st = h["shape"], h["stats"]
+    strips = sh["strips"]
     if not strips:
         return h["multi_items"] * LONE_TRI_DRAW_OPS
-    S = o["s1_multi_tris_per_thread"]
+    S = sh["multi"]
     pairs, passed = int(st["strip_draws"]), int(st["strip_union_pass"])
     lone = max(0, h["multi_items"] - pairs * S)
-    if o["s1_mode"] in (0, 2):
-        tested = pairs * SPHERE_OPS + int(st["strip_sphere_pass"]) * strip_draw_ops(S)
+    if sh["spheres"]:
+        boxes = min(pairs, sh["box_items"] // S)
+        tested = (pairs - boxes) * SPHERE_OPS + (boxes + int(st["strip_sphere_pass"])) * strip_draw_ops(S)
     else:
         tested = pairs * strip_draw_ops(S)
     return tested + passed * S * box_ops(3) + lone * LONE_TRI_DRAW_OPS
@@ -395,12 +427,10 @@ def stage1_rooflines(h):
     that survive the host cull.  Both divide by the launch's own HIP-event time over the timed
     frames."""
     sm = h["stage_ms"]
-    o = h["options"]
-    strip = o["s1_multi_tris_per_thread"] in (2, 4, 8) and not (o["flags"] & 0x100)
-    sph = "true" if strip and o["s1_mode"] in (0, 2) else "false"
-    k_single = f"stage1_fast_kernel<{o['s1_block']}, {o['s1_tris_per_thread']}, false, 0>"
-    k_multi = f"stage1_strips_kernel<{o['s1_multi_tris_per_thread']}, {sph}, false, 0>" if strip else \
-        f"stage1_fast_kernel<{o['s1_block']}, {o['s1_multi_tris_per_thread']}, false, 0>"
+    o, sh = h["options"], h["shape"]
+    k_single = f"stage1_fast_kernel<{o['s1_block']}, {sh['single']}, false, 0>"
+    k_multi = f"stage1_strips_kernel<{sh['multi']}, {'true' if sh['spheres'] else 'false'}, false, 0>" if sh["strips"] else \
+        f"stage1_fast_kernel<{o['s1_block']}, {sh['multi']}, false, 0>"
     single_bytes = stage1_algorithmic_bytes(h["single"])
     t_single = max(sm["stage1_single"] * 1e-3, 1e-12)
     t_multi = max(sm["stage1_multi"] * 1e-3, 1e-12)
@@ -424,8 +454,8 @@ def stage1_rooflines(h):
         "algorithmic_lane_ops": int(ops), "lane_ops_per_unit": round(ops / max(items, 1), 3),
         "unit_of_work": "triangle x draw item", "launch_ms": round(sm["stage1_multi"], 4),
         # VALU wave64 instructions the launch issued (rocprofv3 SQ_INSTS_VALU, committed summary) over
-        # the same live launch time: issued lane-operations (x64, inactive lanes included) and the
-        # fraction of the one-instruction-per-CU-per-clock issue peak
+        # the same live launch time: issued lane-operations (x64, inactive lanes included) and their
+        # ratio to one instruction per CU and clock (which is no bound, see VALU_ISSUE_PEAK)
         "issued_lane_ops_per_s": None if valu is None else round(valu * 64 / t_multi / 1e12, 2),
         "issued_frac": None if valu is None else round(valu / t_multi / VALU_ISSUE_PEAK, 4),
         "issued_lane_ops_per_unit": None if valu is None else round(valu * 64 / max(items, 1), 3),
@@ -478,6 +508,7 @@ def run_batched(args, api, torch, W):
     multi, single, multi_items, single_items = split_meshes(api, scene, gm)
     h = {"name": "c4", "stage_ms": {**stage_ms, "resolve": 0.0}, "options": ctx.options(), "stats": st,
          "multi": multi, "single": single, "multi_items": multi_items, "single_items": single_items}
+    h["shape"] = launch_shape(api, gm, scene.views, h["options"])
     rl = stage1_rooflines(h)
     ctx.close()
     del gm, outs
