@@ -112,7 +112,8 @@ typedef struct {
     uint32_t small_px;          /* stage-1 limit on pixel centres in the clamped bbox (default 32; the
                                    paper's 128, Sec. 4, measured slower here) */
     uint32_t medium_px;         /* stage-2 limit (default 4096, Sec. 4) */
-    uint32_t s1_block;          /* stage-1 workgroup size: 64, 128, 256 or 512 (default 64, Sec. 4.1) */
+    uint32_t s1_block;          /* stage-1 workgroup size: 64, 128, 256 or 512 (default 64, Sec. 4.1); launches
+                                   that look for strips and s1_mode 3 run workgroups of 64 whatever it is */
     uint32_t s1_tris_per_thread;/* triangles per thread per stage-1 work item of a mesh drawn once:
                                    1, 2, 4 or 8 (default 4; with 0 a launch of fewer
                                    than 7M triangles takes 2, of fewer than 0.7M 1, except under
@@ -453,8 +454,8 @@ int curast_reset_stats(curast_ctx* ctx);
 /* Stage durations accumulated over frames run with CURAST_FLAG_TIMING, measured with HIP events
    on the launch stream (synchronizes those events): ms[0..8] = clear, stage-1 launch over the
    meshes with two or more draws (all meshes when s1_mode = 3), stage-1 launch over the other
-   meshes, 0 (the stage-1 overflow pass is part of the stage-2 launch), stage 2, stage 3, resolve (either form), resolve backward, whole
-   rasterized frame; *frames = number of rasterized frames timed.
+   meshes, 0 (the stage-1 overflow pass is part of the stage-2 launch), stage 2, stage 3, resolve
+   (either form), resolve backward, whole rasterized frame; *frames = number of rasterized frames timed.
    Batched (graph) frames contribute only the whole-frame time. */
 int curast_get_stage_times(curast_ctx* ctx, double ms[9], uint64_t* frames);
 int curast_reset_stage_times(curast_ctx* ctx);

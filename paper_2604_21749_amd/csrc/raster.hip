@@ -1,8 +1,9 @@
 // Rasterization kernels for gfx950: the frame's first launch (descriptors and clear), stage 1 (one lane
 // per small triangle, or per strip of a mesh drawn several times), stage 2 (the stage-1 overflow pass;
-// then a wavefront sets up to 64 medium triangles up in parallel, clipping them, and rasterizes them one
-// by one) and stage 3 (workgroups over quarters of the 64x64 tiles that large triangles touch).  Sec. 4.1-4.3 describe the three stages; the wave64
-// mapping, ballot-compacted queues and in-place overflow handling are this implementation's.
+// then a wavefront sets up as many as 64 medium triangles in parallel, clipping them, and rasterizes them one
+// by one) and stage 3 (workgroups over the 64x64 tiles that large triangles touch, or quarters of
+// them).  Sec. 4.1-4.3 describe the three stages; the wave64 mapping, ballot-compacted queues and in-place
+// overflow handling are this implementation's.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -587,8 +588,7 @@ __device__ __forceinline__ void exact_route(const RasterArgs& a, bool have, cons
 
 // Drain ring entries [head, head + n), n <= 64, one per lane.
 template <bool STATS>
-__device__ __forceinline__ void drain_ring(const RasterArgs& a, const ViewDesc* __restrict__ d_views,
-                                           const MeshDesc* __restrict__, const DrawDesc* __restrict__ d_draws,
+__device__ __forceinline__ void drain_ring(const RasterArgs& a, const DrawDesc* __restrict__ d_draws,
                                            const ClipEntry* ring, uint32_t head, uint32_t n, bool tiny_cull,
                                            bool early_out, StatAcc<STATS>& st)
 {
@@ -611,9 +611,8 @@ __device__ __forceinline__ void drain_ring(const RasterArgs& a, const ViewDesc* 
 }
 
 template <bool STATS>
-__device__ __forceinline__ void drain_ring(const RasterArgs& a, const ViewDesc* __restrict__ d_views,
-                                           const MeshDesc* __restrict__ d_meshes, const DrawDesc* __restrict__ d_draws,
-                                           const IdEntry* ring, uint32_t head, uint32_t n, bool tiny_cull,
+__device__ __forceinline__ void drain_ring(const RasterArgs& a, const MeshDesc* __restrict__ d_meshes,
+                                           const DrawDesc* __restrict__ d_draws, const IdEntry* ring, uint32_t head, uint32_t n, bool tiny_cull,
                                            bool early_out, StatAcc<STATS>& st)
 {
     const bool have = lane_id() < n;
@@ -731,22 +730,6 @@ __device__ __forceinline__ bool fast_reject_strip(const float2 (&w)[N], bool any
     return !any_nan && fast_reject_union<N>(w, V, tiny_cull);
 }
 
-// Strip spheres.  Before a strip of an interior draw is projected vertex by vertex, it is tested
-// through a bounding sphere (c, r) of its vertices, computed once per work item in object space.
-// For a vertex v = c + d, |d| <= r, with a = (row x'')[0..2] and b = (row w)[0..2] of the draw,
-//   x(v) - x(c) = ((a - x(c) b) . d) / (w(c) + b . d),  so  |x(v) - x(c)| <= |a - x(c) b| r / (w(c) - |b| r)
-// (and likewise y), provided w(c) - |b| r > 0; the test requires at least w(c) / 2.  By the mean value
-// theorem it is also at most L r, where L bounds the gradient |a - x b| / w over the mesh's bounding sphere
-// (radius p, centre at x0, w0, smallest depth w1): |a - x b| <= |a - x0 b| + |x - x0| |b| and |x - x0| <=
-// |a - x0 b| p / w1, so L = |a - x0 b| (1 + p |b| / w1) / w1, which the host computes once per draw
-// (DrawDesc::scale, the larger axis).  A mesh much nearer than it is large makes L loose; the host then
-// leaves scale 0 and the lane evaluates the first bound.  The box x(c) +- the bound, widened by the per-draw
-// slack the host derived for the binary32 error of the projected centre and of the box arithmetic and by the
-// draw's reach (DrawDesc::grow), holds every exact window position of the strip's vertices up to the draw's
-// margin, so the extent test of the union box applies to it.  The radius itself is inflated by 2^-10 in
-// relative terms, which covers the few roundings in r, the norms, the reciprocal and the products below.
-// A rejected strip covers no pixel centre.  With the first bound alone,
-// 4096 instances of a 2.1M-triangle mesh took 2.95 ms with strips of 8 and 3.75 with 4; with L 2.70 and 2.95.
 // Provably back-facing from fast window positions p0, p1, p2 (in the strip's vertex order, `even`
 // when that order has the triangle's own winding): each fast position is within the draw's margin m of
 // its snapped position, so the snapped signed area differs from the one of the fast positions by at
@@ -764,6 +747,23 @@ __device__ __forceinline__ bool fast_back_facing(float2 p0, float2 p1, float2 p2
     return A < -(B * (1.0f + 1.0f / 65536.0f));
 }
 
+// Strip spheres.  Before a strip of an interior draw is projected vertex by vertex, it is tested
+// through a bounding sphere (c, r) of its vertices, computed once per work item in object space.
+// For a vertex v = c + d, |d| <= r, with a = (row x'')[0..2] and b = (row w)[0..2] of the draw,
+//   x(v) - x(c) = ((a - x(c) b) . d) / (w(c) + b . d),  so  |x(v) - x(c)| <= |a - x(c) b| r / (w(c) - |b| r)
+// (and likewise y), provided w(c) - |b| r > 0; the test requires at least w(c) / 2.  By the mean value
+// theorem it is also at most L r, where L bounds the gradient |a - x b| / w over the mesh's bounding sphere
+// (radius p, centre at x0, w0, smallest depth w1): |a - x b| <= |a - x0 b| + |x - x0| |b| and |x - x0| <=
+// |a - x0 b| p / w1, so L = |a - x0 b| (1 + p |b| / w1) / w1, which the host computes once per draw
+// (DrawDesc::scale, the larger axis).  A mesh much nearer than it is large makes L loose; the host then
+// leaves scale 0 and the lane evaluates the first bound.  The box x(c) +- the bound, widened by the per-draw
+// slack the host derived for the binary32 error of the projected centre and of the box arithmetic and by the
+// draw's reach (DrawDesc::grow), holds every exact window position of the strip's vertices up to the draw's
+// margin, so the extent test of the union box applies to it.  The radius itself is inflated by 2^-10 in
+// relative terms, which covers the few roundings in r, the norms, the reciprocal and the products below.
+// A rejected strip covers no pixel centre.  With the first bound alone,
+// 4096 instances of a 2.1M-triangle mesh took 2.95 ms with strips of 8 and 3.75 with 4; with L 2.70 and 2.95.
+//
 // What the sphere test reads of a draw and its view (one record, so one batch of loads per draw).
 struct SphereDraw {
     float Rx[4], Ry[4], Aw[4];
@@ -893,7 +893,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
             tail += (uint32_t)__popcll(m);
             if (tail - head >= 64) {
                 wave_lds_sync();
-                drain_ring<STATS>(a, d_views, d_meshes, d_draws, ring, head, 64, tiny_cull, early_out, st);
+                drain_ring<STATS>(a, d_draws, ring, head, 64, tiny_cull, early_out, st);
                 head += 64;
                 wave_lds_sync();
             }
@@ -989,7 +989,7 @@ __global__ void __launch_bounds__(BLOCK) stage1_fast_kernel(RasterArgs a, CURAST
     }
     if (tail != head) {
         wave_lds_sync();
-        drain_ring<STATS>(a, d_views, d_meshes, d_draws, ring, head, tail - head, tiny_cull, early_out, st);
+        drain_ring<STATS>(a, d_draws, ring, head, tail - head, tiny_cull, early_out, st);
     }
     st.flush(a.stats);
 }
@@ -1517,7 +1517,7 @@ __global__ void __launch_bounds__(64) stage1_share_kernel(RasterArgs a, CURAST_D
                     tail += (uint32_t)__popcll(m);
                     if (tail - head >= 64) {
                         __syncthreads();
-                        drain_ring<STATS>(a, d_views, d_meshes, d_draws, s_ring, head, 64, tiny_cull, early_out, st);
+                        drain_ring<STATS>(a, d_meshes, d_draws, s_ring, head, 64, tiny_cull, early_out, st);
                         head += 64;
                         __syncthreads();
                     }
@@ -1528,7 +1528,7 @@ __global__ void __launch_bounds__(64) stage1_share_kernel(RasterArgs a, CURAST_D
     }
     if (tail != head) {
         __syncthreads();
-        drain_ring<STATS>(a, d_views, d_meshes, d_draws, s_ring, head, tail - head, tiny_cull, early_out, st);
+        drain_ring<STATS>(a, d_meshes, d_draws, s_ring, head, tail - head, tiny_cull, early_out, st);
     }
     st.flush(a.stats);
 }

@@ -3,8 +3,9 @@
 // Per frame the host (Sec. 4: "before launching the rasterization stages") computes the draw
 // matrix of every (mesh, instance, view), the int64 exclusive prefix of triangle counts that
 // gives global triangle IDs, culls whole (mesh, instance, view) draws by their bounding sphere,
-// splits the surviving work into stage-1 work items, and uploads these descriptors with one
-// asynchronous copy from pinned memory.  Everything after that (clear, stages 1-3, resolve) is
+// splits the surviving work into stage-1 work items, and hands these descriptors to the frame's first
+// launch as its argument (what does not fit that launch reads from pinned memory; frames of many views and
+// captured graphs copy them from there).  Everything after that (clear, stages 1-3, resolve) is
 // device-side and reads counts from device memory, so a batched frame is captured once into a
 // hipGraph and replayed with new descriptor contents.
 #include <hip/hip_runtime.h>
