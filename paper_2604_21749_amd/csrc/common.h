@@ -22,8 +22,8 @@ constexpr uint32_t kNoPart = 0xFFFFFFFFu;         // end of a tile's list of sta
 // x and y: every edge-function value at a pixel centre of the box (and one step past it) then
 // fits in int32 (|E| <= 2 * ext * (ext + 384) < 2^31).
 constexpr int32_t kSmallExtent = 32768 - 512;
-// Twice-areas in 1/256 px squared of the rule that raster_small explains: 1.5 and 6 px.
-constexpr int32_t kSampleArea = 3 << 16, kReadArea = 12 << 16, kNeverSample = 0x7FFFFFFF;
+// Twice the area, in 1/256 px squared, from which a triangle samples a stored depth (see raster_small): 1.5 px.
+constexpr int32_t kSampleArea = 3 << 16, kNeverSample = 0x7FFFFFFF;
 
 struct FrameHeader {              // 48 B
     uint64_t total_batches;       // stage-1 work items over all segments

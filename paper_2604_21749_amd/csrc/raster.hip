@@ -138,22 +138,23 @@ __device__ __forceinline__ ViewDesc draw_view(const DrawDesc& D)
 //
 // Atomics alone are the faster way to write a fragment until many layers lie over one another: then most
 // of them change nothing, and reading first saves them.  So the lane of a triangle of some size reads one stored
-// depth, in the middle of the box: if that is nearer than all of the triangle (for one of 6 px and more: if the
-// pixel holds anything) it reads before each atomic.  Smaller triangles have too few fragments to gain.
-// Stage 1 with grids of 3 px triangles, alone / always reading / sampled: one layer 24.9 / 29.1 / 25.3 us, 40 layers
+// depth, in the middle of the box, and reads before each atomic if that is nearer than all of the triangle.
+// Smaller triangles have too few fragments to gain.
+// Stage 1 with grids of 3 px triangles, alone / always reading / sampled: one layer 24.9 / 29.1 / 24.3 us, 40 layers
 // front to back 600 / 229 / 239, back to front 594 / 440 / 341; of 0.8 px, 40 layers, 496 / 506 and 498 / 714.
-// Of 12 px: one layer 31.0 / 37.9 / 31.4, 40 layers 923 / 286 / 289 and 905 / 491 / 530.
+// Of 12 px: one layer 31.0 / 37.9 / 31.2, 40 layers 923 / 286 / 292 and 905 / 491 / 672.  (Reading wherever larger
+// triangles find anything stored takes 530 us there, but cost a frame of 25 meshes that barely overlap 44 us for 34.)
 template <bool STATS>
 __device__ __forceinline__ void raster_small(const SmallTri& s, uint64_t id, const ViewDesc& V, bool early_out,
                                              int32_t sample_area, StatAcc<STATS>& st)
 {
     // (without tiny culling the box may be empty and lie past the view)
     if (!early_out && s.area >= sample_area && s.px0 <= s.px1 && s.py0 <= s.py1) {
-        // the depth stored in the middle of the box (NaN of an empty pixel) against the nearest vertex
+        // the depth stored in the middle of the box (of an empty pixel: NaN) against the nearest vertex
         const unsigned long long key =
             gl(V.vis)[(size_t)((s.py0 + s.py1) >> 1) * (size_t)V.W + (size_t)((s.px0 + s.px1) >> 1)];
         const float behind = __uint_as_float((uint32_t)(key >> 36) << 3) * fmaxf(s.zI[0], fmaxf(s.zI[1], s.zI[2]));
-        early_out = s.area >= kReadArea ? !__builtin_isnan(behind) : behind < 1.0f;
+        early_out = behind < 1.0f;
     }
     int32_t sdx[3], sdy[3], row[3], bias[3];
     const int32_t Px0 = 256 * s.px0 + 128, Py0 = 256 * s.py0 + 128;

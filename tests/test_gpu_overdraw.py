@@ -33,7 +33,7 @@ def _layers(cell, layers, order, view, jitter):
 @pytest.mark.parametrize("cell", [0.9, 1.7, 1.8, 3.4, 3.6, 5.3])
 @pytest.mark.parametrize("layers,order,jitter", [(1, "back", 0.0), (9, "back", 0.0), (9, "front", 0.01), (9, "mixed", 0.03)])
 def test_layers(cell, layers, order, jitter):
-    """Triangles just below and above 1.5 and 6 px, one layer and nine, in every order."""
+    """Triangles of less and of more than 1.5 px, one layer and nine, in every order."""
     view = W.View(W.camera((0.0, 0.0, 3.0), (0.0, 0.0, 0.0), aspect=203 / 157), W.NEAR, 203, 157)
     mesh = _layers(cell, layers, order, view, jitter)
     ref = O.rasterize([mesh], view)
