@@ -635,13 +635,15 @@ __device__ __forceinline__ void bwd_pos(const BwdTerms& t, const double (&G)[3],
 }
 
 // Table rows of a pixel's three vertices, inserted where they are new (`first`).  A vertex's row is the low bits
-// of its index; if that is taken, a row among those of its group of 16 vertices, which the group's hash places; from
-// there on odd steps, which reach every row.  Low bits alone, with the steps right after them, made the rows of a
-// lat-long sphere's tile share an eighth of the table wherever a row of the mesh has 2^k + 1 vertices (4.2 M triangles,
-// 130 K pixels, 3 channels and positions 46 us, 28 with the groups; 16.8 M triangles 94 and 48); hashed groups
-// alone cost a mesh of rows that do not collide their neighbourhood (train step of a 10M-triangle scan 290 us, 279
-// with the low bits first).  The three are probed together, a placed one again at its own row, so that a round
-// costs one LDS round trip instead of three.
+// of its index; if that is taken, a row among those of its group of 8 vertices, which the group's hash places; from
+// there on odd steps, which reach every row and are the same for all vertices of a block of the table's size.  Low
+// bits alone, with the steps right after them, made the rows of a lat-long sphere's tile share an eighth of the table
+// wherever a row of the mesh has 2^k + 1 vertices (4.2 M triangles, 130 K pixels, 3 channels and positions 46 us, 28
+// with the groups; 16.8 M triangles 95 and 50); hashed groups alone cost a mesh of rows that do not collide their
+// neighbourhood (train step of a 10M-triangle scan 290 us, 283 with the low bits first).  Steps by the group's hash
+// instead scatter what the blocks hold together: a frame of 38 meshes at 28 triangles a pixel 61 us, 35 with the
+// blocks' steps, 32 without the groups.  The three are probed together, a placed one again at its own row, so that
+// a round costs one LDS round trip instead of three.
 template <class Key>
 __device__ __forceinline__ void bwd_slots(Key* keys, const Key (&key)[3], const uint32_t (&v)[3], uint32_t (&slot)[3],
                                           bool (&first)[3])
@@ -650,10 +652,9 @@ __device__ __forceinline__ void bwd_slots(Key* keys, const Key (&key)[3], const 
     uint32_t move[3], step[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const uint32_t h = (v[k] >> 4) * 2654435761u;
         slot[k] = v[k] & (kBwdSlots - 1);
-        move[k] = ((h >> 26) << 4 | (v[k] & 15)) - slot[k];
-        step[k] = (h >> 13) | 1u;
+        move[k] = (((v[k] >> 3) * 2654435761u >> 25) << 3 | (v[k] & 7)) - slot[k];
+        step[k] = ((v[k] / kBwdSlots) * 2654435761u >> 20) | 1u;
         first[k] = false;
     }
     bool more;
