@@ -23,7 +23,9 @@ constexpr uint32_t kNoPart = 0xFFFFFFFFu;         // end of a tile's list of sta
 // fits in int32 (|E| <= 2 * ext * (ext + 384) < 2^31).
 constexpr int32_t kSmallExtent = 32768 - 512;
 // Twice the area, in 1/256 px squared, from which a triangle samples a stored depth (see raster_small): 1.5 px.
-constexpr int32_t kSampleArea = 3 << 16, kNeverSample = 0x7FFFFFFF;
+// It reads before its atomics where at least kSampleLanes lanes of the wavefront are to: each read costs the whole
+// wavefront a round trip, and saves one atomic per lane.
+constexpr int32_t kSampleArea = 3 << 16, kNeverSample = 0x7FFFFFFF, kSampleLanes = 24;
 
 struct FrameHeader {              // 48 B
     uint64_t total_batches;       // stage-1 work items over all segments
