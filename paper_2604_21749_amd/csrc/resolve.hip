@@ -572,13 +572,13 @@ __global__ void __launch_bounds__(256) resolve_screen_kernel(ScreenArgs a)
 //   lambda_0 = d1 x d2, lambda_1 = d2 x d0, lambda_2 = d0 x d1 with d_k = s_k - pixel centre.
 //
 // Each contribution is rounded once to fp32.  Device-scope fp32 atomics are performed at the memory
-// side, one request per 64-byte sector and instruction, about 16 G requests/s: that rate bounds the
+// side, one request per 64-byte sector and instruction, about 17 G requests/s: that rate bounds the
 // kernels, not the bytes.  So a workgroup adds the contributions of its 16 x 16 pixel tile in LDS first,
 // one table row (C attribute and 3 position components) per vertex, and then issues one atomic per
 // touched row and component, neighbouring lanes on neighbouring components and rows.  A vertex's row is
 // its low bits where it can be, so that the rows of neighbouring vertices, which share sectors, stay neighbours
-// in the table.  1.85 M requests (2.25 M with one staged row per pixel and vertex) for 0.46 M pixels of a
-// 10M-triangle mesh take 105 us, 143 before; 0.2 M pixels of coarser meshes, 4 channels and positions,
+// in the table.  1.80 M requests (2.25 M with one staged row per pixel and vertex) for 0.46 M pixels of a
+// 10M-triangle mesh take 103 us, 143 before; 0.2 M pixels of coarser meshes, 4 channels and positions,
 // 269 us with an atomic per value and 57 here.
 constexpr uint32_t kBwdSlots = 1024;           // at most 3 x 256 vertices per tile: never full
 
